@@ -63,6 +63,8 @@ struct huge2_plan {
   CpArgs cpargs;
   bool grouped;   // grouped / depthwise: the direct kernel over a copy of w
   GrArgs grargs;
+  bool depthwise;  // grouped with one input channel per group: weights packed [tap][c_out]
+  DwArgs dwargs;
   bool quad;      // all-phase form of the stride-2, 4x4, padding-1 layer
   QArgs qargs;
   int bias_div;   // GEMM columns per bias entry (r * s for the 1x1-input product form)
@@ -1100,14 +1102,31 @@ huge2_status create_grouped(huge2_plan** out, const huge2_conv_desc& d, int tran
   g.nhwc = d.layout == HUGE2_NHWC;
   g.act = d.activation;
   std::snprintf(p->kernel_name, sizeof(p->kernel_name), "grouped_kernel g%d", d.groups);
+  // depthwise: whole channel pieces or row chains per thread (DwArgs), unless
+  // the shape exceeds its 32-bit indices
+  if (d.groups == d.c_in) {
+    DwArgs& q = p->dwargs;
+    std::memset(&q, 0, sizeof(q));
+    q.n = d.n, q.cin = d.c_in, q.cout = d.c_out, q.h = d.h, q.w_ = d.w, q.r = d.r, q.s = d.s;
+    q.stride_h = d.stride_h, q.stride_w = d.stride_w, q.pad_h = d.pad_h, q.pad_w = d.pad_w;
+    q.dil_h = d.dil_h, q.dil_w = d.dil_w, q.ho = p->ho, q.wo = p->wo;
+    q.transposed = transposed, q.nhwc = g.nhwc, q.act = d.activation;
+    p->depthwise = depthwise_shape(&q, d.dtype, false) && depthwise_shape(&q, d.dtype, true);
+    if (p->depthwise)
+      std::snprintf(p->kernel_name, sizeof(p->kernel_name), "grouped_kernel depthwise%s v%d",
+                    q.rows3 ? "3" : "", q.vec);
+  }
   huge2_status st = dev_alloc(p, &p->wp, p->wp_bytes);
   if (st != HUGE2_OK) {
     free_buffers(p);
     delete p;
     return st;
   }
-  bool ok = !fault("launch") &&
-            hipMemcpyAsync(p->wp, w, p->wp_bytes, hipMemcpyDeviceToDevice, stream) == hipSuccess;
+  bool ok = !fault("launch");
+  if (ok && p->depthwise)
+    ok = launch_pack_depthwise(w, p->wp, d.dtype, d.c_out, d.r * d.s, stream) == hipSuccess;
+  else if (ok)
+    ok = hipMemcpyAsync(p->wp, w, p->wp_bytes, hipMemcpyDeviceToDevice, stream) == hipSuccess;
   if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
@@ -1566,6 +1585,20 @@ huge2_status gemm_impl(const huge2_plan* p, const void* x, const float* bias, vo
     z.y = y;
     z.act = d.activation;
     if (launch_ztile(z, d.dtype, stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return HUGE2_ERR_HIP;
+    }
+    return HUGE2_OK;
+  }
+  if (p->depthwise) {
+    DwArgs g = p->dwargs;
+    // 16-byte channel pieces need 16-byte aligned tensors: others one channel per thread
+    if (g.vec > 1 && (((uintptr_t)x | (uintptr_t)y) & 15) != 0) depthwise_shape(&g, d.dtype, false);
+    g.x = x;
+    g.w = p->wp;
+    g.bias = bias;
+    g.y = y;
+    if (launch_depthwise(g, d.dtype, stream) != hipSuccess) {
       (void)hipGetLastError();
       return HUGE2_ERR_HIP;
     }

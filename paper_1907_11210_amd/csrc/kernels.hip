@@ -14,64 +14,10 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device.hpp"
 #include "kernels.hpp"
 
 namespace huge2 {
-
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
-constexpr int lcm3(int a, int b, int c) {
-  return (a / gcd_c(a, b) * b) / gcd_c(a / gcd_c(a, b) * b, c) * c;
-}
-// f(integral_constant<int, u>) for u = 0 .. N-1, unrolled at compile time.
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unroll_stages(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>());
-    unroll_stages<N, I + 1>(f);
-  }
-}
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// 16-byte store of output data that nothing in the kernel reads back, with
-// the non-temporal (streaming) cache policy.
-__device__ __forceinline__ void store_stream16(void* p, uint4 v) {
-  const u32x4 t = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(t, (u32x4*)p);
-}
-
-// Workgroups are dealt to the 8 XCDs round-robin (id mod 8).  Map them so
-// that each XCD runs one contiguous run of the work list: neighbouring
-// tiles share input rows and weight blocks, which then stay in that XCD's L2.
-__device__ __forceinline__ int xcd_remap(int b, int g) {
-  const int g8 = (g + 7) >> 3, r = g & 7, x = b & 7, y = b >> 3;
-  if (r == 0 || x < r) return x * g8 + y;
-  return r * g8 + (x - r) * (g8 - 1) + y;
-}
-
-// The epilogue's elementwise function (huge2_activation): 0 none, 1 max(v, 0),
-// 2 tanh(v).  act is uniform over the launch.
-__device__ __forceinline__ float activate(float v, int act) {
-  return act == 1 ? fmaxf(v, 0.f) : act == 2 ? tanhf(v) : v;
-}
-
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-  // v_cvt_pk_bf16_f32: round to nearest even, NaN stays a (quiet) NaN
-  return __builtin_bit_cast(uint16_t, (__bf16)f);
-}
-
-// Two floats to bf16 (round to nearest even) in one 32-bit word, lo in the
-// low half: one v_cvt_pk_bf16_f32 with both sources.
-__device__ __forceinline__ uint32_t pack_bf16x2_rne(float lo, float hi) {
-  typedef float f2_t __attribute__((ext_vector_type(2)));
-  typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
-  const f2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2_t));
-}
 
 // Decomposition of a segment pixel index into image, output and input coordinates.
 struct PixelPos {
@@ -82,9 +28,6 @@ struct PixelPos {
 __device__ __forceinline__ int bias_index(const GemmArgs& a, int ch) {
   const int bc = ch / a.bias_div;
   return a.bias_mod > 0 ? bc % a.bias_mod : bc;
-}
-__device__ __forceinline__ uint32_t fast_div(uint32_t v, uint32_t mul, uint32_t shift) {
-  return (uint32_t)(((uint64_t)v * mul) >> shift);
 }
 __device__ __forceinline__ PixelPos pixel_pos(const SegDev& sg, const uint32_t* ptab, int m) {
   PixelPos p;
@@ -2527,92 +2470,6 @@ hipError_t launch_gather_taps(const GatherArgs& a, int dtype, hipStream_t stream
     hipLaunchKernelGGL(gather_taps_kernel<uint16_t>, dim3(blocks), dim3(256), 0, stream, a);
   else
     hipLaunchKernelGGL(gather_taps_kernel<uint32_t>, dim3(blocks), dim3(256), 0, stream, a);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Grouped and depthwise convolutions (see GrArgs).
-template <typename T>
-__device__ __forceinline__ float to_f32(T v) {
-  if constexpr (std::is_same<T, uint16_t>::value)
-    return __uint_as_float((uint32_t)v << 16);
-  else
-    return __uint_as_float(v);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void grouped_kernel(GrArgs a, long long total) {
-  const T* __restrict__ x = (const T*)a.x;
-  const T* __restrict__ w = (const T*)a.w;
-  const int cig = a.cin / a.groups, cog = a.cout / a.groups;
-  for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (long long)gridDim.x * blockDim.x) {
-    long long t = idx;
-    int k, oh, ow, n;
-    if (a.nhwc) {
-      k = (int)(t % a.cout);
-      t /= a.cout;
-      ow = (int)(t % a.wo);
-      t /= a.wo;
-      oh = (int)(t % a.ho);
-      n = (int)(t / a.ho);
-    } else {
-      ow = (int)(t % a.wo);
-      t /= a.wo;
-      oh = (int)(t % a.ho);
-      t /= a.ho;
-      k = (int)(t % a.cout);
-      n = (int)(t / a.cout);
-    }
-    const int g = k / cog, kg = k - g * cog, c0 = g * cig;
-    float acc = 0.f;
-    for (int m = 0; m < a.r; ++m) {
-      int ih;
-      if (a.transposed) {
-        const int num = oh + a.pad_h - m * a.dil_h;  // = ih * stride_h on the phase's taps
-        if (num < 0 || num % a.stride_h != 0) continue;
-        ih = num / a.stride_h;
-      } else {
-        ih = oh * a.stride_h - a.pad_h + m * a.dil_h;
-      }
-      if (ih < 0 || ih >= a.h) continue;
-      for (int q = 0; q < a.s; ++q) {
-        int iw;
-        if (a.transposed) {
-          const int num = ow + a.pad_w - q * a.dil_w;
-          if (num < 0 || num % a.stride_w != 0) continue;
-          iw = num / a.stride_w;
-        } else {
-          iw = ow * a.stride_w - a.pad_w + q * a.dil_w;
-        }
-        if (iw < 0 || iw >= a.w_) continue;
-        for (int ci = 0; ci < cig; ++ci) {
-          const int c = c0 + ci;
-          const size_t xi = a.nhwc ? (((size_t)n * a.h + ih) * a.w_ + iw) * a.cin + c
-                                   : (((size_t)n * a.cin + c) * a.h + ih) * a.w_ + iw;
-          const size_t wi = a.transposed ? (((size_t)c * cog + kg) * a.r + m) * a.s + q
-                                         : (((size_t)k * cig + ci) * a.r + m) * a.s + q;
-          acc = fmaf(to_f32(x[xi]), to_f32(w[wi]), acc);
-        }
-      }
-    }
-    const float v = activate(acc + (a.bias ? a.bias[k] : 0.f), a.act);
-    if constexpr (std::is_same<T, uint16_t>::value)
-      ((uint16_t*)a.y)[idx] = f32_to_bf16_rne(v);
-    else
-      ((float*)a.y)[idx] = v;
-  }
-}
-
-hipError_t launch_grouped(const GrArgs& a, int dtype, hipStream_t stream) {
-  const long long total = (long long)a.n * a.cout * a.ho * a.wo;
-  const long long want = (total + 255) / 256;
-  const int grid = (int)(want < 1048576 ? want : 1048576);
-  if (total == 0) return hipSuccess;
-  if (dtype == 1)
-    hipLaunchKernelGGL(grouped_kernel<uint16_t>, dim3(grid), dim3(256), 0, stream, a, total);
-  else
-    hipLaunchKernelGGL(grouped_kernel<uint32_t>, dim3(grid), dim3(256), 0, stream, a, total);
   return hipGetLastError();
 }
 

@@ -347,6 +347,37 @@ struct GrArgs {
 };
 hipError_t launch_grouped(const GrArgs& a, int dtype, hipStream_t stream);
 
+// Depthwise convolutions (groups = c_in, a channel multiplier cout / cin),
+// weights packed [tap][cout] by launch_pack_depthwise.  A thread owns `vec`
+// consecutive channels (NHWC, multiplier 1, channels whole 16-byte pieces;
+// otherwise one) of `tr` output rows of one column; the divisors of the thread
+// index, fastest first, are channel groups, columns and row chains (NHWC) or
+// columns, row chains and channels (NCHW).
+struct DwArgs {
+  const void* x;
+  const void* w;
+  const float* bias;
+  void* y;
+  int n, cin, cout, mult, h, w_, r, s, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, ho, wo;
+  int transposed, nhwc, act;
+  int vec;           // channels per thread: 16 bytes' worth, or 1
+  int rows3;         // 1: the 3x3 conv kernel with tr outputs per thread, rows oh0 + j * step
+  int step, ratio;   // step = dil_h / g, ratio = stride_h / g, g = gcd(stride_h, dil_h)
+  uint32_t total;    // threads
+  uint32_t dv[5], mul[5], shift[5];  // three index divisors, step, multiplier
+  // transposed: taps of a phase are mstep apart, their inputs istep apart (per axis)
+  int mstep_h, mstep_w, istep_h, istep_w;
+  uint32_t sh_mul, sh_shift, sw_mul, sw_shift;  // division by the strides
+};
+// Fills the launch fields of `a` from its shape (pieces: 16-byte channel
+// pieces where the shape has them); false when the shape is too large for
+// 32-bit indices (the grouped kernel then takes it).
+bool depthwise_shape(DwArgs* a, int dtype, bool pieces);
+hipError_t launch_depthwise(const DwArgs& a, int dtype, hipStream_t stream);
+// [cout][taps] -> [tap][cout]
+hipError_t launch_pack_depthwise(const void* w, void* wp, int dtype, int cout, int taps,
+                                 hipStream_t stream);
+
 // y[i] = act(bias[ch(i) / bias_div] + sum over s < ksplit, in order, of
 // part[s * stride + i]) in the dtype; ch(i) = (i / hw) % cout for NCHW, i %
 // cout for NHWC.
