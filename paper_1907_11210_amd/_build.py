@@ -16,7 +16,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhuge2.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["plan.cpp", "capi.cpp", "kernels.hip", "grouped.hip"]
+SOURCES = ["plan.cpp", "capi.cpp", "kernels.hip", "grouped.hip", "wavek.hip",
+           "gemm_f32.hip"]
 
 # Packed-FP32 VALU ops are disabled for all device code; the host pass only
 # warns that it does not know the feature.  MFMA accumulators live in

@@ -45,6 +45,7 @@ struct huge2_plan {
   int cin_pad, cout_pad;
   size_t x_bytes, wp_bytes;  // extents of the GEMM's input and packed weights
   int n_works;
+  int all_ap;  // every work's taps are a product of progressions
   void* wp;    // packed weights
   void* meta;  // segments, taps, work list
   void* xs;    // staged input (or null)
@@ -131,6 +132,49 @@ long long count_works(const huge2_conv_desc& d, bool transposed, int class_split
   return works;
 }
 
+// Size of a GEMM as the short-problem rules below see it: 64 x 64 output tiles
+// and K stages (128 bytes of channels) of a tile, the mean over the phases of a
+// transposed conv.  Only fields that the plans of one group share enter, so
+// that branches of one input take the same form.
+struct GemmSize {
+  long long tiles, tiles32, stages;
+};
+GemmSize gemm_size(const huge2_conv_desc& d, bool transposed) {
+  int ho = 1, wo = 1;
+  output_dims(d, transposed, &ho, &wo);
+  const long long kc = 128 / elem_size(d.dtype);
+  const long long cb = (d.c_in + kc - 1) / kc, out = (long long)ho * wo;
+  GemmSize g;
+  const long long rows = ((long long)d.n * out + 63) / 64;
+  g.tiles = rows * ((d.c_out + 63) / 64);
+  g.tiles32 = rows * ((d.c_out + 31) / 32);
+  g.stages = (long long)d.r * d.s * cb;
+  if (transposed) g.stages = std::max(1ll, (g.stages * d.h * d.w + out - 1) / out);
+  return g;
+}
+
+// The wave-K form (wavek_kernel): every layer short enough to be bound by the
+// latency of its stages.  bf16, measured against the shared tiles (us, without
+// and with it; NCHW with the same staging pass in both): 88 -> 104 channels 3x3
+// on 2 x 27 x 20 20.0 / 8.4 (7 tiles, 18 stages), 200 -> 120 on 5 x 33 x 41 28.9
+// / 20.2 (212, 36), 290 -> 419 on 3 x 48 x 29 57.6 / 32.6 (462, 45), 424 -> 200
+// 4x4 on 7 x 39 x 12 37.6 / 29.8 (208, 112).  No operand is shared, so the L2
+// traffic ends it: 256 -> 512 4x4 on 64 x 8 x 8 36.4 / 41.8 (512, 64), 120 -> 363
+// on 8 x 44 x 46 33.7 / 47.9 (1518, 18).  Few tiles with a long K keep the K
+// split across workgroups: 408 -> 99 5x5 28.5 / 35.7 (12, 175).
+bool takes_wavek(const huge2_conv_desc& d, const GemmSize& g) {
+  if ((long long)d.r * d.s > kMaxLdsTaps) return false;
+  if (d.dtype == HUGE2_BF16)
+    return g.tiles <= 512 && g.tiles * g.stages <= 24000 && (g.stages < 64 || g.tiles >= 128);
+  // fp32 (three bf16 parts, against its shared tiles): 264 -> 40 3x3 on
+  // 9 x 41 x 50 87 / 58 (289, 81), 504 -> 456 on 21 x 21 57 / 38 (56, 144), 288
+  // -> 72 4x4 on 45 x 28 x 20 54 / 63 (788, 36), 48 -> 64 on 32 x 21 x 27 25 / 31
+  // (284, 18), 208 -> 40 4x4 on 2 x 7 x 33 27 / 33 (8, 112)
+  if (d.c_out <= 32) return g.tiles32 <= 512 || g.stages > 12;
+  if (d.c_out <= 64 && g.tiles > 256 && g.stages <= 24) return false;
+  return g.tiles <= 512 && (g.stages <= 96 || g.tiles >= 32);
+}
+
 // Tile choice, from measurements on MI355X.  bf16: many pixels and at most
 // 128 output channels take the pipelined 4-wave 128 x 128 tile for
 // transposed convs (the odd-kernel layer 20.4 against 23.0 us, the NHWC
@@ -148,13 +192,34 @@ long long count_works(const huge2_conv_desc& d, bool transposed, int class_split
 // layers).  A pointwise GEMM of at most 64 pixel rows and many channels (a
 // generator's projection of z) takes the 4-wave 32 x 256 tile: two row tiles,
 // and no second K group idling on its single K stage.  Few output channels
-// take the narrow 128 x 32 tile.  fp32 keeps the two-operand-LDS tiles.
+// take the narrow 128 x 32 tile.  The wave-K tile is 32 channels wide up to 36
+// stages (two workgroups per compute unit; 88 -> 400 3x3 on 2 x 18 x 30 12.9
+// against 15.5 us), 64 beyond (half the pixel traffic: 29.8 against 38.0 us for
+// the 112 stages above).
+// fp32 (512 -> 256 4x4 on 64 x 8 x 8, 148 us on the fp32 MFMA): 64 x 128 of two
+// 64 x 64 waves in two K groups 87.7, 128 x 128 in two groups 90.3, in one 89.9
+// us; at most 64 channels 128 x 64; fp32's wave-K tile fits a compute unit once,
+// so it is 32 wide only while every unit gets at most one.
 int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
+  const bool bf16 = d.dtype == HUGE2_BF16;
   int forced = env_int("HUGE2_TILE", -1);
-  if (forced >= 0 && forced < TILE_COUNT) return forced;
+  if (forced >= 0 && forced < TILE_COUNT &&
+      (kTiles[forced].kind == 4 ? (long long)d.r * d.s <= kMaxLdsTaps
+                                : (kTiles[forced].kind == 5) == !bf16))
+    return forced;
+  const GemmSize g = gemm_size(d, transposed);
+  if (takes_wavek(d, g)) {
+    if (d.c_out <= 32) return TILE_WK_64x32;
+    if (bf16) return g.stages <= 36 ? TILE_WK_64x32 : TILE_WK_64x64;
+    return g.tiles32 <= kComputeUnits ? TILE_WK_64x32 : TILE_WK_64x64;
+  }
+  if (!bf16) {
+    if (d.c_out <= 32) return TILE_F32_128x32;
+    if (d.c_out <= 64) return TILE_F32_128x64;
+    return g.tiles >= 8 * kComputeUnits ? TILE_F32_128x128 : TILE_F32_64x128_K2;
+  }
   if (d.c_out <= 32) return TILE_128x32;
   const bool large = count_works(d, transposed, class_split, TILE_128x128) >= 512;
-  if (d.dtype != HUGE2_BF16) return large ? TILE_128x128 : TILE_64x128;
   if (large && d.c_out <= 128) return transposed ? TILE_P3_128x128 : TILE_128x128;
   if (d.r == 1 && d.s == 1 && (long long)d.n * d.h * d.w <= 64 && d.c_out >= 256)
     return TILE_SW_32x256;  // a pointwise GEMM of at most 64 rows (the 1x1-input product form)
@@ -309,6 +374,12 @@ int64_t makespan_of(const std::vector<int64_t>& costs, int cfg) {
   return end;
 }
 
+// Cost of a work of so many stages in the model: the wave-K form runs an
+// eighth of them in a row behind a fixed part of about five.
+int64_t work_cost(int cfg, int64_t stages) {
+  return kTiles[cfg].kind == 4 ? (stages + 7) / 8 + 5 : stages + 2;
+}
+
 int64_t cblocks_of(const huge2_conv_desc& d, int cfg) {
   const int64_t kc = tile_kb(cfg) / elem_size(d.dtype);
   return (d.c_in + kc - 1) / kc;
@@ -322,7 +393,7 @@ int64_t makespan_stages(const huge2_conv_desc& d, const PlanShape& shape, int cf
   for (const huge2_segment& s : shape.segs) {
     const int64_t m = (int64_t)d.n * s.nphase_h * s.nphase_w * s.qn_h * s.qn_w;
     const int64_t works = (m + bm - 1) / bm * ntn;
-    costs.insert(costs.end(), works, (int64_t)s.tap_count * cblocks + 2);
+    costs.insert(costs.end(), works, work_cost(cfg, (int64_t)s.tap_count * cblocks));
   }
   return makespan_of(costs, cfg);
 }
@@ -335,7 +406,7 @@ int64_t makespan_listed(const huge2_conv_desc& d, const ListedShape& ls, int cfg
   std::vector<int64_t> costs;
   for (int img = 0; img < d.n; ++img)
     for (const auto& taps : ls.tile_taps)
-      costs.insert(costs.end(), ntn, (int64_t)taps.size() * cblocks + 2);
+      costs.insert(costs.end(), ntn, work_cost(cfg, (int64_t)taps.size() * cblocks));
   return makespan_of(costs, cfg);
 }
 
@@ -1200,6 +1271,12 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
     if (t.kind == 0)
       std::snprintf(p->kernel_name, sizeof(p->kernel_name), "phase_gemm_kernel %dx%d w%dx%d",
                     t.bm, t.bn, t.pw, t.cw);
+    else if (t.kind == 5)
+      std::snprintf(p->kernel_name, sizeof(p->kernel_name), "phase_gemm_f32_kernel %dx%d k%d",
+                    t.bm, t.bn, t.ksplit);
+    else if (t.kind == 4)
+      std::snprintf(p->kernel_name, sizeof(p->kernel_name), "phase_gemm wavek_kernel %dx%d", t.bm,
+                    t.bn);
     else
       std::snprintf(p->kernel_name, sizeof(p->kernel_name), "phase_gemm%d_kernel %dx%d w%d k%d",
                     t.kind == 3 ? 3 : 2, t.bm, t.bn, t.pw * t.cw, t.ksplit);
@@ -1362,8 +1439,10 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
   bool all_ap = true;
   for (WorkDev& wd : works) {
     work_progressions(taps.data() + wd.tap_begin, wd.tap_count, d.s, &wd);
-    all_ap = all_ap && wd.ap_ntw > 0;
+    // (a work without taps has no step to take)
+    all_ap = all_ap && (wd.ap_ntw > 0 || wd.tap_count == 0);
   }
+  p->all_ap = all_ap;
   if (kTiles[p->cfg].kind == 3 && !all_ap) {
     // the pipelined kernel steps through progressions only: the split-wave
     // kernel of the same tile and packing takes tap lists
@@ -1397,12 +1476,18 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
     const int cblocks = p->cin_pad / bk;
     int max_taps = 1;
     for (const SegDev& sd : segs) max_taps = std::max(max_taps, (int)sd.tap_count);
+    // (a listed segment has no taps of its own, its works do; plans that read
+    // the caller's NHWC input count the segments alone, so that the branches
+    // of a pyramid stay in one K slice and can share a launch)
+    if (p->staged)
+      for (const WorkDev& wd : works) max_taps = std::max(max_taps, (int)wd.tap_count);
     // at least 8 K stages per slice: shorter slices lose more to the second
     // launch than they gain (measured on a 2-block, 1-tap GEMM)
     int ks = std::min({cblocks, kComputeUnits / std::max(1, (int)works.size()), 8,
                        std::max(1, cblocks * max_taps / 8)});
     const int forced = env_int("HUGE2_SPLITK", -1);
     if (forced >= 1) ks = std::min(forced, cblocks);
+    if (kTiles[p->cfg].kind == 4) ks = 1;  // its waves split K already
     const size_t ny = (size_t)d.n * d.c_out * p->ho * p->wo;
     while (ks > 1 && (ks * ny * 4 > ((size_t)1 << 28) || ny >= ((size_t)1 << 31))) --ks;
     p->ksplit = std::max(1, ks);
@@ -1450,7 +1535,9 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
   const size_t work_b = works.size() * sizeof(WorkDev);
   const size_t ptab_b = ptab.size() * sizeof(uint32_t);
   const size_t meta_b = seg_b + tap_b + work_b + ptab_b;
-  const size_t wp_b = (size_t)d.r * d.s * p->cout_pad * p->cin_pad * esz;
+  // fp32 weights of the wave-K and three-part forms: three bf16 planes
+  const bool split_w = kTiles[p->cfg].kind >= 4 && d.dtype == HUGE2_F32;
+  const size_t wp_b = (size_t)d.r * d.s * p->cout_pad * p->cin_pad * (split_w ? 6 : esz);
   const size_t xs_b = p->staged ? p->x_bytes : 0;
   p->wp_bytes = wp_b;
 
@@ -1478,7 +1565,10 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
   bool ok = !fault("launch");
   if (ok && meta_b)
     ok = hipMemcpyAsync(p->meta, host.data(), meta_b, hipMemcpyHostToDevice, stream) == hipSuccess;
-  if (ok)
+  if (ok && split_w)
+    ok = launch_pack_split(w, p->wp, tr, d.c_in, d.c_out, d.r, d.s, p->cin_pad, p->cout_pad,
+                           p->prod_rs, stream) == hipSuccess;
+  else if (ok)
     ok = launch_pack_weights(w, p->wp, d.dtype, tr, d.c_in, d.c_out, d.r, d.s, p->cin_pad,
                              p->cout_pad, kTiles[p->cfg].kind != 0 ? kPackKB : 0, stream,
                              p->prod_rs) == hipSuccess;
@@ -1682,6 +1772,8 @@ huge2_status gemm_impl(const huge2_plan* p, const void* x, const float* bias, vo
   a.w = d.w;
   a.cin = p->c_stride;
   a.ks = d.s;
+  a.nslots = d.r * d.s;
+  a.all_ap = p->all_ap;
   a.x_bytes = (uint32_t)p->x_bytes;
   a.wp_bytes = (uint32_t)p->wp_bytes;
   a.cin_pad = p->cin_pad;
@@ -2175,6 +2267,9 @@ huge2_status group_execute(const huge2_group* g, const void* x, const float* con
   a.w = d.w;
   a.cin = p->c_stride;
   a.ks = d.s;
+  a.nslots = d.r * d.s;
+  a.all_ap = 1;
+  for (int i = 0; i < g->count; ++i) a.all_ap &= g->plans[i]->all_ap;
   a.x_bytes = (uint32_t)p->x_bytes;
   a.wp_bytes = (uint32_t)p->wp_bytes;
   a.cin_pad = p->cin_pad;

@@ -5,6 +5,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "kernels.hpp"
+
 namespace huge2 {
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -71,6 +73,176 @@ __device__ __forceinline__ float to_f32(T v) {
     return __uint_as_float((uint32_t)v << 16);
   else
     return __uint_as_float(v);
+}
+
+// Decomposition of a segment pixel index into image, output and input coordinates.
+struct PixelPos {
+  int img, oh, ow, ih, iw;
+};
+// Bias entry of GEMM column ch (the 1x1-input product forms: bias_div
+// columns per entry, or entries repeating every bias_mod columns).
+__device__ __forceinline__ int bias_index(const GemmArgs& a, int ch) {
+  const int bc = ch / a.bias_div;
+  return a.bias_mod > 0 ? bc % a.bias_mod : bc;
+}
+__device__ __forceinline__ PixelPos pixel_pos(const SegDev& sg, const uint32_t* ptab, int m) {
+  PixelPos p;
+  uint32_t j = (uint32_t)m;
+  if (sg.ptab >= 0) {
+    const uint32_t img = fast_div(j, sg.div_mul[2], sg.div_shift[2]);
+    const uint32_t e = ptab[sg.ptab + (int)(j - img * (uint32_t)sg.per_img)];
+    p.img = (int)img;
+    p.oh = (int)(e >> 16);
+    p.ow = (int)(e & 0xffffu);
+    p.ih = sg.in0_h + p.oh;
+    p.iw = sg.in0_w + p.ow;
+    return p;
+  }
+  uint32_t t = fast_div(j, sg.div_mul[0], sg.div_shift[0]);
+  const int a_w = (int)(j - t * (uint32_t)sg.qn_w);
+  j = t;
+  t = fast_div(j, sg.div_mul[1], sg.div_shift[1]);
+  const int a_h = (int)(j - t * (uint32_t)sg.qn_h);
+  j = t;
+  t = fast_div(j, sg.div_mul[2], sg.div_shift[2]);
+  const uint32_t iph = j - t * (uint32_t)sg.nphase;
+  p.img = (int)t;
+  const uint32_t iph_h = fast_div(iph, sg.div_mul[3], sg.div_shift[3]);
+  const int iph_w = (int)(iph - iph_h * (uint32_t)sg.nphase_w);
+  const int qh = sg.q0_h + a_h, qw = sg.q0_w + a_w;
+  p.oh = sg.phase0_h + (int)iph_h + sg.out_step_h * qh;
+  p.ow = sg.phase0_w + iph_w + sg.out_step_w * qw;
+  p.ih = sg.in0_h + sg.in_dphase_h * (int)iph_h + sg.in_step_h * qh;
+  p.iw = sg.in0_w + sg.in_dphase_w * iph_w + sg.in_step_w * qw;
+  return p;
+}
+
+// Epilogue: bias, rounding, and the scatter of a wave's TP x TC blocks of
+// 32 x 32 results (pixels from pix0, output channels from ch0) to the
+// interleaved output positions of their phase.  32x32 MFMA result layout:
+// lane l holds column l % 32 and rows 8*(r/4) + 4*(l/32) + (r%4), r = 0..15.
+// NCHW output puts pixels on the columns (a channel's stores coalesce along
+// the lanes); NHWC output puts pixels on the rows.
+// sb: bias by output channel (sb[ch], staged in LDS, zeros without bias):
+// reading it from global memory between the stores would make every load
+// wait for the stores issued before it.
+template <bool BF16, bool NCHW_OUT, int TP, int TC>
+__device__ __forceinline__ void store_tile(const GemmArgs& a, const SegDev& sg, int m_end, void* y,
+                                           const f32x16 (&acc)[TP][TC], int pix0, int ch0,
+                                           int lane, const float* sb) {
+  const int hw_o = a.ho * a.wo;
+  // the bias values are read from LDS up front: an LDS read between the
+  // global stores would wait for its own latency element by element
+  if constexpr (!NCHW_OUT) {
+    float bv[TC];
+#pragma unroll
+    for (int j = 0; j < TC; ++j) {
+      const int ch = ch0 + 32 * j + (lane & 31);
+      bv[j] = ch < a.cout ? sb[ch] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      // the 16 rows' positions before their stores: a table lookup issued
+      // behind stores would wait for them (the memory counter is in order)
+      int pixr[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = pix0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const PixelPos p = pixel_pos(sg, a.ptab, m < m_end ? m : pix0);
+        pixr[r] = m < m_end ? (p.img * a.ho + p.oh) * a.wo + p.ow : -1;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int pix = pixr[r];
+        if (pix < 0) continue;
+#pragma unroll
+        for (int j = 0; j < TC; ++j) {
+          const int ch = ch0 + 32 * j + (lane & 31);
+          if (ch >= a.cout) continue;
+          const float v = activate(acc[i][j][r] + bv[j], a.act);
+          const size_t off = (size_t)pix * a.cout + ch;
+          if constexpr (BF16)
+            ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
+          else
+            ((float*)y)[off] = v;
+        }
+      }
+    }
+  } else {
+    size_t base[TP];
+    bool ok[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+      const int m = pix0 + 32 * i + (lane & 31);
+      ok[i] = m < m_end;
+      const PixelPos p = pixel_pos(sg, a.ptab, ok[i] ? m : pix0);
+      base[i] = (size_t)p.img * a.cout * hw_o + (size_t)p.oh * a.wo + p.ow;
+    }
+#pragma unroll
+    for (int j = 0; j < TC; ++j) {
+      float bv[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int ch = ch0 + 32 * j + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        bv[r] = ch < a.cout ? sb[ch] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < TP; ++i) {
+        if (!ok[i]) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int ch = ch0 + 32 * j + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          if (ch >= a.cout) continue;
+          const float v = activate(acc[i][j][r] + bv[r], a.act);
+          const size_t off = base[i] + (size_t)ch * hw_o;
+          if constexpr (BF16)
+            ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
+          else
+            ((float*)y)[off] = v;
+        }
+      }
+    }
+  }
+}
+
+// Eight floats as three bf16 parts, x = x1 + x2 + x3: each part rounds what the
+// ones before it left over, to nearest even, so with 8 bits a part the sum
+// holds all 24 (barring underflow), and part k is at most 2^-9k of x.
+struct Split8 {
+  uint4 p[3];
+};
+__device__ __forceinline__ Split8 split8(uint4 lo, uint4 hi) {
+  const uint32_t u[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(u[e]);
+  Split8 s;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      w[e] = pack_bf16x2_rne(v[2 * e], v[2 * e + 1]);
+      if (k < 2) {
+        v[2 * e] -= __uint_as_float(w[e] << 16);
+        v[2 * e + 1] -= __uint_as_float(w[e] & 0xffff0000u);
+      }
+    }
+    s.p[k] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  return s;
+}
+
+// Weight (tap block at byte slot_b, channel ch, input channel c) of the
+// three-part fp32 packing: the exact sum of its parts.
+__device__ __forceinline__ float split_weight(const char* wp, size_t plane_b, uint32_t slot_b,
+                                              int cin_pad, int ch, int c) {
+  const size_t at = slot_b + ((size_t)(ch >> 5) * (cin_pad >> 5) + (c >> 5)) * 2048u +
+                    ((c >> 3) & 1) * 1024u + (((c >> 4) & 1) * 32 + (ch & 31)) * 16u + (c & 7) * 2u;
+  float v = 0.f;
+  for (int p = 2; p >= 0; --p)
+    v += __uint_as_float((uint32_t) * (const uint16_t*)(wp + p * plane_b + at) << 16);
+  return v;
 }
 
 }  // namespace huge2

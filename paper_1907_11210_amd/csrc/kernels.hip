@@ -19,136 +19,6 @@
 
 namespace huge2 {
 
-// Decomposition of a segment pixel index into image, output and input coordinates.
-struct PixelPos {
-  int img, oh, ow, ih, iw;
-};
-// Bias entry of GEMM column ch (the 1x1-input product forms: bias_div
-// columns per entry, or entries repeating every bias_mod columns).
-__device__ __forceinline__ int bias_index(const GemmArgs& a, int ch) {
-  const int bc = ch / a.bias_div;
-  return a.bias_mod > 0 ? bc % a.bias_mod : bc;
-}
-__device__ __forceinline__ PixelPos pixel_pos(const SegDev& sg, const uint32_t* ptab, int m) {
-  PixelPos p;
-  uint32_t j = (uint32_t)m;
-  if (sg.ptab >= 0) {
-    const uint32_t img = fast_div(j, sg.div_mul[2], sg.div_shift[2]);
-    const uint32_t e = ptab[sg.ptab + (int)(j - img * (uint32_t)sg.per_img)];
-    p.img = (int)img;
-    p.oh = (int)(e >> 16);
-    p.ow = (int)(e & 0xffffu);
-    p.ih = sg.in0_h + p.oh;
-    p.iw = sg.in0_w + p.ow;
-    return p;
-  }
-  uint32_t t = fast_div(j, sg.div_mul[0], sg.div_shift[0]);
-  const int a_w = (int)(j - t * (uint32_t)sg.qn_w);
-  j = t;
-  t = fast_div(j, sg.div_mul[1], sg.div_shift[1]);
-  const int a_h = (int)(j - t * (uint32_t)sg.qn_h);
-  j = t;
-  t = fast_div(j, sg.div_mul[2], sg.div_shift[2]);
-  const uint32_t iph = j - t * (uint32_t)sg.nphase;
-  p.img = (int)t;
-  const uint32_t iph_h = fast_div(iph, sg.div_mul[3], sg.div_shift[3]);
-  const int iph_w = (int)(iph - iph_h * (uint32_t)sg.nphase_w);
-  const int qh = sg.q0_h + a_h, qw = sg.q0_w + a_w;
-  p.oh = sg.phase0_h + (int)iph_h + sg.out_step_h * qh;
-  p.ow = sg.phase0_w + iph_w + sg.out_step_w * qw;
-  p.ih = sg.in0_h + sg.in_dphase_h * (int)iph_h + sg.in_step_h * qh;
-  p.iw = sg.in0_w + sg.in_dphase_w * iph_w + sg.in_step_w * qw;
-  return p;
-}
-
-// Epilogue: bias, rounding, and the scatter of a wave's TP x TC blocks of
-// 32 x 32 results (pixels from pix0, output channels from ch0) to the
-// interleaved output positions of their phase.  32x32 MFMA result layout:
-// lane l holds column l % 32 and rows 8*(r/4) + 4*(l/32) + (r%4), r = 0..15.
-// NCHW output puts pixels on the columns (a channel's stores coalesce along
-// the lanes); NHWC output puts pixels on the rows.
-// sb: bias by output channel (sb[ch], staged in LDS, zeros without bias):
-// reading it from global memory between the stores would make every load
-// wait for the stores issued before it.
-template <bool BF16, bool NCHW_OUT, int TP, int TC>
-__device__ __forceinline__ void store_tile(const GemmArgs& a, const SegDev& sg, int m_end, void* y,
-                                           const f32x16 (&acc)[TP][TC], int pix0, int ch0,
-                                           int lane, const float* sb) {
-  const int hw_o = a.ho * a.wo;
-  // the bias values are read from LDS up front: an LDS read between the
-  // global stores would wait for its own latency element by element
-  if constexpr (!NCHW_OUT) {
-    float bv[TC];
-#pragma unroll
-    for (int j = 0; j < TC; ++j) {
-      const int ch = ch0 + 32 * j + (lane & 31);
-      bv[j] = ch < a.cout ? sb[ch] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      // the 16 rows' positions before their stores: a table lookup issued
-      // behind stores would wait for them (the memory counter is in order)
-      int pixr[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = pix0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const PixelPos p = pixel_pos(sg, a.ptab, m < m_end ? m : pix0);
-        pixr[r] = m < m_end ? (p.img * a.ho + p.oh) * a.wo + p.ow : -1;
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int pix = pixr[r];
-        if (pix < 0) continue;
-#pragma unroll
-        for (int j = 0; j < TC; ++j) {
-          const int ch = ch0 + 32 * j + (lane & 31);
-          if (ch >= a.cout) continue;
-          const float v = activate(acc[i][j][r] + bv[j], a.act);
-          const size_t off = (size_t)pix * a.cout + ch;
-          if constexpr (BF16)
-            ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
-          else
-            ((float*)y)[off] = v;
-        }
-      }
-    }
-  } else {
-    size_t base[TP];
-    bool ok[TP];
-#pragma unroll
-    for (int i = 0; i < TP; ++i) {
-      const int m = pix0 + 32 * i + (lane & 31);
-      ok[i] = m < m_end;
-      const PixelPos p = pixel_pos(sg, a.ptab, ok[i] ? m : pix0);
-      base[i] = (size_t)p.img * a.cout * hw_o + (size_t)p.oh * a.wo + p.ow;
-    }
-#pragma unroll
-    for (int j = 0; j < TC; ++j) {
-      float bv[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ch = ch0 + 32 * j + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        bv[r] = ch < a.cout ? sb[ch] : 0.f;
-      }
-#pragma unroll
-      for (int i = 0; i < TP; ++i) {
-        if (!ok[i]) continue;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int ch = ch0 + 32 * j + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (ch >= a.cout) continue;
-          const float v = activate(acc[i][j][r] + bv[r], a.act);
-          const size_t off = base[i] + (size_t)ch * hw_o;
-          if constexpr (BF16)
-            ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
-          else
-            ((float*)y)[off] = v;
-        }
-      }
-    }
-  }
-}
-
 // NHWC bf16 epilogue through LDS, for tiles whose output rows are whole
 // 16-byte pieces (C_out a multiple of 8, a 16-byte aligned output).  The
 // waves write their results (bias, activation, rounding) into a [BM][BN]
@@ -226,10 +96,10 @@ __device__ __forceinline__ void store_rows_nhwc(const GemmArgs& a, int n0, void*
 // NCHW output puts pixels on MFMA columns (lanes hold consecutive pixels, so
 // a channel's stores coalesce); NHWC output puts pixels on MFMA rows (lanes
 // hold consecutive channels of a pixel).
-template <bool BF16, int BM, int BN, int PWAVES, int CWAVES, int KB, int DEPTH, bool NCHW_OUT>
+template <int BM, int BN, int PWAVES, int CWAVES, int KB, int DEPTH, bool NCHW_OUT>
 __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmArgs a) {
   constexpr int NT = PWAVES * CWAVES * 64;  // threads per workgroup
-  constexpr int ESZ = BF16 ? 2 : 4;
+  constexpr int ESZ = 2;
   constexpr int KC = KB / ESZ;    // K elements per stage
   constexpr int VE = 16 / ESZ;    // elements per 16-byte chunk
   constexpr int CPR = KB / 16;    // 16-byte chunks per row
@@ -238,7 +108,7 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
   constexpr int TP = WP / 32, TC = WC / 32;
   constexpr int A_LD = BM * CPR / NT;
   constexpr int B_LD = (BN * CPR + NT - 1) / NT;  // the last may be partial
-  constexpr int KSUB = BF16 ? KB / 32 : KB / 8;  // MFMAs per operand pair and stage
+  constexpr int KSUB = KB / 32;  // MFMAs per operand pair and stage
   static_assert(BM * CPR % NT == 0, "whole A loads per thread");
   static_assert(TP >= 1 && TC >= 1 && WP % 32 == 0 && WC % 32 == 0, "32x32 MFMA blocks");
   constexpr int STAGE_B = (BM + BN) * ROWB;
@@ -405,49 +275,24 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
   auto compute = [&](int buf) {
     const char* as = smem + buf * STAGE_B + (wp_i * WP + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
     const char* bs = smem + buf * STAGE_B + (BM + wc_i * WC + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
-    if constexpr (BF16) {
 #pragma unroll
-      for (int t = 0; t < KSUB; ++t) {
-        uint4 fp[TP], fc[TC];
+    for (int t = 0; t < KSUB; ++t) {
+      uint4 fp[TP], fc[TC];
 #pragma unroll
-        for (int i = 0; i < TP; ++i) fp[i] = *(const uint4*)(as + 32 * i * ROWB + 16 * t);
+      for (int i = 0; i < TP; ++i) fp[i] = *(const uint4*)(as + 32 * i * ROWB + 16 * t);
 #pragma unroll
-        for (int j = 0; j < TC; ++j) fc[j] = *(const uint4*)(bs + 32 * j * ROWB + 16 * t);
+      for (int j = 0; j < TC; ++j) fc[j] = *(const uint4*)(bs + 32 * j * ROWB + 16 * t);
 #pragma unroll
-        for (int i = 0; i < TP; ++i)
+      for (int i = 0; i < TP; ++i)
 #pragma unroll
-          for (int j = 0; j < TC; ++j) {
-            const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
-            const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
-            if constexpr (NCHW_OUT)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
-          }
-      }
-    } else {
-#pragma unroll
-      for (int t4 = 0; t4 < KSUB / 4; ++t4) {
-        uint4 fp[TP], fc[TC];
-#pragma unroll
-        for (int i = 0; i < TP; ++i) fp[i] = *(const uint4*)(as + 32 * i * ROWB + 16 * t4);
-#pragma unroll
-        for (int j = 0; j < TC; ++j) fc[j] = *(const uint4*)(bs + 32 * j * ROWB + 16 * t4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < TP; ++i)
-#pragma unroll
-            for (int j = 0; j < TC; ++j) {
-              const uint32_t bp = e == 0 ? fp[i].x : e == 1 ? fp[i].y : e == 2 ? fp[i].z : fp[i].w;
-              const uint32_t bc = e == 0 ? fc[j].x : e == 1 ? fc[j].y : e == 2 ? fc[j].z : fc[j].w;
-              const float vp = __uint_as_float(bp), vc = __uint_as_float(bc);
-              if constexpr (NCHW_OUT)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vc, vp, acc[i][j], 0, 0, 0);
-              else
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp, vc, acc[i][j], 0, 0, 0);
-            }
-      }
+        for (int j = 0; j < TC; ++j) {
+          const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
+          const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
+          if constexpr (NCHW_OUT)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
+        }
     }
   };
 
@@ -494,7 +339,7 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
     store_tile<false, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.part + (size_t)wk.ks * a.part_stride, acc,
                                         wk.m0 + wp_i * WP, wk.n0 + wc_i * WC, lane, s_bias - wk.n0);
   } else {
-    store_tile<BF16, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0 + wp_i * WP,
+    store_tile<true, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0 + wp_i * WP,
                                        wk.n0 + wc_i * WC, lane, s_bias - wk.n0);
   }
 }
@@ -511,11 +356,11 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
 // form above, which is what bounds the MFMA rate at small wave tiles.
 // DEPTH register buffers hold the stages in flight; the loop is unrolled by
 // U = lcm(DEPTH, 2) so that every buffer index is a compile-time constant.
-template <bool BF16, int BM, int BN, int W, int KB, int DEPTH, bool SHARE_A, int KS, bool NCHW_OUT>
+template <int BM, int BN, int W, int KB, int DEPTH, bool SHARE_A, int KS, bool NCHW_OUT>
 __global__ __launch_bounds__(W * 64 * KS) void phase_gemm2_kernel(GemmArgs a) {
   constexpr int NTA = W * 64 * KS;  // threads of the workgroup
   constexpr int NT = W * 64;        // threads of one K group
-  constexpr int ESZ = BF16 ? 2 : 4;
+  constexpr int ESZ = 2;
   constexpr int KC = KB / ESZ;    // K elements per stage
   constexpr int VE = 16 / ESZ;    // elements per 16-byte chunk
   constexpr int CPR = KB / 16;    // 16-byte chunks per row and stage
@@ -736,34 +581,17 @@ __global__ __launch_bounds__(W * 64 * KS) void phase_gemm2_kernel(GemmArgs a) {
       for (int i = 0; i < TP; ++i) fp[i] = SHARE_A ? fs[i] : R.d[i][c];
 #pragma unroll
       for (int j = 0; j < TC; ++j) fc[j] = SHARE_A ? R.d[j][c] : fs[j];
-      if constexpr (BF16) {
 #pragma unroll
-        for (int i = 0; i < TP; ++i)
+      for (int i = 0; i < TP; ++i)
 #pragma unroll
-          for (int j = 0; j < TC; ++j) {
-            const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
-            const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
-            if constexpr (NCHW_OUT)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
-          }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < TP; ++i)
-#pragma unroll
-            for (int j = 0; j < TC; ++j) {
-              const uint32_t bp = e == 0 ? fp[i].x : e == 1 ? fp[i].y : e == 2 ? fp[i].z : fp[i].w;
-              const uint32_t bc = e == 0 ? fc[j].x : e == 1 ? fc[j].y : e == 2 ? fc[j].z : fc[j].w;
-              const float vp = __uint_as_float(bp), vc = __uint_as_float(bc);
-              if constexpr (NCHW_OUT)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vc, vp, acc[i][j], 0, 0, 0);
-              else
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp, vc, acc[i][j], 0, 0, 0);
-            }
-      }
+        for (int j = 0; j < TC; ++j) {
+          const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
+          const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
+          if constexpr (NCHW_OUT)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
+        }
     }
   };
 
@@ -815,7 +643,7 @@ __global__ __launch_bounds__(W * 64 * KS) void phase_gemm2_kernel(GemmArgs a) {
     store_tile<false, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.part + (size_t)wk.ks * a.part_stride, acc,
                                         pix0, ch0, lane, s_bias - wk.n0);
   } else {
-    store_tile<BF16, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, pix0, ch0, lane,
+    store_tile<true, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, pix0, ch0, lane,
                                        s_bias - wk.n0);
   }
 }
@@ -838,10 +666,10 @@ __global__ __launch_bounds__(W * 64 * KS) void phase_gemm2_kernel(GemmArgs a) {
 //    kernel).
 // The loop is unrolled by U = 6 (a multiple of the 3 LDS buffers and of DA
 // and DB), so every buffer index is a compile-time constant.
-template <bool BF16, int BM, int BN, int W, int KB, int DA, int DB, int KS, bool NCHW_OUT>
+template <int BM, int BN, int W, int KB, int DA, int DB, int KS, bool NCHW_OUT>
 __global__ __launch_bounds__(W * 64 * KS, 2) void phase_gemm3_kernel(GemmArgs a) {
   constexpr int NTA = W * 64 * KS, NT = W * 64;
-  constexpr int ESZ = BF16 ? 2 : 4;
+  constexpr int ESZ = 2;
   constexpr int KC = KB / ESZ;   // K elements per stage
   constexpr int VE = 16 / ESZ;   // elements per 16-byte chunk
   constexpr int CPR = KB / 16;   // 16-byte chunks per row and stage
@@ -858,7 +686,7 @@ __global__ __launch_bounds__(W * 64 * KS, 2) void phase_gemm3_kernel(GemmArgs a)
   constexpr int STAGE_B = BM * ROWB;
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int ACC_B = KS > 1 ? W * 64 * TP * TC * 16 * 4 : 0;
-  constexpr bool ROWS_OUT = BF16 && !NCHW_OUT && KS == 1;  // row epilogue through LDS
+  constexpr bool ROWS_OUT = !NCHW_OUT && KS == 1;  // row epilogue through LDS
   constexpr int EPI_B = ROWS_OUT ? BM * (2 * BN + 16) : 0;
   constexpr int SMEM_B0 = KS * NB * STAGE_B > ACC_B ? KS * NB * STAGE_B : ACC_B;
   constexpr int SMEM_B = SMEM_B0 > EPI_B ? SMEM_B0 : EPI_B;
@@ -1007,35 +835,17 @@ __global__ __launch_bounds__(W * 64 * KS, 2) void phase_gemm3_kernel(GemmArgs a)
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   auto mfma_chunk = [&](const uint4 (&fp)[TP], const RegB& R, int c) {
-    if constexpr (BF16) {
 #pragma unroll
-      for (int i = 0; i < TP; ++i)
+    for (int i = 0; i < TP; ++i)
 #pragma unroll
-        for (int j = 0; j < TC; ++j) {
-          const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
-          const bf16x8 vc = __builtin_bit_cast(bf16x8, R.v[j][c]);
-          if constexpr (NCHW_OUT)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
-          else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
-        }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < TP; ++i)
-#pragma unroll
-          for (int j = 0; j < TC; ++j) {
-            const uint4 x4 = fp[i], w4 = R.v[j][c];
-            const uint32_t bp = e == 0 ? x4.x : e == 1 ? x4.y : e == 2 ? x4.z : x4.w;
-            const uint32_t bc = e == 0 ? w4.x : e == 1 ? w4.y : e == 2 ? w4.z : w4.w;
-            const float vp = __uint_as_float(bp), vc = __uint_as_float(bc);
-            if constexpr (NCHW_OUT)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vc, vp, acc[i][j], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp, vc, acc[i][j], 0, 0, 0);
-          }
-    }
+      for (int j = 0; j < TC; ++j) {
+        const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
+        const bf16x8 vc = __builtin_bit_cast(bf16x8, R.v[j][c]);
+        if constexpr (NCHW_OUT)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
+        else
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
+      }
   };
 
   // Prologue: stages 0 and 1 in LDS buffers 0 and 1, stages 2 and 3 in the
@@ -1142,46 +952,49 @@ __global__ __launch_bounds__(W * 64 * KS, 2) void phase_gemm3_kernel(GemmArgs a)
     store_tile<false, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.part + (size_t)wk.ks * a.part_stride, acc,
                                         wk.m0, ch0, lane, s_bias - wk.n0);
   } else {
-    store_tile<BF16, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0, ch0, lane,
+    store_tile<true, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0, ch0, lane,
                                        s_bias - wk.n0);
   }
 }
 
-template <bool BF16, bool NCHW_OUT, int CFG>
+template <bool NCHW_OUT, int CFG>
 static void launch_one(const GemmArgs& a, hipStream_t stream) {
   constexpr TileShape t = kTiles[CFG];
   if constexpr (t.kind == 0)
-    hipLaunchKernelGGL((phase_gemm_kernel<BF16, t.bm, t.bn, t.pw, t.cw, t.kb, t.depth, NCHW_OUT>),
+    hipLaunchKernelGGL((phase_gemm_kernel<t.bm, t.bn, t.pw, t.cw, t.kb, t.depth, NCHW_OUT>),
                        dim3(a.n_works), dim3(t.pw * t.cw * 64), 0, stream, a);
   else if constexpr (t.kind == 3)
-    hipLaunchKernelGGL((phase_gemm3_kernel<BF16, t.bm, t.bn, t.pw * t.cw, t.kb, t.depth % 10,
+    hipLaunchKernelGGL((phase_gemm3_kernel<t.bm, t.bn, t.pw * t.cw, t.kb, t.depth % 10,
                                            t.depth / 10, t.ksplit, NCHW_OUT>),
                        dim3(a.n_works), dim3(t.pw * t.cw * t.ksplit * 64), 0, stream, a);
   else
-    hipLaunchKernelGGL((phase_gemm2_kernel<BF16, t.bm, t.bn, t.pw * t.cw, t.kb, t.depth,
-                                           t.kind == 1, t.ksplit, NCHW_OUT>),
+    hipLaunchKernelGGL((phase_gemm2_kernel<t.bm, t.bn, t.pw * t.cw, t.kb, t.depth, t.kind == 1,
+                                           t.ksplit, NCHW_OUT>),
                        dim3(a.n_works), dim3(t.pw * t.cw * t.ksplit * 64), 0, stream, a);
 }
 
-template <bool BF16, bool NCHW_OUT, int CFG = 0>
+template <bool NCHW_OUT, int CFG = 0>
 static hipError_t launch_cfg(const GemmArgs& a, int cfg, hipStream_t stream) {
   if constexpr (CFG < TILE_COUNT) {
-    if (cfg == CFG) {
-      launch_one<BF16, NCHW_OUT, CFG>(a, stream);
-      return hipGetLastError();
+    if constexpr (kTiles[CFG].kind < 4) {
+      if (cfg == CFG) {
+        launch_one<NCHW_OUT, CFG>(a, stream);
+        return hipGetLastError();
+      }
     }
-    return launch_cfg<BF16, NCHW_OUT, CFG + 1>(a, cfg, stream);
+    return launch_cfg<NCHW_OUT, CFG + 1>(a, cfg, stream);
   } else {
     return hipErrorInvalidValue;
   }
 }
 
+// (the wave-K tiles take both dtypes, the three-part ones fp32, the rest bf16)
 hipError_t launch_phase_gemm(const GemmArgs& a, int dtype, int cfg, bool nchw_out,
                              hipStream_t stream) {
   if (a.n_works <= 0) return hipSuccess;
-  if (dtype == 1)
-    return nchw_out ? launch_cfg<true, true>(a, cfg, stream) : launch_cfg<true, false>(a, cfg, stream);
-  return nchw_out ? launch_cfg<false, true>(a, cfg, stream) : launch_cfg<false, false>(a, cfg, stream);
+  if (kTiles[cfg].kind == 4) return launch_wavek(a, dtype, kTiles[cfg].bn, nchw_out, stream);
+  if (dtype != 1) return launch_gemm_f32(a, cfg, nchw_out, stream);
+  return nchw_out ? launch_cfg<true>(a, cfg, stream) : launch_cfg<false>(a, cfg, stream);
 }
 
 // ---------------------------------------------------------------------------

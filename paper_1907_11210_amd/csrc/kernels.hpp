@@ -90,6 +90,8 @@ struct GemmArgs {
   int32_t cout, cout_pad;
   int32_t ho, wo;
   int32_t ks;  // kernel width s: weight slot of tap (kh, kw) = kh * ks + kw
+  int32_t nslots;  // r * s
+  int32_t all_ap;  // 1: every work's taps are a product of progressions (ap_ntw > 0)
   int32_t bias_div, bias_mod;
   // K split across workgroups: ksplit > 1 writes each slice's fp32 partial
   // tile (no bias, no activation) to part + slice * part_stride, in the
@@ -111,6 +113,8 @@ struct GemmArgs {
 // kind 0: both operands through LDS, PW x CW waves of (BM/PW) x (BN/CW).
 // kind 1: split-wave form, the pixel tile through LDS, CW waves each loading
 //         BN/CW weight rows itself (PW = 1) from lane-ordered packed weights.
+// kind 4: wave-K form (wavek_kernel), every wave the whole tile.
+// kind 5: fp32 in three bf16 parts (phase_gemm_f32_kernel).
 // kind 3: the same tile and packing, pipelined over three LDS stage buffers
 //         (phase_gemm3_kernel; depth = 10 x weight stages in flight + pixel
 //         stages held in registers).
@@ -134,6 +138,12 @@ enum TileCfg {
   TILE_P3_128x256 = 9,   // pipelined split-wave: 8 waves of 128 x 32 channels
   TILE_P3_128x256_W4 = 10,  // pipelined split-wave: 4 waves of 128 x 64 channels, 64-byte K
   TILE_P3_128x128 = 11,  // pipelined split-wave: 4 waves of 128 x 32 channels
+  TILE_WK_64x64 = 12,    // wave-K: 8 waves of the whole tile, every eighth K stage each
+  TILE_WK_64x32 = 13,
+  TILE_F32_64x128_K2 = 14,  // fp32 in three bf16 parts: 2 waves of 64 x 64, two K groups
+  TILE_F32_128x128 = 15,    // 2 x 2 waves of 64 x 64
+  TILE_F32_128x64 = 16,     // 2 x 2 waves of 64 x 32
+  TILE_F32_128x32 = 17,     // 4 waves of 32 x 32
 };
 constexpr TileShape kTiles[] = {
     {128, 128, 4, 2, 128, 2, 2, 0},     // TILE_128x128
@@ -148,6 +158,12 @@ constexpr TileShape kTiles[] = {
     {128, 256, 1, 8, 128, 32, 1, 3, 1},  // TILE_P3_128x256
     {128, 256, 1, 4, 64, 32, 2, 3, 1},   // TILE_P3_128x256_W4
     {128, 128, 1, 4, 128, 32, 2, 3, 1},  // TILE_P3_128x128
+    {64, 64, 1, 8, 128, 1, 1, 4, 1},     // TILE_WK_64x64
+    {64, 32, 1, 8, 128, 1, 2, 4, 1},     // TILE_WK_64x32
+    {64, 128, 1, 2, 128, 2, 2, 5, 2},    // TILE_F32_64x128_K2
+    {128, 128, 2, 2, 128, 2, 2, 5, 1},   // TILE_F32_128x128
+    {128, 64, 2, 2, 128, 2, 2, 5, 1},    // TILE_F32_128x64
+    {128, 32, 4, 1, 128, 2, 2, 5, 1},    // TILE_F32_128x32
 };
 // A split-K plan may switch from the two-K-group 64 x 128 tile to its
 // one-group form after the work list and the weight packing were laid out for
@@ -187,6 +203,16 @@ constexpr int kMaxBlockK_bytes = 256;  // largest K block per stage: 128 bf16 or
 // dtype: 0 fp32, 1 bf16; nchw_out selects the output layout.
 hipError_t launch_phase_gemm(const GemmArgs& a, int dtype, int cfg, bool nchw_out,
                              hipStream_t stream);
+
+// The wave-K form (wavek_kernel) of 64 x bn tiles, bn 64 or 32; at most
+// kMaxLdsTaps taps per work, no K split across workgroups.  fp32 weights come
+// in three bf16 planes (launch_pack_split), a.wp_bytes counting all three.
+hipError_t launch_wavek(const GemmArgs& a, int dtype, int bn, bool nchw_out, hipStream_t stream);
+// The fp32 GEMM (phase_gemm_f32_kernel) of the TILE_F32 configurations, on the
+// same three-plane weights.
+hipError_t launch_gemm_f32(const GemmArgs& a, int cfg, bool nchw_out, hipStream_t stream);
+hipError_t launch_pack_split(const void* w, void* wp, bool transposed, int cin, int cout, int r,
+                             int s, int cin_pad, int cout_pad, int prod_rs, hipStream_t stream);
 
 // Gather w into [slot = kh*s + kw][cout_pad][cin_pad] (zero padded), in the
 // layout the tile kind reads.

@@ -1,0 +1,132 @@
+"""GPU tests of the wave-K form and of fp32 on the bf16 matrix cores."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1907_11210_amd import huge2 as h2
+from paper_1907_11210_amd import workloads as wl
+from paper_1907_11210_amd.workloads import Layer
+
+import parity as P
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+
+def L(name, tr, n, ci, h, w, co, k, st, pd, op, dl, layout, dtype):
+    return Layer(name, tr, n, ci, h, w, co, k, k, st, pd, op, dl, layout, dtype)
+
+
+# (layer, kernel): both sides of the rules' lines, ragged tiles and K tails
+FORMS = [
+    # one stage and one tile; fewer stages than waves; a stage more than eight
+    (L("wk_1x1", False, 1, 8, 3, 5, 8, 1, 1, 0, 0, 1, "NHWC", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_7_stages", False, 1, 7 * 64, 4, 4, 40, 1, 1, 0, 0, 1, "NHWC", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_9_stages", False, 2, 70, 9, 9, 65, 3, 1, 1, 0, 1, "NCHW", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_listed_100", False, 1, 100, 17, 19, 33, 3, 1, 5, 0, 5, "NCHW", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_wide", False, 1, 520, 13, 11, 66, 3, 1, 2, 0, 2, "NHWC", "bf16"), "phase_gemm2"),
+    (L("wk_wide_tiles", False, 6, 264, 33, 33, 70, 3, 1, 2, 0, 2, "NHWC", "bf16"), "wavek_kernel 64x64"),
+    (L("wk_f32", True, 1, 37, 5, 7, 21, 4, 2, 1, 0, 1, "NCHW", "f32"), "wavek_kernel 64x32"),
+    (L("wk_f32_64", True, 9, 40, 14, 12, 100, 5, 2, 2, 1, 1, "NHWC", "f32"), "wavek_kernel 64x64"),
+    (L("wk_no_taps", True, 1, 16, 4, 5, 24, 2, 3, 0, 2, 1, "NHWC", "f32"), "wavek_kernel"),
+    (L("f32_128x64", False, 3, 20, 81, 75, 50, 3, 1, 2, 0, 2, "NCHW", "f32"), "f32_kernel 128x64"),
+    (L("f32_128x32", True, 3, 10, 61, 59, 9, 3, 2, 1, 1, 1, "NHWC", "f32"), "f32_kernel 128x32"),
+    (L("f32_64x128", True, 5, 33, 29, 31, 130, 4, 2, 1, 0, 1, "NCHW", "f32"), "f32_kernel 64x128"),
+    (L("f32_128x128", True, 8, 20, 41, 43, 150, 3, 2, 1, 1, 1, "NHWC", "f32"), "f32_kernel 128x128"),
+    # a K split across workgroups, more taps than the wave-K form holds
+    (L("f32_splitk", False, 1, 600, 9, 9, 70, 3, 1, 1, 0, 1, "NCHW", "f32"), "f32_kernel 64x128"),
+    (L("f32_9x9", False, 1, 20, 21, 22, 40, 9, 1, 4, 0, 1, "NHWC", "f32"), "f32_kernel 128x64"),
+]
+
+
+def _inputs(layer, seed):
+    dt = wl.torch_dtype(layer.dtype)
+    return (wl.layer_input(layer, seed).to(dt), wl.random_weight(layer, seed + 1, 0.1).to(dt))
+
+
+@pytest.mark.parametrize("layer,kernel", FORMS, ids=lambda v: getattr(v, "name", None))
+def test_forms(layer, kernel):
+    """Each form the size rules pick matches the oracle with bias and ReLU,
+    writes every output and repeats bit for bit."""
+    layer = layer.with_(act="relu")
+    P.say("case", layer)
+    xq, wq = _inputs(layer, 3)
+    bias = torch.linspace(-0.5, 0.5, layer.c_out)
+    ref = P.oracle_full(layer, xq, wq, bias)
+    absref = P.oracle_full(layer, xq, wq, bias, absolute=True)
+    y = P.run_gpu(layer, xq, wq, bias, prefill_nan=True)
+    P.check(y, ref, absref, layer.dtype, layer.name)
+    assert np.array_equal(y, P.run_gpu(layer, xq, wq, bias))
+    if layer.dtype == "f32":
+        # the parts hold all 24 bits and 2^-25 of a product is left out: the
+        # sums in fp32 are what is left, within 2^-24 of the largest partial
+        # sum per addition, random over at most 5400 of them
+        assert np.all(np.abs(y - ref) <= 75 * 2.0 ** -24 * absref + 1e-30)
+    plan = P.make_plan(layer, wq.to(DEV))
+    try:
+        assert kernel in plan.kernel, plan.kernel
+    finally:
+        plan.close()
+
+
+F32 = [l for l, _ in FORMS if l.name in ("wk_f32", "f32_128x64", "f32_64x128", "f32_splitk")]
+
+
+def _run(layer, x, w):
+    return P.run_gpu(layer, x, w).astype(np.float64)
+
+
+@pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)
+def test_fp32_non_finite(layer):
+    """Infinities and NaN in x or w, and values that round to infinity in
+    bf16, give what fp32 arithmetic gives: infinite operands have no finite
+    parts, so these sums are formed again term by term."""
+    P.say("case", layer)
+    x, w = _inputs(layer, 5)
+    x, w = x.abs() + 0.1, w.abs() + 0.1  # one sign: the expected sums are known
+    big = 3.4e38
+    x[0, 1, 0, 0] = float("inf")
+    x[0, 2, -1, -1] = float("nan")
+    x[0, 0, 1, 1] = big
+    w.view(-1)[:] *= 1e-3
+    torch_f = torch.nn.functional
+    xd, wd = x.double(), w.double()
+    ref = (torch_f.conv_transpose2d(xd, wd, None, layer.stride, layer.pad, layer.out_pad)
+           if layer.transposed else
+           torch_f.conv2d(xd, wd, None, layer.stride, layer.pad, layer.dil)).numpy()
+    y = _run(layer, x, w)
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(np.isinf(y), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert np.any(fin & (np.abs(ref) > 1e33))
+    # (the oracle has no infinities to work with: a relative bound instead)
+    assert np.all(np.abs(y[fin] - ref[fin]) <= 75 * 2.0 ** -24 * np.abs(ref[fin]))
+
+
+@pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)
+def test_fp32_infinite_weight(layer):
+    x, w = _inputs(layer, 7)
+    x = x.abs() + 0.1
+    w = w.abs()
+    w[1, 0, 0, 0] = float("inf")
+    w[0, 1, -1, -1] = -float("inf")
+    y = _run(layer, x, w)
+    co = 0 if layer.transposed else 1
+    out = y[:, [co, 1 - co]] if layer.transposed else y[:, [1, 0]]
+    assert np.any(np.isposinf(out[:, 0])) and np.any(np.isneginf(out[:, 1]))
+    assert not np.isnan(out).any()  # infinities of one sign per channel
+    rest = np.delete(y, [0, 1], axis=1)
+    assert np.isfinite(rest).all()
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-18, 1.0, 1e15])
+@pytest.mark.parametrize("layer", F32[:2], ids=lambda l: l.name)
+def test_fp32_scales(layer, scale):
+    """The three parts span fp32's exponents: the relative error stays that
+    of fp32 sums from tiny to huge inputs."""
+    x, w = _inputs(layer, 11)
+    xs = (x.double() * scale).float()
+    ref = P.oracle_full(layer, xs, w)
+    y = _run(layer, xs, w)
+    err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
+    assert err <= 1e-6, err
