@@ -11,9 +11,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <queue>
+#include <utility>
 #include <vector>
 
 #include "huge2.h"
@@ -46,6 +48,7 @@ struct huge2_plan {
   size_t x_bytes, wp_bytes;  // extents of the GEMM's input and packed weights
   int n_works;
   int all_ap;  // every work's taps are a product of progressions
+  void* block; // one allocation, which the buffers below lie in
   void* wp;    // packed weights
   void* meta;  // segments, taps, work list
   void* xs;    // staged input (or null)
@@ -119,18 +122,7 @@ int env_int(const char* name, int dflt) {
   return std::atoi(v);
 }
 
-long long count_works(const huge2_conv_desc& d, bool transposed, int class_split, int cfg) {
-  PlanShape shape;
-  const int bm = tile_bm(cfg), bn = tile_bn(cfg);
-  if (!build_shape(d, transposed, class_split, bm, &shape)) return 0;
-  long long works = 0;
-  const long long ntiles = (d.c_out + bn - 1) / bn;
-  for (const huge2_segment& s : shape.segs) {
-    long long m = (long long)d.n * s.nphase_h * s.nphase_w * s.qn_h * s.qn_w;
-    works += (m + bm - 1) / bm * ntiles;
-  }
-  return works;
-}
+long long count_works(const huge2_conv_desc& d, bool transposed, int class_split, int cfg);
 
 // Size of a GEMM as the short-problem rules below see it: 64 x 64 output tiles
 // and K stages (128 bytes of channels) of a tile, the mean over the phases of a
@@ -358,6 +350,8 @@ void order_works_resident(std::vector<WorkDev>& works, int cblocks, int ksplit, 
 // makespan, which a finer split into border classes can cause.
 int64_t makespan_of(const std::vector<int64_t>& costs, int cfg) {
   const int64_t slots = (int64_t)kComputeUnits * kTiles[cfg].wg_per_cu;
+  if ((int64_t)costs.size() <= slots)  // one round
+    return costs.empty() ? 0 : *std::max_element(costs.begin(), costs.end());
   std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> free_at;
   int64_t used = 0, end = 0;
   for (int64_t cost : costs) {
@@ -824,6 +818,24 @@ void work_progressions(const TapDev* tl, int count, int s_width, WorkDev* w) {
   w->ap_doff_w = sd.doff_w;
 }
 
+// Works of a decomposition in tiles of configuration cfg.
+long long count_works(const huge2_conv_desc& d, const PlanShape& shape, int cfg) {
+  const int bm = tile_bm(cfg), bn = tile_bn(cfg);
+  long long works = 0;
+  const long long ntiles = (d.c_out + bn - 1) / bn;
+  for (const huge2_segment& s : shape.segs) {
+    long long m = (long long)d.n * s.nphase_h * s.nphase_w * s.qn_h * s.qn_w;
+    works += (m + bm - 1) / bm * ntiles;
+  }
+  return works;
+}
+
+long long count_works(const huge2_conv_desc& d, bool transposed, int class_split, int cfg) {
+  PlanShape shape;
+  return build_shape(d, transposed, class_split, tile_bm(cfg), &shape) ? count_works(d, shape, cfg)
+                                                                       : 0;
+}
+
 // Border-class splitting of a plan: HUGE2_CLASS_SPLIT (0, 1, 2) forces it;
 // otherwise 0 (one segment per phase group, out-of-range taps read zeros) or
 // 2 (per group, the form that issues fewer tile-taps), whichever the schedule
@@ -831,18 +843,19 @@ void work_progressions(const TapDev* tl, int count, int s_width, WorkDev* w) {
 // at once and the split's ragged segments add works beyond the resident
 // slots, form 0 wins: such a straggler starts only when a unit frees and
 // adds its whole latency (measured on the odd-kernel layer, 512 against 514
-// works: 21.3 against 25.1 us).
-int choose_split(const huge2_conv_desc& d, bool transposed, int cfg) {
+// works: 21.3 against 25.1 us).  Both forms are built once, here.
+bool choose_shape(const huge2_conv_desc& d, bool transposed, int cfg, PlanShape* shape) {
+  const int bm = tile_bm(cfg);
   const int forced = env_int("HUGE2_CLASS_SPLIT", -1);
-  if (forced >= 0 && forced <= 2) return forced;
-  PlanShape s0, s2;
-  if (!build_shape(d, transposed, 0, tile_bm(cfg), &s0) ||
-      !build_shape(d, transposed, 2, tile_bm(cfg), &s2))
-    return 2;
+  if (forced >= 0 && forced <= 2) return build_shape(d, transposed, forced, bm, shape);
+  PlanShape s0;
+  if (!build_shape(d, transposed, 2, bm, shape)) return false;
+  if (!build_shape(d, transposed, 0, bm, &s0)) return true;
   const long long slots = (long long)kComputeUnits * kTiles[cfg].wg_per_cu;
-  const long long w0 = count_works(d, transposed, 0, cfg), w2 = count_works(d, transposed, 2, cfg);
-  if (w0 <= slots && w2 > slots) return 0;
-  return makespan_stages(d, s0, cfg) < makespan_stages(d, s2, cfg) ? 0 : 2;
+  const long long w0 = count_works(d, s0, cfg), w2 = count_works(d, *shape, cfg);
+  if ((w0 <= slots && w2 > slots) || makespan_stages(d, s0, cfg) < makespan_stages(d, *shape, cfg))
+    std::swap(*shape, s0);
+  return true;
 }
 
 // Tile configuration, border-class form and decomposition of a GEMM plan
@@ -853,8 +866,7 @@ int choose_split(const huge2_conv_desc& d, bool transposed, int cfg) {
 int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* listed,
                     ListedShape* ls) {
   const int cfg = choose_cfg(d, tr, 2);
-  const int split = choose_split(d, tr, cfg);
-  if (!build_shape(d, tr, split, tile_bm(cfg), shape)) return -1;
+  if (!choose_shape(d, tr, cfg, shape)) return -1;
   *listed = false;
   const int force = env_int("HUGE2_LISTED", -1);
   if (!tr && force != 0 && build_listed(d, tile_bm(cfg), ls))
@@ -863,18 +875,158 @@ int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* l
 }
 
 
-void free_buffers(huge2_plan* p) {
-  void* bufs[5] = {p->wp, p->meta, p->xs, p->part, p->zbuf};
-  for (void* b : bufs) {
-    if (!b) continue;
-    if (p->mem.arena)
-      continue;  // a region the plan does not own
-    if (p->mem.stream_ordered)
-      (void)hipFreeAsync(b, p->alloc_stream);
-    else
-      (void)hipFree(b);
+// Buffers of the one-shot entry points.  hipMallocAsync and hipFreeAsync cost
+// 25 to 80 us a call here (the pool is mapped and unmapped around every
+// synchronisation, also a pool of one's own with a release threshold), more
+// than the kernels of a short layer.  Blocks are therefore kept between calls:
+// a call takes an idle block of its device and leaves it with an event
+// recorded behind its work; the next call, on any stream and thread, orders
+// its own work behind that event.  At most 64 MiB a GPU are kept, in at most 16
+// blocks in all; larger or further buffers are stream-ordered allocations.
+// Destroying any plan gives idle blocks back, and so does an allocation that
+// fails or would exceed the bound.
+constexpr size_t kBlockKeepBytes = (size_t)64 << 20;
+constexpr int kMaxBlocks = 16;
+struct Block {
+  void* ptr;  // null: free entry
+  size_t bytes;
+  int dev;
+  hipEvent_t done;  // recorded behind the last call that used it
+  bool busy;        // held by a call that has not enqueued all its work
+};
+std::mutex g_blocks_mutex;
+Block g_blocks[kMaxBlocks];
+
+// Frees idle blocks (of device dev, or of all with dev < 0) whose work has
+// completed.  With the lock held.
+void drop_idle_blocks(int dev) {
+  for (Block& b : g_blocks) {
+    if (!b.ptr || b.busy || (dev >= 0 && b.dev != dev)) continue;
+    if (hipEventQuery(b.done) != hipSuccess) {
+      (void)hipGetLastError();
+      continue;
+    }
+    (void)hipFree(b.ptr);
+    (void)hipEventDestroy(b.done);
+    b = Block{};
   }
-  p->wp = p->meta = p->xs = p->part = p->zbuf = nullptr;
+}
+
+void give_back_blocks() {
+  std::lock_guard<std::mutex> lock(g_blocks_mutex);
+  drop_idle_blocks(-1);
+}
+
+// A block for work on `stream`, or null (the caller allocates in stream order).
+void* take_block(size_t bytes, hipStream_t stream) {
+  bytes = (bytes + 0xffffu) & ~(size_t)0xffffu;
+  hipDevice_t dev = -1;
+  int current = -1;
+  if (bytes > kBlockKeepBytes || hipStreamGetDevice(stream, &dev) != hipSuccess ||
+      hipGetDevice(&current) != hipSuccess || dev != current) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::lock_guard<std::mutex> lock(g_blocks_mutex);
+  auto find = [&](Block** entry, size_t* held) {
+    Block* best = nullptr;
+    *entry = nullptr;
+    *held = 0;
+    for (Block& b : g_blocks) {
+      if (!b.ptr) {
+        *entry = &b;
+        continue;
+      }
+      if (b.dev != dev) continue;
+      *held += b.bytes;
+      if (!b.busy && b.bytes >= bytes && (!best || b.bytes < best->bytes)) best = &b;
+    }
+    return best;
+  };
+  Block* entry;
+  size_t held;
+  Block* b = find(&entry, &held);
+  if (b) {
+    const hipError_t e = hipEventQuery(b->done);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (e != hipErrorNotReady || hipStreamWaitEvent(stream, b->done, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+    }
+    b->busy = true;
+    return b->ptr;
+  }
+  if (!entry || held + bytes > kBlockKeepBytes) {
+    drop_idle_blocks(dev);
+    (void)find(&entry, &held);
+    if (!entry || held + bytes > kBlockKeepBytes) return nullptr;
+  }
+  Block nb{};
+  if (hipEventCreateWithFlags(&nb.done, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (hipMalloc(&nb.ptr, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipEventDestroy(nb.done);
+    drop_idle_blocks(dev);
+    return nullptr;
+  }
+  nb.bytes = bytes;
+  nb.dev = dev;
+  nb.busy = true;
+  *entry = nb;
+  return nb.ptr;
+}
+
+// Leaves a block behind the work enqueued on `stream`; false if ptr is none.
+bool leave_block(void* ptr, hipStream_t stream) {
+  std::lock_guard<std::mutex> lock(g_blocks_mutex);
+  for (Block& b : g_blocks) {
+    if (b.ptr != ptr) continue;
+    if (hipEventRecord(b.done, stream) == hipSuccess) {
+      b.busy = false;
+    } else {  // nothing to order the next use by: wait and free
+      (void)hipGetLastError();
+      (void)hipStreamSynchronize(stream);
+      (void)hipFree(b.ptr);
+      (void)hipEventDestroy(b.done);
+      b = Block{};
+    }
+    return true;
+  }
+  return false;
+}
+
+hipError_t one_shot_alloc(void** out, size_t bytes, hipStream_t stream) {
+  *out = take_block(bytes, stream);
+  return *out ? hipSuccess : hipMallocAsync(out, bytes, stream);
+}
+void one_shot_free(void* ptr, hipStream_t stream) {
+  if (!leave_block(ptr, stream)) (void)hipFreeAsync(ptr, stream);
+}
+
+// The one-shot entry points cannot be recorded: their buffers and the host
+// copy of the work list end with the call.
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+void free_buffers(huge2_plan* p) {
+  if (p->block && !p->mem.arena) {  // (an arena is a region the plan does not own)
+    if (p->mem.stream_ordered)
+      one_shot_free(p->block, p->alloc_stream);
+    else
+      (void)hipFree(p->block);
+  }
+  p->block = p->wp = p->meta = p->xs = p->part = p->zbuf = nullptr;
   if (p->inner) {
     free_buffers(p->inner);
     delete p->inner;
@@ -882,24 +1034,43 @@ void free_buffers(huge2_plan* p) {
   }
 }
 
-huge2_status dev_alloc(huge2_plan* p, void** out, size_t bytes) {
-  *out = nullptr;
+// The plan's device buffers as one allocation: each parts[i] gets sizes[i]
+// bytes of it (null for 0), on 256-byte boundaries.
+huge2_status dev_alloc(huge2_plan* p, std::initializer_list<std::pair<void**, size_t>> parts) {
+  size_t bytes = 0;
+  for (const auto& part : parts) {
+    *part.first = nullptr;
+    bytes += (part.second + 255) / 256 * 256;
+  }
   if (bytes == 0) return HUGE2_OK;
   if (p->mem.arena) {
     Arena& a = *p->mem.arena;
     const size_t at = (a.used + 255) / 256 * 256;
     if (at > a.cap || bytes > a.cap - at) return HUGE2_ERR_UNSUPPORTED;
-    *out = a.base + at;
+    p->block = a.base + at;
     a.used = at + bytes;
-    return HUGE2_OK;
+  } else {
+    if (fault("alloc")) return HUGE2_ERR_ALLOC;
+    auto alloc = [&] {
+      return p->mem.stream_ordered ? one_shot_alloc(&p->block, bytes, p->alloc_stream)
+                                   : hipMalloc(&p->block, bytes);
+    };
+    hipError_t e = alloc();
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      give_back_blocks();
+      e = alloc();
+    }
+    if (e != hipSuccess) {
+      p->block = nullptr;
+      (void)hipGetLastError();
+      return HUGE2_ERR_ALLOC;
+    }
   }
-  if (fault("alloc")) return HUGE2_ERR_ALLOC;
-  hipError_t e = p->mem.stream_ordered ? hipMallocAsync(out, bytes, p->alloc_stream)
-                                   : hipMalloc(out, bytes);
-  if (e != hipSuccess) {
-    *out = nullptr;
-    (void)hipGetLastError();
-    return HUGE2_ERR_ALLOC;
+  char* at = (char*)p->block;
+  for (const auto& part : parts) {
+    if (part.second) *part.first = at;
+    at += (part.second + 255) / 256 * 256;
   }
   return HUGE2_OK;
 }
@@ -956,7 +1127,7 @@ huge2_status create_direct(huge2_plan** out, const huge2_conv_desc& d, int trans
     std::snprintf(p->kernel_name, sizeof(p->kernel_name), "quad_kernel %dx%dx%d c%d k%d d%d",
                   qp->ni, qp->qbh, d.w, 32 * qp->nch, qp->ks, qp->depth);
   }
-  huge2_status st = dev_alloc(p, &p->wp, p->wp_bytes);
+  huge2_status st = dev_alloc(p, {{&p->wp, p->wp_bytes}});
   if (st != HUGE2_OK) {
     free_buffers(p);
     delete p;
@@ -969,7 +1140,7 @@ huge2_status create_direct(huge2_plan** out, const huge2_conv_desc& d, int trans
   else if (ok)
     ok = launch_pack_weights(w, p->wp, d.dtype, true, d.c_in, d.c_out, d.r, d.s, p->cin_pad,
                              p->cout_pad, qp ? 128 : 0, stream) == hipSuccess;
-  if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
+  if (ok && !mem.stream_ordered) ok = hipStreamSynchronize(stream) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     free_buffers(p);
@@ -1120,7 +1291,8 @@ huge2_status create_two_pass(huge2_plan** out, const huge2_conv_desc& d, const h
   p->nonzero_macs = build_shape(d, true, 2, 128, &shape) ? shape.nonzero_macs : 0;
   std::snprintf(p->kernel_name, sizeof(p->kernel_name), "two-pass: %.40s + taps_combine",
                 inner->kernel_name);
-  if ((st = dev_alloc(p, &p->zbuf, (size_t)d.n * d1.c_out * d.h * d.w * sizeof(float))) != HUGE2_OK) {
+  if ((st = dev_alloc(p, {{&p->zbuf, (size_t)d.n * d1.c_out * d.h * d.w * sizeof(float)}})) !=
+      HUGE2_OK) {
     free_buffers(p);
     delete p;
     return st;
@@ -1187,7 +1359,7 @@ huge2_status create_grouped(huge2_plan** out, const huge2_conv_desc& d, int tran
       std::snprintf(p->kernel_name, sizeof(p->kernel_name), "grouped_kernel depthwise%s v%d",
                     q.rows3 ? "3" : "", q.vec);
   }
-  huge2_status st = dev_alloc(p, &p->wp, p->wp_bytes);
+  huge2_status st = dev_alloc(p, {{&p->wp, p->wp_bytes}});
   if (st != HUGE2_OK) {
     free_buffers(p);
     delete p;
@@ -1198,7 +1370,7 @@ huge2_status create_grouped(huge2_plan** out, const huge2_conv_desc& d, int tran
     ok = launch_pack_depthwise(w, p->wp, d.dtype, d.c_out, d.r * d.s, stream) == hipSuccess;
   else if (ok)
     ok = hipMemcpyAsync(p->wp, w, p->wp_bytes, hipMemcpyDeviceToDevice, stream) == hipSuccess;
-  if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
+  if (ok && !mem.stream_ordered) ok = hipStreamSynchronize(stream) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     free_buffers(p);
@@ -1543,10 +1715,8 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
 
   const size_t part_b =
       p->ksplit > 1 ? (size_t)p->ksplit * d.n * d.c_out * p->ho * p->wo * sizeof(float) : 0;
-  if ((st = dev_alloc(p, &p->meta, meta_b)) != HUGE2_OK ||
-      (st = dev_alloc(p, &p->wp, wp_b)) != HUGE2_OK ||
-      (st = dev_alloc(p, &p->xs, xs_b)) != HUGE2_OK ||
-      (st = dev_alloc(p, &p->part, part_b)) != HUGE2_OK) {
+  st = dev_alloc(p, {{&p->meta, meta_b}, {&p->wp, wp_b}, {&p->xs, xs_b}, {&p->part, part_b}});
+  if (st != HUGE2_OK) {
     free_buffers(p);
     delete p;
     return st;
@@ -1572,8 +1742,9 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
     ok = launch_pack_weights(w, p->wp, d.dtype, tr, d.c_in, d.c_out, d.r, d.s, p->cin_pad,
                              p->cout_pad, kTiles[p->cfg].kind != 0 ? kPackKB : 0, stream,
                              p->prod_rs) == hipSuccess;
-  // the host copy of the metadata must outlive the transfer
-  if (ok) ok = hipStreamSynchronize(stream) == hipSuccess;
+  // the host copy of the metadata must outlive the transfer (which is
+  // synchronous from pageable memory; a kept plan waits for the packing too)
+  if (ok && !mem.stream_ordered) ok = hipStreamSynchronize(stream) == hipSuccess;
   if (ok) {
     p->h_segs = std::move(segs);
     p->h_taps = std::move(taps);
@@ -1820,6 +1991,7 @@ huge2_status one_shot(const huge2_conv_desc* desc, int transposed, const void* x
   huge2_status st = validate_desc(desc, transposed != 0);
   if (st != HUGE2_OK) return st;
   if (!x || !w || !y || x == y) return HUGE2_ERR_INVALID_ARG;
+  if (capturing(stream)) return HUGE2_ERR_HIP;
   huge2_plan* p = nullptr;
   Mem mem;
   mem.stream_ordered = true;
@@ -1902,9 +2074,12 @@ struct huge2_wgrad_plan {
   int bt_phase;        // Bt in phase planes (WgArgs::bt_phase)
   int hr, sh_min;
   int direct;          // St read in place from the small tensor (WgArgs::direct)
+  void* block;  // one allocation, which the three lie in
   void* st;
   void* bt;
   float* g;
+  bool stream_ordered;  // buffers of a one-shot call (one_shot_alloc on alloc_stream)
+  hipStream_t alloc_stream;
 };
 
 namespace {
@@ -1912,14 +2087,18 @@ namespace {
 constexpr long long kWgradStageBudget = 256ll << 20;  // staged operands of one chunk
 
 void wgrad_free(huge2_wgrad_plan* p) {
-  void* bufs[3] = {p->st, p->bt, p->g};
-  for (void* b : bufs)
-    if (b) (void)hipFree(b);
-  p->st = p->bt = nullptr;
+  if (p->block) {
+    if (p->stream_ordered)
+      one_shot_free(p->block, p->alloc_stream);
+    else
+      (void)hipFree(p->block);
+  }
+  p->block = p->st = p->bt = nullptr;
   p->g = nullptr;
 }
 
-huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, int transposed) {
+huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, int transposed,
+                          bool stream_ordered = false, hipStream_t stream = nullptr) {
   if (!out) return HUGE2_ERR_INVALID_ARG;
   *out = nullptr;
   if (transposed != 0 && transposed != 1) return HUGE2_ERR_INVALID_ARG;
@@ -2029,14 +2208,31 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   p->chunk = (int)chunk;
   p->kp = (int)kp;
   p->ksplit = (int)ksplit;
-  if (fault("alloc") || (st_b > 0 && hipMalloc(&p->st, st_b) != hipSuccess) ||
-      hipMalloc(&p->bt, bt_b) != hipSuccess ||
-      (g_b > 0 && hipMalloc((void**)&p->g, g_b) != hipSuccess)) {
+  p->stream_ordered = stream_ordered;
+  p->alloc_stream = stream;
+  auto up = [](long long v) { return (size_t)(v + 255) / 256 * 256; };
+  const size_t bytes = up(st_b) + up(bt_b) + up(g_b);
+  auto alloc = [&] {
+    return (stream_ordered ? one_shot_alloc(&p->block, bytes, stream)
+                           : hipMalloc(&p->block, bytes)) == hipSuccess;
+  };
+  bool ok = !fault("alloc");
+  if (ok && !alloc()) {
+    (void)hipGetLastError();
+    give_back_blocks();
+    ok = alloc();
+  }
+  if (!ok) {
+    p->block = nullptr;
     (void)hipGetLastError();
     wgrad_free(p);
     delete p;
     return HUGE2_ERR_ALLOC;
   }
+  char* const base = (char*)p->block;
+  if (st_b) p->st = base;
+  p->bt = base + up(st_b);
+  if (g_b) p->g = (float*)(base + up(st_b) + up(bt_b));
   *out = p;
   return HUGE2_OK;
 }
@@ -2102,12 +2298,13 @@ huge2_status wgrad_one_shot(const huge2_conv_desc* desc, int transposed, const v
                             const void* dy, void* dw, hipStream_t stream) {
   if (!x || !dy || !dw || dw == x || dw == dy) return HUGE2_ERR_INVALID_ARG;
   huge2_wgrad_plan* p = nullptr;
-  huge2_status st = wgrad_create(&p, desc, transposed);
+  if (capturing(stream)) return HUGE2_ERR_HIP;
+  huge2_status st = wgrad_create(&p, desc, transposed, true, stream);
   if (st != HUGE2_OK) return st;
   st = wgrad_execute(p, x, dy, dw, stream);
-  if (hipStreamSynchronize(stream) != hipSuccess && st == HUGE2_OK) st = HUGE2_ERR_HIP;
-  wgrad_free(p);
+  wgrad_free(p);  // stream-ordered: released after the enqueued work
   delete p;
+  if (hipStreamSynchronize(stream) != hipSuccess && st == HUGE2_OK) st = HUGE2_ERR_HIP;
   return st;
 }
 
@@ -2376,6 +2573,7 @@ huge2_status huge2_plan_destroy(huge2_plan* plan) {
   if (!plan) return HUGE2_OK;
   free_buffers(plan);
   delete plan;
+  give_back_blocks();
   return HUGE2_OK;
 }
 
@@ -2512,6 +2710,7 @@ huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan) {
   if (!plan) return HUGE2_OK;
   wgrad_free(plan);
   delete plan;
+  give_back_blocks();
   return HUGE2_OK;
 }
 

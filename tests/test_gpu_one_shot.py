@@ -1,0 +1,113 @@
+"""GPU tests of the one-shot entry points' kept blocks: streams, threads and
+graph capture."""
+import threading
+
+import pytest
+import torch
+
+from paper_1907_11210_amd import huge2 as h2
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+
+def _case(i):
+    g = torch.Generator(DEV).manual_seed(i)
+    x = torch.randn(4, 16 + 8 * (i % 3), 12, 10 + i % 5, generator=g, device=DEV)
+    w = torch.randn(x.shape[1], 24, 4, 4, generator=g, device=DEV) * 0.1
+    dy = torch.randn(4, 24, 24, 2 * (10 + i % 5), generator=g, device=DEV)
+    return x, w, dy
+
+
+def _step(x, w, dy):
+    return (h2.conv2d_transpose(x, w, None, 2, 1),
+            h2.conv2d_transpose_wgrad(x, dy, w.shape, 2, 1),
+            h2.conv2d_transpose_dgrad(dy, w, 2, 1))
+
+
+def _same(a, b):
+    return all(torch.equal(p, q) for p, q in zip(a, b))
+
+
+def test_two_streams():
+    """Calls alternating between two streams, nothing waited for in between,
+    reuse each other's blocks and give the bits of calls one at a time."""
+    cases = [_case(i) for i in range(12)]
+    want = []
+    for c in cases:
+        want.append(_step(*c))
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(DEV), torch.cuda.Stream(DEV)]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream(DEV))
+    got = []
+    for i, c in enumerate(cases):
+        with torch.cuda.stream(streams[i % 2]):
+            got.append((h2.conv2d_transpose(c[0], c[1], None, 2, 1),
+                        h2.conv2d_transpose_dgrad(c[2], c[1], 2, 1)))
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert _same(g, (w[0], w[2]))
+
+
+def test_threads():
+    """Four host threads, each on a stream of its own."""
+    cases = [_case(i) for i in range(4)]
+    want = [_step(*c) for c in cases]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        try:
+            s = torch.cuda.Stream(DEV)
+            with torch.cuda.stream(s):
+                for _ in range(8):
+                    got = _step(*cases[i])
+                    s.synchronize()
+                    if not _same(got, want[i]):
+                        bad.append(i)
+        except Exception as e:  # reported by the main thread
+            bad.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
+
+
+def test_memory_is_bounded_and_given_back():
+    """What the calls keep stays under 64 MiB, and destroying a plan frees
+    it."""
+    x, w, dy = _case(1)
+    torch.cuda.synchronize()
+    for n in (2, 8, 32, 96):
+        big = torch.randn(n, 64, 40, 40, device=DEV)
+        wb = torch.randn(64, 64, 4, 4, device=DEV)
+        h2.conv2d_transpose(big, wb, None, 2, 1)
+    del big, wb
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free0, _ = torch.cuda.mem_get_info(DEV)
+    h2.Plan(w, tuple(x.shape), True, 2, 1).close()
+    torch.cuda.synchronize()
+    free1, _ = torch.cuda.mem_get_info(DEV)
+    assert free0 <= free1 <= free0 + (64 << 20) + (4 << 20), (free0, free1)
+
+
+def test_refused_under_capture():
+    """A one-shot call cannot be recorded: it reports an error and the
+    graph's own work is unharmed."""
+    x, w, _ = _case(2)
+    y = h2.conv2d_transpose(x, w, None, 2, 1)
+    z = torch.zeros(8, device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        z.add_(1)
+        with pytest.raises(h2.Huge2Error):
+            h2.conv2d_transpose(x, w, None, 2, 1, out=y)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert z.tolist() == [1.0] * 8
