@@ -182,7 +182,7 @@ huge2_status huge2_plan_destroy(huge2_plan* plan);
 
 /* One-shot transposed convolution (Algorithm 1 semantics, computed by the
  * phase decomposition): plan_create + plan_execute + stream-ordered release
- * of the plan's buffers.  The one-shot entry points keep up to 64 MiB of
+ * of the plan's buffers.  The one-shot entry points keep up to 512 MiB of
  * released buffers per GPU for later calls (any stream or thread; a later
  * call's work is ordered behind the last use), which destroying any plan
  * frees; they cannot be recorded into a HIP graph (HUGE2_ERR_HIP on a

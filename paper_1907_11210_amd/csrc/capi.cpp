@@ -15,7 +15,6 @@
 #include <mutex>
 #include <new>
 #include <queue>
-#include <utility>
 #include <vector>
 
 #include "huge2.h"
@@ -37,6 +36,21 @@ struct Mem {
   Arena* arena = nullptr;
 };
 
+// Device buffers of one plan: a kept plan's are allocated one by one (small
+// ones come cheaper than their sum: 55 against 87 us for a weight-gradient
+// plan), a one-shot call's lie in one block, an arena's in a region it does not
+// own.
+constexpr int kMaxParts = 4;
+struct Buffers {
+  void* held[kMaxParts] = {};  // what to free
+  bool one_shot = false;
+  hipStream_t stream = nullptr;
+};
+struct Part {
+  void** out;
+  size_t bytes;  // 0: *out null
+};
+
 struct huge2_plan {
   huge2_conv_desc desc;
   int transposed;
@@ -48,7 +62,7 @@ struct huge2_plan {
   size_t x_bytes, wp_bytes;  // extents of the GEMM's input and packed weights
   int n_works;
   int all_ap;  // every work's taps are a product of progressions
-  void* block; // one allocation, which the buffers below lie in
+  Buffers bufs;  // the device buffers below
   void* wp;    // packed weights
   void* meta;  // segments, taps, work list
   void* xs;    // staged input (or null)
@@ -881,11 +895,11 @@ int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* l
 // than the kernels of a short layer.  Blocks are therefore kept between calls:
 // a call takes an idle block of its device and leaves it with an event
 // recorded behind its work; the next call, on any stream and thread, orders
-// its own work behind that event.  At most 64 MiB a GPU are kept, in at most 16
-// blocks in all; larger or further buffers are stream-ordered allocations.
+// its own work behind that event.  At most 512 MiB a GPU are kept (the largest
+// weight gradient's workspace is under 320), in at most 16 blocks in all; larger or further buffers are stream-ordered allocations.
 // Destroying any plan gives idle blocks back, and so does an allocation that
 // fails or would exceed the bound.
-constexpr size_t kBlockKeepBytes = (size_t)64 << 20;
+constexpr size_t kBlockKeepBytes = (size_t)512 << 20;
 constexpr int kMaxBlocks = 16;
 struct Block {
   void* ptr;  // null: free entry
@@ -1019,14 +1033,77 @@ bool capturing(hipStream_t stream) {
   return st != hipStreamCaptureStatusNone;
 }
 
-void free_buffers(huge2_plan* p) {
-  if (p->block && !p->mem.arena) {  // (an arena is a region the plan does not own)
-    if (p->mem.stream_ordered)
-      one_shot_free(p->block, p->alloc_stream);
-    else
-      (void)hipFree(p->block);
+void release(Buffers* b) {
+  for (void*& p : b->held) {
+    if (p) (void)(b->one_shot ? (one_shot_free(p, b->stream), hipSuccess) : hipFree(p));
+    p = nullptr;
   }
-  p->block = p->wp = p->meta = p->xs = p->part = p->zbuf = nullptr;
+}
+
+size_t round256(size_t v) { return (v + 255) / 256 * 256; }
+
+// Every part its buffer (on 256-byte boundaries), or nothing at all.
+huge2_status allocate(Buffers* b, std::initializer_list<Part> parts, const Mem& mem,
+                      hipStream_t stream) {
+  size_t sum = 0;
+  for (const Part& part : parts) {
+    *part.out = nullptr;
+    sum += round256(part.bytes);
+  }
+  if (sum == 0) return HUGE2_OK;
+  b->one_shot = mem.stream_ordered;
+  b->stream = stream;
+  char* at = nullptr;
+  if (mem.arena) {
+    Arena& a = *mem.arena;
+    const size_t begin = round256(a.used);
+    if (begin > a.cap || sum > a.cap - begin) return HUGE2_ERR_UNSUPPORTED;
+    at = a.base + begin;
+    a.used = begin + sum;
+  } else if (fault("alloc")) {
+    return HUGE2_ERR_ALLOC;
+  }
+  auto attempt = [&] {
+    if (mem.stream_ordered) {
+      if (one_shot_alloc(&b->held[0], sum, stream) != hipSuccess) {
+        b->held[0] = nullptr;
+        return false;
+      }
+      at = (char*)b->held[0];
+      return true;
+    }
+    int k = 0;
+    for (const Part& part : parts) {
+      if (part.bytes == 0) continue;
+      if (hipMalloc(part.out, part.bytes) != hipSuccess) {
+        *part.out = nullptr;
+        release(b);
+        return false;
+      }
+      b->held[k++] = *part.out;
+    }
+    return true;
+  };
+  if (!mem.arena && !attempt()) {
+    (void)hipGetLastError();
+    give_back_blocks();
+    if (!attempt()) {
+      (void)hipGetLastError();
+      for (const Part& part : parts) *part.out = nullptr;
+      return HUGE2_ERR_ALLOC;
+    }
+  }
+  for (const Part& part : parts) {
+    if (!at) break;
+    if (part.bytes) *part.out = at;
+    at += round256(part.bytes);
+  }
+  return HUGE2_OK;
+}
+
+void free_buffers(huge2_plan* p) {
+  release(&p->bufs);
+  p->wp = p->meta = p->xs = p->part = p->zbuf = nullptr;
   if (p->inner) {
     free_buffers(p->inner);
     delete p->inner;
@@ -1034,45 +1111,8 @@ void free_buffers(huge2_plan* p) {
   }
 }
 
-// The plan's device buffers as one allocation: each parts[i] gets sizes[i]
-// bytes of it (null for 0), on 256-byte boundaries.
-huge2_status dev_alloc(huge2_plan* p, std::initializer_list<std::pair<void**, size_t>> parts) {
-  size_t bytes = 0;
-  for (const auto& part : parts) {
-    *part.first = nullptr;
-    bytes += (part.second + 255) / 256 * 256;
-  }
-  if (bytes == 0) return HUGE2_OK;
-  if (p->mem.arena) {
-    Arena& a = *p->mem.arena;
-    const size_t at = (a.used + 255) / 256 * 256;
-    if (at > a.cap || bytes > a.cap - at) return HUGE2_ERR_UNSUPPORTED;
-    p->block = a.base + at;
-    a.used = at + bytes;
-  } else {
-    if (fault("alloc")) return HUGE2_ERR_ALLOC;
-    auto alloc = [&] {
-      return p->mem.stream_ordered ? one_shot_alloc(&p->block, bytes, p->alloc_stream)
-                                   : hipMalloc(&p->block, bytes);
-    };
-    hipError_t e = alloc();
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      give_back_blocks();
-      e = alloc();
-    }
-    if (e != hipSuccess) {
-      p->block = nullptr;
-      (void)hipGetLastError();
-      return HUGE2_ERR_ALLOC;
-    }
-  }
-  char* at = (char*)p->block;
-  for (const auto& part : parts) {
-    if (part.second) *part.first = at;
-    at += (part.second + 255) / 256 * 256;
-  }
-  return HUGE2_OK;
+huge2_status dev_alloc(huge2_plan* p, std::initializer_list<Part> parts) {
+  return allocate(&p->bufs, parts, p->mem, p->alloc_stream);
 }
 
 // Plan of the all-taps form (zp), the output-stationary form (rp) or the
@@ -1609,8 +1649,18 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
   }
   p->issued_macs = issued;
   bool all_ap = true;
+  const WorkDev* prev = nullptr;  // most works share the tap list of the one before
   for (WorkDev& wd : works) {
-    work_progressions(taps.data() + wd.tap_begin, wd.tap_count, d.s, &wd);
+    if (prev && prev->tap_begin == wd.tap_begin && prev->tap_count == wd.tap_count) {
+      wd.ap_ntw = prev->ap_ntw;
+      wd.ap_kh0 = prev->ap_kh0, wd.ap_dkh = prev->ap_dkh;
+      wd.ap_kw0 = prev->ap_kw0, wd.ap_dkw = prev->ap_dkw;
+      wd.ap_off0_h = prev->ap_off0_h, wd.ap_doff_h = prev->ap_doff_h;
+      wd.ap_off0_w = prev->ap_off0_w, wd.ap_doff_w = prev->ap_doff_w;
+    } else {
+      work_progressions(taps.data() + wd.tap_begin, wd.tap_count, d.s, &wd);
+    }
+    prev = &wd;
     // (a work without taps has no step to take)
     all_ap = all_ap && (wd.ap_ntw > 0 || wd.tap_count == 0);
   }
@@ -2070,16 +2120,15 @@ struct huge2_wgrad_plan {
   int ksplit;          // K slices of the GEMM (workgroups along K)
   int groups;          // > 1: grouped conv (direct per-plane sums, no workspace)
   int direct_out;      // the GEMM writes dw (WgArgs::direct_out)
+  WgTile tile;         // the GEMM's
   int gather_ib;       // images per LDS-gather workgroup (0: the staging kernel gathers)
   int bt_phase;        // Bt in phase planes (WgArgs::bt_phase)
   int hr, sh_min;
   int direct;          // St read in place from the small tensor (WgArgs::direct)
-  void* block;  // one allocation, which the three lie in
+  Buffers bufs;  // the three below
   void* st;
   void* bt;
   float* g;
-  bool stream_ordered;  // buffers of a one-shot call (one_shot_alloc on alloc_stream)
-  hipStream_t alloc_stream;
 };
 
 namespace {
@@ -2087,13 +2136,8 @@ namespace {
 constexpr long long kWgradStageBudget = 256ll << 20;  // staged operands of one chunk
 
 void wgrad_free(huge2_wgrad_plan* p) {
-  if (p->block) {
-    if (p->stream_ordered)
-      one_shot_free(p->block, p->alloc_stream);
-    else
-      (void)hipFree(p->block);
-  }
-  p->block = p->st = p->bt = nullptr;
+  release(&p->bufs);
+  p->st = p->bt = nullptr;
   p->g = nullptr;
 }
 
@@ -2149,7 +2193,8 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   // the large tensor's copies through LDS where its planes fit
   // (HUGE2_WGRAD_GATHER=0: the plain staging kernel gathers them)
   p->gather_ib = env_int("HUGE2_WGRAD_GATHER", 1) != 0
-                     ? wgrad_gather_images(p->hs, p->ws, p->hb, p->wb, (int)esz, (int)chunk, p->nb)
+                     ? wgrad_gather_images(p->hs, p->ws, p->hb, p->wb, (int)esz, (int)chunk, p->nb,
+                                           (int)taps)
                      : 0;
   // phase planes instead of per-tap copies where a K stage lies in one image
   // and the planes (hr rows each) are smaller than the taps' copies
@@ -2169,14 +2214,13 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
     delete p;
     return HUGE2_ERR_UNSUPPORTED;
   }
-  // split K so that the GEMM has about two workgroups per compute unit
-  // (the 128 x 128 tiles run two per compute unit; the 64 x 64 ones four),
-  // each split keeping at least 8 K stages
-  const long long wt = wgrad_tile(p->ms, (int)nb_g);
-  const long long tiles = ((p->ms + wt - 1) / wt) * ((nb_g + wt - 1) / wt);
+  // split K so that the GEMM fills the compute units (WgTile::per_cu), each
+  // split keeping at least 8 K stages
   const long long stages = kp * esz / 128;
-  const long long per_cu = wt == 128 ? 2 : 4;
-  long long ksplit = std::max(1ll, (per_cu * kComputeUnits + tiles - 1) / tiles);
+  const WgTile wt = wgrad_tile(p->ms, (int)nb_g, d.dtype,
+                               (p->ms + 63) / 64 * ((nb_g + 63) / 64) * stages);
+  const long long tiles = ((p->ms + wt.m - 1) / wt.m) * ((nb_g + wt.n - 1) / wt.n);
+  long long ksplit = std::max(1ll, ((long long)wt.per_cu * kComputeUnits + tiles - 1) / tiles);
   ksplit = std::max(1ll, std::min(ksplit, stages / 8));
   // each slice's fp32 gradient is read back by the store: at most 32 MiB of
   // them (DCGAN's 512 -> 256 and 256 -> 128 layers measured fastest at 4 and
@@ -2200,39 +2244,23 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   const long long big_b = (long long)d.n * p->nb * p->hb * p->wb * esz;
   const long long small_b = (long long)d.n * p->ms * hws * esz;
   if (st_b >= (1ll << 31) || bt_b >= (1ll << 31) || g_b >= (1ll << 31) || big_b >= (1ll << 40) ||
-      small_b >= (1ll << 40) || taps > 65535 || (p->ms + wt - 1) / wt > 65535 ||
-      (nb_g + wt - 1) / wt > 65535) {
+      small_b >= (1ll << 40) || taps > 65535 || (p->ms + 63) / 64 > 65535 ||
+      (nb_g + 63) / 64 > 65535) {
     delete p;
     return HUGE2_ERR_UNSUPPORTED;
   }
   p->chunk = (int)chunk;
   p->kp = (int)kp;
+  p->tile = wt;
   p->ksplit = (int)ksplit;
-  p->stream_ordered = stream_ordered;
-  p->alloc_stream = stream;
-  auto up = [](long long v) { return (size_t)(v + 255) / 256 * 256; };
-  const size_t bytes = up(st_b) + up(bt_b) + up(g_b);
-  auto alloc = [&] {
-    return (stream_ordered ? one_shot_alloc(&p->block, bytes, stream)
-                           : hipMalloc(&p->block, bytes)) == hipSuccess;
-  };
-  bool ok = !fault("alloc");
-  if (ok && !alloc()) {
-    (void)hipGetLastError();
-    give_back_blocks();
-    ok = alloc();
-  }
-  if (!ok) {
-    p->block = nullptr;
-    (void)hipGetLastError();
-    wgrad_free(p);
+  Mem mem;
+  mem.stream_ordered = stream_ordered;
+  st = allocate(&p->bufs, {{&p->st, (size_t)st_b}, {&p->bt, (size_t)bt_b}, {(void**)&p->g, (size_t)g_b}},
+                mem, stream);
+  if (st != HUGE2_OK) {
     delete p;
-    return HUGE2_ERR_ALLOC;
+    return st;
   }
-  char* const base = (char*)p->block;
-  if (st_b) p->st = base;
-  p->bt = base + up(st_b);
-  if (g_b) p->g = (float*)(base + up(st_b) + up(bt_b));
   *out = p;
   return HUGE2_OK;
 }
@@ -2270,6 +2298,7 @@ huge2_status wgrad_execute(const huge2_wgrad_plan* p, const void* x, const void*
   a.bt_phase = p->bt_phase;
   a.hr = p->hr;
   a.sh_min = p->sh_min;
+  a.tile_m = p->tile.m, a.tile_n = p->tile.n;
   division_magic((uint32_t)p->ws, &a.ws_mul, &a.ws_shift);
   division_magic((uint32_t)hws, &a.hws_mul, &a.hws_shift);
   division_magic((uint32_t)(p->hr * p->ws), &a.hrws_mul, &a.hrws_shift);

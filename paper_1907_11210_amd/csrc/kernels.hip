@@ -2425,9 +2425,15 @@ __global__ __launch_bounds__(256) void wgrad_stage_kernel(WgArgs a) {
       if (img8 && k0 < kreal) {
         __builtin_memcpy(v, sm + base + q0, sizeof(v));
       } else {
+        // element t's image is il0 or, past its last pixel, one of the next
 #pragma unroll
         for (int t = 0; t < V; ++t) {
-          const uint32_t k = k0 + t, il = k / hws, q = k - il * hws;
+          const uint32_t k = k0 + t;
+          uint32_t il = il0, q = q0 + t;
+          if (q >= hws) {
+            il = fast_div(k, a.hws_mul, a.hws_shift);
+            q = k - il * hws;
+          }
           v[t] = k < kreal ? sm[((size_t)(a.img0 + il) * a.ms + row) * hws + q] : T(0);
         }
       }
@@ -2515,7 +2521,7 @@ __device__ __forceinline__ size_t wgrad_b_stage(const WgArgs& a, int ks, int kc,
 }
 
 // Tile of a weight-gradient GEMM workgroup: the grid's (m block, n block,
-// tap + taps * split) in that order of the linear workgroup index, each XCD
+// split) in that order of the linear workgroup index, each XCD
 // taking a contiguous run of it (xcd_remap), so that the m blocks that read
 // one Bt tile, and the taps that read one St tile, share an L2.
 __device__ __forceinline__ void wgrad_block(int& bx, int& by, int& bz) {
@@ -2530,274 +2536,199 @@ __device__ __forceinline__ void wgrad_block(int& bx, int& by, int& bz) {
 // The GEMM of all taps at once: column c = n * taps + tap of G is Bt's row
 // (n, tap), so that G[m][c] is dw's element (m, n, tap) and a big tensor
 // with few channels is not padded to a tile per tap.
-// G[m][c] (+)= sum_k St[m][k] * Bt[c][k]: a 64 x 64 tile per
-// workgroup of 4 waves (32 x 32 each), K in 128-byte stages through LDS,
-// double buffered, the next stage's loads in registers while this one
-// multiplies.  K order inside a stage is permuted identically for both
-// operands (lane half h takes the stage's h-th half), as in the phase GEMM.
-template <bool BF16>
-__global__ __launch_bounds__(256) void wgrad_gemm_kernel(WgArgs a) {
+// G[m][c] (+)= sum_k St[m][k] * Bt[c][k]: a tile of 64 TI x 64 TJ per
+// workgroup of 2 x 2 waves (32 TI x 32 TJ each; a fragment read from LDS feeds
+// TJ or TI MFMAs, so the wide tiles halve the LDS reads that bound the 64 x 64
+// one: 424 x 9 columns x 104 rows, K 13216, bf16, 47.6 us on 64 x 64), K in
+// 128-byte stages through LDS, double buffered, the loads two stages ahead.
+// K order inside a stage is permuted identically for both operands (lane half
+// h takes the h-th half of a 64-byte block, bf16), as in the phase GEMM.  The
+// split's stages run from a start rotated by (column block, split), so that
+// the workgroups of one XCD do not stream the same power-of-two strided rows
+// at the same offsets in lockstep.
+// fp32 runs on the bf16 matrix cores: both operands are split into three
+// bf16 parts on their way into LDS (split8) and six of the nine products are
+// summed in fp32; a sum that comes out infinite or NaN is formed again.
+template <bool BF16, int TI, int TJ>
+__global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
   constexpr int ESZ = BF16 ? 2 : 4;
-  constexpr int KB = 128, KC = KB / ESZ, ROWB = KB + 16;
-  constexpr int STAGE_B = 2 * 64 * ROWB;
+  constexpr int NPL = BF16 ? 1 : 3;
+  constexpr int KB = 128, KC = KB / ESZ, KCH = KC / 16;
+  constexpr int ROWB = KC * 2 + 16;
+  constexpr int TM = 64 * TI, TN = 64 * TJ;
+  constexpr int PLANE_B = (TM + TN) * ROWB, STAGE_B = NPL * PLANE_B;
+  constexpr int LPR = BF16 ? 8 : 4, NLD = BF16 ? 1 : 2;  // lanes per row, 16-byte loads each
+  constexpr int RPP = 256 / LPR, PA = TM / RPP, PB = TN / RPP;
   __shared__ __attribute__((aligned(16))) char smem[2 * STAGE_B];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
-  const int taps = a.r * a.s;
-  int bx, by, bz;
-  wgrad_block(bx, by, bz);
-  const int m0 = bx * 64, n0 = by * 64, tap = bz % taps;
-  const int split = bz / taps;
-  // this thread's two rows of each operand (rows past the end repeat the last)
-  const int chunk = tid & 7, row = tid >> 3;  // 8 chunks of 16 bytes per row
-  const char* const st = (const char*)(a.direct ? a.sm : a.st);
-  const char* const bt = (const char*)a.bt;
-  const size_t a0 = wgrad_a_row(a, min(m0 + row, a.ms - 1), ESZ) + chunk * 16;
-  const size_t a1 = wgrad_a_row(a, min(m0 + row + 32, a.ms - 1), ESZ) + chunk * 16;
-  const size_t b0 = wgrad_b_row(a, tap * a.nb + min(n0 + row, a.nb - 1), ESZ) + chunk * 16;
-  const size_t b1 = wgrad_b_row(a, tap * a.nb + min(n0 + row + 32, a.nb - 1), ESZ) + chunk * 16;
-  struct Regs {
-    uint4 a0, a1, b0, b1;
-  };
-  auto load = [&](int ks) {
-    const size_t off = wgrad_b_stage(a, ks, KC, ESZ), aoff = wgrad_a_stage(a, ks, KC, ESZ);
-    Regs r;
-    r.a0 = *(const uint4*)(st + a0 + aoff);
-    r.a1 = *(const uint4*)(st + a1 + aoff);
-    r.b0 = *(const uint4*)(bt + b0 + off);
-    r.b1 = *(const uint4*)(bt + b1 + off);
-    return r;
-  };
-  auto store = [&](int buf, const Regs& r) {
-    char* as = smem + buf * STAGE_B;
-    char* bs = as + 64 * ROWB;
-    *(uint4*)(as + row * ROWB + chunk * 16) = r.a0;
-    *(uint4*)(as + (row + 32) * ROWB + chunk * 16) = r.a1;
-    *(uint4*)(bs + row * ROWB + chunk * 16) = r.b0;
-    *(uint4*)(bs + (row + 32) * ROWB + chunk * 16) = r.b1;
-  };
-  f32x16 acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  auto compute = [&](int buf) {
-    const char* as = smem + buf * STAGE_B + (wm * 32 + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
-    const char* bs = smem + buf * STAGE_B + (64 + wn * 32 + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
-    if constexpr (BF16) {
-#pragma unroll
-      for (int t = 0; t < KB / 32; ++t) {
-        const bf16x8 va = __builtin_bit_cast(bf16x8, *(const uint4*)(as + 16 * t));
-        const bf16x8 vb = __builtin_bit_cast(bf16x8, *(const uint4*)(bs + 16 * t));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb, va, acc, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int t4 = 0; t4 < KB / 32; ++t4) {
-        const uint4 fa = *(const uint4*)(as + 16 * t4);
-        const uint4 fb = *(const uint4*)(bs + 16 * t4);
-        const uint32_t ea[4] = {fa.x, fa.y, fa.z, fa.w}, eb[4] = {fb.x, fb.y, fb.z, fb.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(eb[e]), __uint_as_float(ea[e]), acc, 0, 0, 0);
-      }
-    }
-  };
-  // this split's K stages [k_lo, k_hi)
-  const int nk_all = a.kp / KC;
-  const int per = (nk_all + a.ksplit - 1) / a.ksplit;
-  const int k_lo = min(split * per, nk_all), k_hi = min(k_lo + per, nk_all);
-  if (k_hi > k_lo) {
-    store(0, load(k_lo));
-    __syncthreads();
-    for (int ks = k_lo; ks < k_hi; ++ks) {
-      // the next stage's loads (the first again past the end: unused)
-      // overlap this stage's MFMAs
-      const Regs nx = load(ks + 1 < k_hi ? ks + 1 : k_lo);
-      compute((ks - k_lo) & 1);
-      if (ks + 1 < k_hi) store((ks + 1 - k_lo) & 1, nx);
-      __syncthreads();
-    }
-  }
-  // acc: lane holds m = m0 + wm*32 + lane%32 (MFMA column: the St operand went
-  // second) and n = n0 + wn*32 + 8*(r/4) + 4*(lane/32) + r%4 (rows)
-  const int m = m0 + wm * 32 + (lane & 31);
-  if (a.direct_out) {  // one K slice and one chunk: the gradient itself
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int n = n0 + wn * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      if (m >= a.ms || n >= a.nb) continue;
-      const size_t d = (size_t)m * a.nb + n;
-      if constexpr (BF16)
-        ((uint16_t*)a.dw)[d] = f32_to_bf16_rne(acc[r]);
-      else
-        ((float*)a.dw)[d] = acc[r];
-    }
-    return;
-  }
-  float* gt = a.g + (((size_t)split * taps + tap) * a.ms + min(m, a.ms - 1)) * a.nb;
-  const bool acc_in = a.accumulate != 0;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int n = n0 + wn * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    const float v = acc[r];
-    if (m < a.ms && n < a.nb) gt[n] = acc_in ? gt[n] + v : v;
-  }
-}
-
-// The same product on 128 x 128 tiles: 4 waves of 64 x 64 (four
-// accumulators each, so consecutive MFMAs do not wait for each other, and
-// each fragment read from LDS feeds two MFMAs), two workgroups per compute
-// unit.  The St fragments go first: a lane holds one output channel n of
-// each 32 x 32 block, so the fp32 partial rows of G are written 128 bytes at
-// a time.
-template <bool BF16>
-__global__ __launch_bounds__(256, 2) void wgrad_gemm2_kernel(WgArgs a) {
-  constexpr int ESZ = BF16 ? 2 : 4;
-  constexpr int KB = 128, KC = KB / ESZ, ROWB = KB + 16;
-  constexpr int TM = 128, TN = 128;
-  constexpr int STAGE_B = (TM + TN) * ROWB;
-  __shared__ __attribute__((aligned(16))) char smem[2 * STAGE_B];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 1, wn = wave >> 1;
-  const int taps = a.r * a.s;
-  int bx, by, bz;
-  wgrad_block(bx, by, bz);
-  const int m0 = bx * TM, n0 = by * TN, tap = bz % taps;
-  const int split = bz / taps;
-  const int chunk = tid & 7, row = tid >> 3;  // 8 chunks of 16 bytes per row, 32 rows per pass
+  const int half = lane >> 5, row32 = lane & 31;
+  int bx, by, split;
+  wgrad_block(bx, by, split);
+  const int m0 = bx * TM, n0 = by * TN;
+  const int chunk = tid % LPR, row = tid / LPR;
   const char* const st = (const char*)(a.direct ? a.sm : a.st);
   const char* const bt = (const char*)a.bt;
   // this thread's rows (rows past the end repeat the last: their products
   // are never stored)
-  size_t ao[4], bo[4];
+  size_t ro[PA + PB];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    ao[j] = wgrad_a_row(a, min(m0 + row + 32 * j, a.ms - 1), ESZ) + chunk * 16;
-    bo[j] = wgrad_b_row(a, tap * a.nb + min(n0 + row + 32 * j, a.nb - 1), ESZ) + chunk * 16;
-  }
+  for (int j = 0; j < PA; ++j)
+    ro[j] = wgrad_a_row(a, min(m0 + row + RPP * j, a.ms - 1), ESZ) + chunk * 16 * NLD;
+#pragma unroll
+  for (int j = 0; j < PB; ++j)
+    ro[PA + j] = wgrad_b_row(a, min(n0 + row + RPP * j, a.nb - 1), ESZ) + chunk * 16 * NLD;
   struct Regs {
-    uint4 a[4], b[4];
+    u32x4 v[PA + PB][NLD];
   };
   auto load = [&](int ks, Regs& r) {
     const size_t off = wgrad_b_stage(a, ks, KC, ESZ), aoff = wgrad_a_stage(a, ks, KC, ESZ);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      r.a[j] = *(const uint4*)(st + ao[j] + aoff);
-      r.b[j] = *(const uint4*)(bt + bo[j] + off);
-    }
+    for (int j = 0; j < PA + PB; ++j)
+#pragma unroll
+      for (int l = 0; l < NLD; ++l)
+        r.v[j][l] = *(const u32x4*)((j < PA ? st + ro[j] + aoff : bt + ro[j] + off) + 16 * l);
   };
   auto store = [&](int buf, const Regs& r) {
-    char* as = smem + buf * STAGE_B;
-    char* bs = as + TM * ROWB;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      *(uint4*)(as + (row + 32 * j) * ROWB + chunk * 16) = r.a[j];
-      *(uint4*)(bs + (row + 32 * j) * ROWB + chunk * 16) = r.b[j];
+    for (int j = 0; j < PA + PB; ++j) {
+      char* const at = smem + buf * STAGE_B + ((j < PA ? 0 : TM) + row + RPP * (j < PA ? j : j - PA)) * ROWB +
+                       chunk * 16;
+      if constexpr (BF16) {
+        *(u32x4*)at = r.v[j][0];
+      } else {
+        const Split8 s = split8(__builtin_bit_cast(uint4, r.v[j][0]), __builtin_bit_cast(uint4, r.v[j][1]));
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *(uint4*)(at + p * PLANE_B) = s.p[p];
+      }
     }
   };
-  f32x16 acc[2][2];
+  f32x16 acc[TI][TJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   auto compute = [&](int buf) {
-    const char* as = smem + buf * STAGE_B + (wm * 64 + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
-    const char* bs =
-        smem + buf * STAGE_B + (TM + wn * 64 + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
+    const char* const as = smem + buf * STAGE_B + (wm * 32 * TI + row32) * ROWB;
+    const char* const bs = smem + buf * STAGE_B + (TM + wn * 32 * TJ + row32) * ROWB;
 #pragma unroll
-    for (int t = 0; t < KB / 32; ++t) {
-      uint4 fa[2], fb[2];
+    for (int c = 0; c < KCH; ++c) {
+      uint4 fa[NPL][TI], fb[NPL][TJ];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[i] = *(const uint4*)(as + 32 * i * ROWB + 16 * t);
-        fb[i] = *(const uint4*)(bs + 32 * i * ROWB + 16 * t);
+      for (int p = NPL - 1; p >= 0; --p) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+          fa[p][i] = *(const uint4*)(as + p * PLANE_B + 32 * i * ROWB + pack_chunk_byte(c, half));
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          fb[p][j] = *(const uint4*)(bs + p * PLANE_B + 32 * j * ROWB + pack_chunk_byte(c, half));
       }
-      if constexpr (BF16) {
+      // the smallest products first
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int o = NPL - 1; o >= 0; --o)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0,
-                0);
-      } else {
+        for (int p = 0; p <= o; ++p)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+          for (int i = 0; i < TI; ++i)
 #pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const uint32_t ea = e == 0 ? fa[i].x : e == 1 ? fa[i].y : e == 2 ? fa[i].z : fa[i].w;
-              const uint32_t eb = e == 0 ? fb[j].x : e == 1 ? fb[j].y : e == 2 ? fb[j].z : fb[j].w;
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(ea), __uint_as_float(eb),
-                                                               acc[i][j], 0, 0, 0);
-            }
-      }
+            for (int j = 0; j < TJ; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  __builtin_bit_cast(bf16x8, fa[p][i]), __builtin_bit_cast(bf16x8, fb[o - p][j]),
+                  acc[i][j], 0, 0, 0);
     }
   };
   const int nk_all = a.kp / KC;
   const int per = (nk_all + a.ksplit - 1) / a.ksplit;
   const int k_lo = min(split * per, nk_all), k_hi = min(k_lo + per, nk_all);
   if (k_hi > k_lo) {
-    // the split's stages from a start rotated by (column block, split):
-    // the workgroups of one XCD do not stream the same power-of-two strided
-    // rows at the same offsets in lockstep (the m blocks that share a Bt
-    // tile keep the same order)
-    const int nst = k_hi - k_lo, rot = ((bz * (int)gridDim.y + by) * 5) % nst;
-    auto stage_of = [&](int i) {
-      const int j = i + rot;
+    const int nst = k_hi - k_lo, rot = ((split * (int)gridDim.y + by) * 5) % nst;
+    auto stage_of = [&](int i) {  // (past the end: any stage, its loads are not used)
+      const int j = min(i, nst - 1) + rot;
       return k_lo + (j >= nst ? j - nst : j);
     };
-    Regs cur, nx;
-    load(stage_of(0), cur);
-    store(0, cur);
+    Regs r0, r1;
+    load(stage_of(0), r0);
+    load(stage_of(1), r1);
+    store(0, r0);
     __syncthreads();
-    for (int i = 0; i < nst; ++i) {
-      // the next stage's loads (the first again past the end: unused)
-      // overlap this stage's MFMAs
-      load(stage_of(i + 1 < nst ? i + 1 : 0), nx);
-      compute(i & 1);
-      if (i + 1 < nst) store((i + 1) & 1, nx);
+    auto step = [&](int i, auto buf_c, Regs& free_r, Regs& next_r) {
+      constexpr int buf = decltype(buf_c)::value;
+      load(stage_of(i + 2), free_r);
+      compute(buf);
+      if (i + 1 < nst) store(buf ^ 1, next_r);
       __syncthreads();
+    };
+    for (int i = 0; i < nst; i += 2) {
+      step(i, std::integral_constant<int, 0>(), r0, r1);
+      if (i + 1 < nst) step(i + 1, std::integral_constant<int, 1>(), r1, r0);
     }
   }
-  // lane: n = n0 + wn*64 + 32 j + lane % 32; m = m0 + wm*64 + 32 i + 8 (r/4) + 4 (lane/32) + r%4
+  // lane: n = n0 + 32 TJ wn + 32 j + lane % 32; m = m0 + 32 TI wm + 32 i + 8 (r/4) + 4 (lane/32) + r%4
   const bool acc_in = a.accumulate != 0;
-  const int n = n0 + wn * 64 + (lane & 31);
-  if (a.direct_out) {  // one K slice and one chunk: the gradient itself
+  const int n = n0 + wn * 32 * TJ + row32;
+  const int mw = m0 + wm * 32 * TI + 4 * half;
+  if constexpr (!BF16) {
+    bool bad = false;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * 64 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (m >= a.ms) continue;
+      for (int j = 0; j < TJ; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if (n + 32 * j >= a.nb) continue;
-          const size_t d = (size_t)m * a.nb + n + 32 * j;
-          if constexpr (BF16)
-            ((uint16_t*)a.dw)[d] = f32_to_bf16_rne(acc[i][j][r]);
-          else
-            ((float*)a.dw)[d] = acc[i][j][r];
+        for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+    if (__any(bad)) {
+      // through this wave's own piece of LDS, so that the loop over the
+      // results stays a loop (every wave has left the stages behind)
+      float* const red = (float*)smem + wave * (TI * TJ * 16 * 64) + lane;
+      static_assert(4 * TI * TJ * 16 * 64 * 4 <= 2 * STAGE_B, "room for the sums");
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) red[((i * TJ + j) * 16 + r) * 64] = acc[i][j][r];
+      for (int e = 0; e < TI * TJ * 16; ++e) {
+        if (fabsf(red[e * 64]) <= 3.402823466e38f) continue;
+        const int i = e / (16 * TJ), j = (e >> 4) % TJ, r = e & 15;
+        const int m = mw + 32 * i + 8 * (r >> 2) + (r & 3), c = n + 32 * j;
+        if (m >= a.ms || c >= a.nb) continue;
+        const size_t ar = wgrad_a_row(a, m, 4), br = wgrad_b_row(a, c, 4);
+        float v = 0.f;
+        for (int ks = k_lo; ks < k_hi; ++ks) {
+          const float* const ap = (const float*)(st + ar + wgrad_a_stage(a, ks, KC, 4));
+          const float* const bp = (const float*)(bt + br + wgrad_b_stage(a, ks, KC, 4));
+          for (int k = 0; k < KC; ++k) v = fmaf(ap[k], bp[k], v);
         }
+        red[e * 64] = v;
       }
-    return;
-  }
-  float* const gt = a.g + ((size_t)split * taps + tap) * a.ms * a.nb;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = red[((i * TJ + j) * 16 + r) * 64];
+    }
+  }
+  // one K slice and one chunk: the gradient itself, else this slice of G
+  float* const gt = a.g + (size_t)split * a.ms * a.nb;
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int m = m0 + wm * 64 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      const int m = mw + 32 * i + 8 * (r >> 2) + (r & 3);
       if (m >= a.ms) continue;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < TJ; ++j) {
         if (n + 32 * j >= a.nb) continue;
-        float* gp = gt + (size_t)m * a.nb + n + 32 * j;
-        *gp = acc_in ? *gp + acc[i][j][r] : acc[i][j][r];
+        const size_t d = (size_t)m * a.nb + n + 32 * j;
+        if (!a.direct_out)
+          gt[d] = acc_in ? gt[d] + acc[i][j][r] : acc[i][j][r];
+        else if constexpr (BF16)
+          ((uint16_t*)a.dw)[d] = f32_to_bf16_rne(acc[i][j][r]);
+        else
+          ((float*)a.dw)[d] = acc[i][j][r];
       }
     }
 }
@@ -2846,9 +2777,8 @@ static dim3 grid_for(long long total) {
   return dim3((unsigned)(want < 65536 ? (want > 0 ? want : 1) : 65536));
 }
 
-// Bt through LDS (hs*ws a multiple of 8, a big-tensor plane within
-// kWgGatherLds): workgroup (n, block of gather_ib images of the chunk) reads
-// the block's planes big[img][n] whole and coalesced, then writes for every
+// Bt through LDS (a big-tensor plane within kWgGatherLds): workgroup (n, block
+// of gather_ib images of the chunk) reads the block's planes big[img][n] whole and coalesced, then writes for every
 // tap the block's run of row (n, tap), runs of 4 bytes of consecutive k per
 // thread (coalesced across the lanes), the last block also the zero padding
 // up to kp.  The strided gather then reads LDS, where
@@ -2882,8 +2812,8 @@ __global__ __launch_bounds__(256) void wgrad_gather_kernel(WgArgs a) {
     }
   }
   __syncthreads();
-  // each thread takes 4-byte runs of k (EPT elements of one image: the run
-  // starts at a multiple of 8), finds their pixels once, then writes them to
+  // each thread takes 4-byte runs of k (EPT elements: a block's images start
+  // at a multiple of EPT), finds their pixels once, then writes them to
   // every tap's row: consecutive lanes hold consecutive k, so both the LDS
   // reads (stride-apart pixels of one row) and the row stores coalesce
   constexpr int EPT = 4 / (int)sizeof(T);
@@ -2932,8 +2862,8 @@ __global__ __launch_bounds__(256) void wgrad_gather_kernel(WgArgs a) {
     for (int e = 0; e < EPT; ++e) {
       const int k = k0 + e;
       if (k < kreal) {
-        const int il = k / hws, q = k - il * hws;
-        const int qh = (int)(((uint64_t)(uint32_t)q * a.ws_mul) >> a.ws_shift), qw = q - qh * a.ws;
+        const int il = (int)fast_div((uint32_t)k, a.hws_mul, a.hws_shift), q = k - il * hws;
+        const int qh = (int)fast_div((uint32_t)q, a.ws_mul, a.ws_shift), qw = q - qh * a.ws;
         bh[e] = qh * a.stride_h - a.pad_h;
         bw[e] = qw * a.stride_w - a.pad_w;
         base[e] = (il - il0) * plane;
@@ -2985,16 +2915,19 @@ hipError_t launch_wgrad_gemm(const WgArgs& a0, int dtype, hipStream_t stream) {
   a.g_s = a.s;
   a.nb *= a.r * a.s;
   a.r = a.s = 1;
-  const int t = wgrad_tile(a.ms, a.nb);
-  const dim3 grid((a.ms + t - 1) / t, (a.nb + t - 1) / t, a.r * a.s * a.ksplit);
-  if (t == 128 && dtype == 1)
-    hipLaunchKernelGGL(wgrad_gemm2_kernel<true>, grid, dim3(256), 0, stream, a);
-  else if (t == 128)
-    hipLaunchKernelGGL(wgrad_gemm2_kernel<false>, grid, dim3(256), 0, stream, a);
-  else if (dtype == 1)
-    hipLaunchKernelGGL(wgrad_gemm_kernel<true>, grid, dim3(256), 0, stream, a);
-  else
-    hipLaunchKernelGGL(wgrad_gemm_kernel<false>, grid, dim3(256), 0, stream, a);
+  const int tm = a.tile_m, tn = a.tile_n;
+  const dim3 grid((a.ms + tm - 1) / tm, (a.nb + tn - 1) / tn, a.ksplit);
+#define HUGE2_WGEMM(BF16_, TI_, TJ_) \
+  hipLaunchKernelGGL((wgrad_gemm_kernel<BF16_, TI_, TJ_>), grid, dim3(256), 0, stream, a)
+  if (dtype == 1) {
+    if (tm == 128 && tn == 128) HUGE2_WGEMM(true, 2, 2);
+    else if (tm == 128) HUGE2_WGEMM(true, 2, 1);
+    else if (tn == 128) HUGE2_WGEMM(true, 1, 2);
+    else HUGE2_WGEMM(true, 1, 1);
+  } else {
+    HUGE2_WGEMM(false, 1, 1);
+  }
+#undef HUGE2_WGEMM
   return hipGetLastError();
 }
 

@@ -480,12 +480,27 @@ struct WgArgs {
   int bt_phase;
   int hr, sh_min;
   uint32_t hrws_mul, hrws_shift;  // floor(v / (hr*ws)) (division_magic)
+  int tile_m, tile_n;             // the GEMM's tile (wgrad_tile)
   int g_taps, g_s;                // the layer's taps and kernel width (the
                                   // GEMM launch folds r, s into nb)
 };
-// Output tile of the weight-gradient GEMM (square, channels of the small x
-// the large tensor): 128 x 128 when both channel counts reach 128, else 64.
-inline int wgrad_tile(int ms, int nb) { return ms >= 128 && nb >= 128 ? 128 : 64; }
+// Output tile of the weight-gradient GEMM, rows of the small tensor x columns
+// (channel of the large tensor, tap), and the K slices to aim at per compute
+// unit; work: 64 x 64 tiles times 128-byte K stages.  A side over 64 takes
+// 128 once the work fills the chip (104 x 424 * 9, 24840: 35.6 us against 47.6
+// on 64 x 64; 88 x 120 * 9, 8772: 19.6 against 26.6); below, 64 x 64 tiles are
+// more workgroups (32 x 15 * 16, 28: 10.7 against 15.3 for the pass), but for two
+// large sides.  fp32 keeps three parts of each operand in LDS, where two 64 x 64
+// workgroups fit a compute unit and hide each other's splitting, and one 128 x
+// 128 does not (168 x 281 * 9 on 10 x 19 x 14: 49.8 against 68.8 us a pass).
+struct WgTile {
+  int m, n, per_cu;
+};
+inline WgTile wgrad_tile(int ms, int nb, int dtype, long long work) {
+  if (dtype != 1) return {64, 64, 2};
+  if (work < 4096) return ms >= 128 && nb >= 128 ? WgTile{128, 128, 2} : WgTile{64, 64, 4};
+  return {ms > 64 ? 128 : 64, nb > 64 ? 128 : 64, ms > 64 && nb > 64 ? 2 : ms > 64 || nb > 64 ? 3 : 4};
+}
 hipError_t launch_wgrad_stage(const WgArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_wgrad_gemm(const WgArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_wgrad_store(const WgArgs& a, int dtype, hipStream_t stream);
@@ -495,15 +510,24 @@ constexpr int kWgSplitStore = 16;
 hipError_t launch_wgrad_grouped(const WgArgs& a, int dtype, hipStream_t stream);
 // Images per workgroup of the LDS gather for a chunk (0: the plain staging
 // kernel gathers Bt): each workgroup holds that many big-tensor planes, as
-// many as fit and still leave about four workgroups per compute unit.
+// many as fit and still leave about four workgroups per compute unit.  The
+// gather writes 4 bytes of k at a time, so with an odd number of small pixels
+// in 16 bits a workgroup takes an even number of images.  Where the pixels
+// are no multiple of 8, the plain staging reads element by element: 424
+// channels of 8 x 59 x 28, 3x3 (50M copied elements), 91 us against 27.7; but it
+// shares a launch with the small tensor's, so it keeps less than 6M elements
+// (2.8M: 12.8 us against 11.2 and the other launch's 4).
 constexpr int kWgGatherLds = 32 * 1024;
-inline int wgrad_gather_images(int hs, int ws, int hb, int wb, int esz, int nimg, int nb) {
+inline int wgrad_gather_images(int hs, int ws, int hb, int wb, int esz, int nimg, int nb, int taps) {
   const long long plane = (long long)hb * wb * esz;
-  if ((hs * ws) % 8 != 0 || plane > kWgGatherLds) return 0;
+  if ((hs * ws) % 8 != 0 && (long long)hs * ws * nimg * nb * taps < (6 << 20)) return 0;
+  const bool pairs = esz == 2 && ((long long)hs * ws) % 2 != 0 && nimg > 1;
+  if (plane > kWgGatherLds) return 0;
   long long ib = (long long)nimg * nb / 1024;
   if (ib > kWgGatherLds / plane) ib = kWgGatherLds / plane;
   if (ib > nimg) ib = nimg;
-  return (int)(ib < 1 ? 1 : ib);
+  if (ib < 1) ib = 1;
+  return (int)(pairs ? (ib + 1) / 2 * 2 : ib);
 }
 
 // Re-layout the input into [n][h*w][c_stride] with zero channel padding.

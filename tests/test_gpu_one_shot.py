@@ -78,7 +78,7 @@ def test_threads():
 
 
 def test_memory_is_bounded_and_given_back():
-    """What the calls keep stays under 64 MiB, and destroying a plan frees
+    """What the calls keep stays under 512 MiB, and destroying a plan frees
     it."""
     x, w, dy = _case(1)
     torch.cuda.synchronize()
@@ -93,7 +93,7 @@ def test_memory_is_bounded_and_given_back():
     h2.Plan(w, tuple(x.shape), True, 2, 1).close()
     torch.cuda.synchronize()
     free1, _ = torch.cuda.mem_get_info(DEV)
-    assert free0 <= free1 <= free0 + (64 << 20) + (4 << 20), (free0, free1)
+    assert free0 <= free1 <= free0 + (512 << 20) + (4 << 20), (free0, free1)
 
 
 def test_refused_under_capture():

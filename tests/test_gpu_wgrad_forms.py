@@ -1,0 +1,65 @@
+"""GPU tests of the weight gradients' gather on any pixel count and of the
+GEMM's tiles, against the float64 oracle."""
+import numpy as np
+import pytest
+
+import parity as P
+import test_gpu_wgrad as W
+
+pytestmark = pytest.mark.gpu
+
+# name, transposed, n, c_in, h, w, c_out, r, s, stride, pad, out_pad, dil, dtype
+CASES = [
+    # small grids of an odd pixel count: pairs of images per workgroup, an odd
+    # last one, a single image, pairs of elements across an image's end
+    ("odd_pixels", False, 5, 12, 9, 7, 20, 3, 3, 1, 1, 0, 1, "bf16"),
+    ("odd_one_image", False, 1, 9, 7, 5, 70, 3, 3, 1, 2, 0, 2, "bf16"),
+    ("odd_many_channels", False, 7, 520, 5, 5, 24, 3, 3, 1, 1, 0, 1, "bf16"),
+    ("even_pixels", True, 3, 33, 5, 6, 10, 4, 4, 2, 1, 0, 1, "bf16"),
+    ("odd_f32", False, 3, 10, 11, 13, 33, 5, 5, 2, 2, 0, 1, "f32"),
+    # tiles: 64 x 64, 64 x 128, 128 x 64, 128 x 128 with remainders
+    ("tile_64_64", False, 2, 60, 8, 9, 64, 1, 1, 1, 0, 0, 1, "bf16"),
+    ("tile_64_128", True, 2, 61, 6, 7, 17, 3, 3, 2, 1, 1, 1, "bf16"),
+    ("tile_128_64", True, 2, 130, 6, 7, 3, 4, 4, 2, 1, 0, 1, "bf16"),
+    ("tile_128_128", False, 3, 30, 12, 11, 129, 3, 3, 1, 1, 0, 1, "bf16"),
+    ("tile_f32_128", False, 2, 30, 12, 11, 129, 3, 3, 1, 1, 0, 1, "f32"),
+    ("tile_f32_64", False, 2, 66, 9, 9, 40, 1, 1, 1, 0, 0, 1, "f32"),
+    # one K slice, fewer stages than the loads run ahead
+    ("short_k", False, 1, 66, 4, 4, 66, 2, 2, 1, 0, 0, 1, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: c[0])
+def test_forms(case, monkeypatch):
+    """Gathered through LDS or by the plain staging kernel
+    (HUGE2_WGRAD_GATHER=0): the oracle's values, and the same bits."""
+    P.say("case", case)
+    xq, dyq = W._inputs(case, seed=21)
+    ref, absref = W._oracle(case, xq, dyq), W._oracle(case, xq, dyq, absolute=True)
+    got = W._gpu(case, xq, dyq)
+    P.check(got, ref, absref, case[-1], case[0])
+    if case[-1] == "f32":
+        # three bf16 parts leave 2^-25 of a product out; the fp32 sums of at
+        # most 512 terms round within 2^-24 of the largest partial sum each
+        assert np.all(np.abs(got - ref) <= 24 * 2.0 ** -24 * absref + 1e-30)
+    monkeypatch.setenv("HUGE2_WGRAD_GATHER", "0")
+    assert np.array_equal(got, W._gpu(case, xq, dyq))
+
+
+@pytest.mark.parametrize("case", [c for c in CASES if c[0] in ("odd_f32", "tile_f32_128")],
+                         ids=lambda c: c[0])
+def test_non_finite(case):
+    """An infinity and a NaN in x reach the gradients that fp32 arithmetic
+    gives them, and no others."""
+    P.say("case", case)
+    xq, dyq = W._inputs(case, seed=23)
+    xq, dyq = xq.abs() + 0.1, dyq.abs() + 0.1
+    clean = W._gpu(case, xq, dyq)
+    xq[0, 1, 5, 5] = float("inf")
+    xq[0, 2, 5, 5] = float("nan")
+    got = W._gpu(case, xq, dyq)
+    assert np.isfinite(clean).all()
+    assert np.isposinf(got[:, 1]).any() and not np.isneginf(got).any()
+    assert np.isnan(got[:, 2]).any()
+    rest = np.delete(got, [1, 2], axis=1)
+    assert np.array_equal(rest, np.delete(clean, [1, 2], axis=1))
