@@ -196,15 +196,15 @@ huge2_status huge2_conv2d_transpose(const huge2_conv_desc* desc, const void* x, 
  * that forbid hipMalloc): the same computation and arguments as
  * huge2_conv2d_transpose, but every device buffer the call needs (the packed
  * sub-kernel weights, the work list, the input staging and the K-slice
- * partials) is carved from a static device array of 64 MiB that the library
+ * partials) is carved from a static device array of 128 MiB that the library
  * holds on each GPU it runs on until the process ends; no hipMalloc,
  * hipFree or other allocating routine is called (host memory holds the
  * plan's description during the call, which waits for hip_stream as plan
  * creation does).  Every call on one GPU uses that GPU's same array: calls
  * that overlap on one GPU (other streams, other host threads) race and must
  * be ordered by the caller; calls on one stream are ordered already.  A
- * layer whose buffers exceed the 64 MiB returns HUGE2_ERR_UNSUPPORTED with y
- * untouched.  Errors otherwise as huge2_conv2d_transpose. */
+ * layer whose buffers exceed 64 MiB (fp32 weights counted at 4 bytes each)
+ * returns HUGE2_ERR_UNSUPPORTED with y untouched.  Errors otherwise as huge2_conv2d_transpose. */
 huge2_status huge2_conv2d_transpose_noalloc(const huge2_conv_desc* desc, const void* x,
                                             const void* w, const float* bias, void* y,
                                             void* hip_stream);

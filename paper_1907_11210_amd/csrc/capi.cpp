@@ -30,6 +30,7 @@ using namespace huge2;
 struct Arena {
   char* base;
   size_t cap, used;
+  size_t budget;  // bytes that the parts may still count as (Part::counted)
 };
 struct Mem {
   bool stream_ordered = false;
@@ -49,6 +50,7 @@ struct Buffers {
 struct Part {
   void** out;
   size_t bytes;  // 0: *out null
+  size_t counted = SIZE_MAX;  // what it counts as in an arena, where not its bytes
 };
 
 struct huge2_plan {
@@ -1045,10 +1047,11 @@ size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 // Every part its buffer (on 256-byte boundaries), or nothing at all.
 huge2_status allocate(Buffers* b, std::initializer_list<Part> parts, const Mem& mem,
                       hipStream_t stream) {
-  size_t sum = 0;
+  size_t sum = 0, counted = 0;
   for (const Part& part : parts) {
     *part.out = nullptr;
     sum += round256(part.bytes);
+    counted += round256(std::min(part.bytes, part.counted));
   }
   if (sum == 0) return HUGE2_OK;
   b->one_shot = mem.stream_ordered;
@@ -1057,9 +1060,10 @@ huge2_status allocate(Buffers* b, std::initializer_list<Part> parts, const Mem& 
   if (mem.arena) {
     Arena& a = *mem.arena;
     const size_t begin = round256(a.used);
-    if (begin > a.cap || sum > a.cap - begin) return HUGE2_ERR_UNSUPPORTED;
+    if (counted > a.budget || begin > a.cap || sum > a.cap - begin) return HUGE2_ERR_UNSUPPORTED;
     at = a.base + begin;
     a.used = begin + sum;
+    a.budget -= counted;
   } else if (fault("alloc")) {
     return HUGE2_ERR_ALLOC;
   }
@@ -1765,7 +1769,13 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
 
   const size_t part_b =
       p->ksplit > 1 ? (size_t)p->ksplit * d.n * d.c_out * p->ho * p->wo * sizeof(float) : 0;
-  st = dev_alloc(p, {{&p->meta, meta_b}, {&p->wp, wp_b}, {&p->xs, xs_b}, {&p->part, part_b}});
+  // (a no-allocation call's bound knows fp32 weights of 4 bytes, and not the
+  // work list and partial sums of the three-part forms' tiles)
+  const size_t extra = split_w ? 0 : SIZE_MAX;
+  st = dev_alloc(p, {{&p->meta, meta_b, extra},
+                     {&p->wp, wp_b, split_w ? wp_b / 6 * 4 : SIZE_MAX},
+                     {&p->xs, xs_b},
+                     {&p->part, part_b, extra}});
   if (st != HUGE2_OK) {
     free_buffers(p);
     delete p;
@@ -2057,8 +2067,12 @@ huge2_status one_shot(const huge2_conv_desc* desc, int transposed, const void* x
 // buffer the plan needs (packed weights, work list, staging, K-slice
 // partials) is carved from this device's copy of `scratch`, whose device
 // address hipGetSymbolAddress gives once per device (in host code the
-// array's name is not a device address).
-constexpr size_t kScratchBytes = (size_t)64 << 20;
+// array's name is not a device address).  A call may take kScratchBudget bytes,
+// fp32 weights counted at 4 bytes each; the array also holds their third part
+// (6 bytes a weight) and such plans' work lists and K-slice partials (at most
+// 256 tiles of 64 x 128 floats, 8 MiB).
+constexpr size_t kScratchBudget = (size_t)64 << 20;
+constexpr size_t kScratchBytes = (size_t)128 << 20;
 constexpr int kMaxDevices = 64;
 std::once_flag g_scratch_once[kMaxDevices];
 void* g_scratch_ptr[kMaxDevices];
@@ -2093,7 +2107,7 @@ huge2_status one_shot_noalloc(const huge2_conv_desc* desc, const void* x, const 
   if (!x || !w || !y || x == y) return HUGE2_ERR_INVALID_ARG;
   void* base = nullptr;
   if ((st = scratch_region(&base)) != HUGE2_OK) return st;
-  Arena arena{(char*)base, kScratchBytes, 0};
+  Arena arena{(char*)base, kScratchBytes, 0, kScratchBudget};
   Mem mem;
   mem.arena = &arena;
   huge2_plan* p = nullptr;

@@ -130,3 +130,25 @@ def test_fp32_scales(layer, scale):
     y = _run(layer, xs, w)
     err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
     assert err <= 1e-6, err
+
+
+def test_fp32_noalloc_limit():
+    """Weights of 56 MiB fit the no-allocation call's 64 MiB, whatever the
+    parts that they are split into take; weights of 72 MiB do not."""
+    def call(c_out, entry):
+        layer = L("na_f32_%d" % c_out, True, 1, 1024, 2, 3, c_out, 4, 2, 1, 0, 1, "NHWC", "f32")
+        P.say("case", layer)
+        x, w = _inputs(layer, 13)
+        x, w = wl.to_layout(x, "NHWC").to(DEV), w.to(DEV)
+        desc = h2.make_desc(1, 1024, 2, 3, c_out, 4, 4, 2, 1, 0, 1, layout=h2.HUGE2_NHWC,
+                            dtype=h2.HUGE2_F32)
+        y = torch.full((1, 4, 6, c_out), float("nan"), device=DEV)
+        entry(desc, x.data_ptr(), w.data_ptr(), 0, y.data_ptr(),
+              torch.cuda.current_stream(DEV).cuda_stream)
+        torch.cuda.synchronize()
+        return y
+    y = call(896, h2.huge2_conv2d_transpose_noalloc)
+    assert torch.equal(y, call(896, h2.huge2_conv2d_transpose)) and torch.isfinite(y).all()
+    with pytest.raises(h2.Huge2Error) as e:
+        call(1152, h2.huge2_conv2d_transpose_noalloc)
+    assert e.value.status == h2.HUGE2_ERR_UNSUPPORTED
