@@ -168,12 +168,24 @@ GemmSize gemm_size(const huge2_conv_desc& d, bool transposed) {
 // / 20.2 (212, 36), 290 -> 419 on 3 x 48 x 29 57.6 / 32.6 (462, 45), 424 -> 200
 // 4x4 on 7 x 39 x 12 37.6 / 29.8 (208, 112).  No operand is shared, so the L2
 // traffic ends it: 256 -> 512 4x4 on 64 x 8 x 8 36.4 / 41.8 (512, 64), 120 -> 363
-// on 8 x 44 x 46 33.7 / 47.9 (1518, 18).  Few tiles with a long K keep the K
-// split across workgroups: 408 -> 99 5x5 28.5 / 35.7 (12, 175).
-bool takes_wavek(const huge2_conv_desc& d, const GemmSize& g) {
-  if ((long long)d.r * d.s > kMaxLdsTaps) return false;
-  if (d.dtype == HUGE2_BF16)
-    return g.tiles <= 512 && g.tiles * g.stages <= 24000 && (g.stages < 64 || g.tiles >= 128);
+// on 8 x 44 x 46 33.7 / 47.9 (1518, 18).
+// Few tiles with a long K stand against a K split across workgroups.  Staged
+// inputs split it by all their taps: 256 -> 512 4x4 on 1 x 16 x 16 19.1 / 15.3
+// (8, 64), 512 -> 256 3x3 on 4 x 16 x 16 21.2 / 16.3 (64, 72), but 512 -> 256 4x4
+// on 2 x 32 x 32 22.0 / 26.0 (32, 128); 1024 -> 512 transposed on 4 x 4, whose
+// phases fill a quarter of a tile: batch 1 15.9 / 15.6, 4 17.8 / 16.0, 8 19.9 /
+// 16.1.  NHWC inputs read in place split by channel blocks alone: 512 -> 256 3x3
+// on 1 x 8 x 8 19.2 / 13.0 (4, 72), 512 -> 256 4x4 on 4 x 32 x 32 24.6 / 22.0
+// (64, 128), 448 -> 96 5x5 on 1 x 8 x 8 25.7 / 23.9 (2, 175).
+bool takes_wavek(const huge2_conv_desc& d, bool transposed, const GemmSize& g) {
+  // (HUGE2_SPLITK asks for slices across workgroups, which it has none of)
+  if ((long long)d.r * d.s > kMaxLdsTaps || env_int("HUGE2_SPLITK", -1) > 1) return false;
+  if (d.dtype == HUGE2_BF16) {
+    if (g.tiles > 512 || g.tiles * g.stages > 24000) return false;
+    if (g.stages < 64 || g.tiles >= 128) return true;
+    const bool in_place = d.layout == HUGE2_NHWC && d.c_in % 8 == 0;
+    return in_place ? g.stages <= 192 : g.stages < 96 && (!transposed || g.tiles >= 16);
+  }
   // fp32 (three bf16 parts, against its shared tiles): 264 -> 40 3x3 on
   // 9 x 41 x 50 87 / 58 (289, 81), 504 -> 456 on 21 x 21 57 / 38 (56, 144), 288
   // -> 72 4x4 on 45 x 28 x 20 54 / 63 (788, 36), 48 -> 64 on 32 x 21 x 27 25 / 31
@@ -202,8 +214,9 @@ bool takes_wavek(const huge2_conv_desc& d, const GemmSize& g) {
 // and no second K group idling on its single K stage.  Few output channels
 // take the narrow 128 x 32 tile.  The wave-K tile is 32 channels wide up to 36
 // stages (two workgroups per compute unit; 88 -> 400 3x3 on 2 x 18 x 30 12.9
-// against 15.5 us), 64 beyond (half the pixel traffic: 29.8 against 38.0 us for
-// the 112 stages above).
+// against 15.5 us) and wherever every unit gets at most one (512 -> 256 4x4 on 8 x
+// 32 x 32 22.2 against 27.1), 64 beyond (half the pixel traffic: 29.8 against
+// 38.0 us for the 112 stages above, 19.1 against 21.3 for 64 stages of 512).
 // fp32 (512 -> 256 4x4 on 64 x 8 x 8, 148 us on the fp32 MFMA): 64 x 128 of two
 // 64 x 64 waves in two K groups 87.7, 128 x 128 in two groups 90.3, in one 89.9
 // us; at most 64 channels 128 x 64; fp32's wave-K tile fits a compute unit once,
@@ -216,10 +229,10 @@ int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
                                 : (kTiles[forced].kind == 5) == !bf16))
     return forced;
   const GemmSize g = gemm_size(d, transposed);
-  if (takes_wavek(d, g)) {
-    if (d.c_out <= 32) return TILE_WK_64x32;
-    if (bf16) return g.stages <= 36 ? TILE_WK_64x32 : TILE_WK_64x64;
-    return g.tiles32 <= kComputeUnits ? TILE_WK_64x32 : TILE_WK_64x64;
+  if (takes_wavek(d, transposed, g)) {
+    if (d.c_out <= 32 || g.tiles32 <= kComputeUnits || (bf16 && g.stages <= 36))
+      return TILE_WK_64x32;
+    return TILE_WK_64x64;
   }
   if (!bf16) {
     if (d.c_out <= 32) return TILE_F32_128x32;
@@ -456,9 +469,13 @@ bool ztile_shape(const huge2_conv_desc& d, bool transposed, ZArgs* z, int64_t* i
   const int cin_pad = round_up(d.c_in, 64);
   const int i_off = ceil_div_i(d.pad_h - (d.r - 1) * d.dil_h, d.stride_h);
   // output rows per workgroup: the tile (and its Z) must fit, and the input
-  // items of a pass must fit the threads; prefer two workgroups per compute
-  // unit, then one
-  int best2 = -1, best1 = -1, fallback = -1;
+  // items of a pass must fit the threads.  A batch whose workgroups can all have
+  // a compute unit of their own takes the fewest rows that still give them one
+  // (128 -> 3 channels, 32 x 32 -> 64 x 64, us with 2 / 4 / 10 rows: batch 1 8.5 /
+  // 8.8 / 10.6, batch 8 (256 workgroups with 2) 8.6 / 8.8 / 10.7, batch 16 (512,
+  // 256, 112) 11.6 / 8.8 / 10.7); larger ones prefer two workgroups per unit,
+  // then one
+  int alone = -1, best2 = -1, best1 = -1, fallback = -1;
   for (int q = (ho + d.stride_h - 1) / d.stride_h; q >= 1; --q) {
     const int ob = std::min(q * d.stride_h, ho);
     const int tr = floor_div_i(ob - 1 + d.pad_h, d.stride_h) - i_off + 1;
@@ -467,12 +484,16 @@ bool ztile_shape(const huge2_conv_desc& d, bool transposed, ZArgs* z, int64_t* i
     if ((long long)std::min(tr, d.h) * d.w * 4 > (long long)kZtileMaxItems * kZtileThreads) continue;
     const long long blocks = (long long)d.n * ((ho + ob - 1) / ob);
     if (fallback < 0) fallback = ob;
+    if (blocks <= kComputeUnits) alone = ob;
     if (best1 < 0 && blocks >= kComputeUnits) best1 = ob;
     if (best2 < 0 && blocks >= 2 * kComputeUnits) best2 = ob;
   }
   // two workgroups share a compute unit only if their LDS fits twice
   const bool two_per_cu = 2 * kZtileLds <= 160 * 1024;
-  const int ob = (two_per_cu && best2 >= 0) ? best2 : best1 >= 0 ? best1 : fallback;
+  const int ob = alone >= 0                   ? alone
+                 : (two_per_cu && best2 >= 0) ? best2
+                 : best1 >= 0                 ? best1
+                                              : fallback;
   if (ob < 0) return false;
   std::memset(z, 0, sizeof(*z));
   z->x_bytes = (uint32_t)x_bytes;
@@ -664,15 +685,32 @@ bool colphase_shape(const huge2_conv_desc& d, bool transposed, CpArgs* z, int64_
 // 128 positions per workgroup (np = 4) halve the weight bytes per
 // multiply-add; they are taken when they still give every compute unit a
 // workgroup of 64 channels (DCGAN L3: 32.5 -> 29.4 us).
+//
+// Short layers take the wave-K phase GEMM instead, whose chain of stages is an
+// eighth as long (us, this kernel / that one).  NHWC, up to 512 of its 64 x 32
+// tiles: 512 -> 256 on 8 x 8, batch 1 12.6 / 8.5, 8 12.5 / 8.8, 16 (512 tiles)
+// 12.8 / 12.2, 32 13.7 / 21.1; 256 -> 128 on 16 x 16, batch 8 (512) 10.1 / 9.1,
+// 16 10.6 / 15.6; 64 -> 64 on 16 x 16, batch 16 (512) 8.8 / 7.8, 32 8.9 / 9.5.
+// NCHW, where that form adds a staging pass, up to 256 tiles of 64 stages: 1024
+// -> 512 on 4 x 4, batch 16 (256) 20.0 / 16.3, 32 20.0 / 20.9; with 16 stages
+// (256 -> 128 on 16 x 16, batch 4) 10.4 / 10.3, with 8 9.0 / 10.3.
+// (HUGE2_QUAD=1 keeps this kernel.)
 bool quad_shape(const huge2_conv_desc& d, bool transposed, QArgs* q, int64_t* issued) {
   if (!transposed || d.dtype != HUGE2_BF16) return false;
   const bool nhwc = d.layout == HUGE2_NHWC;
   if (nhwc && (d.c_out % 8 != 0 || env_int("HUGE2_QUAD_NHWC", 1) == 0)) return false;
-  if (env_int("HUGE2_QUAD", 1) == 0 || env_int("HUGE2_TILE", -1) >= 0) return false;
+  const int quad_env = env_int("HUGE2_QUAD", -1);
+  if (quad_env == 0 || env_int("HUGE2_TILE", -1) >= 0) return false;
   if (d.stride_h != 2 || d.stride_w != 2 || d.r != 4 || d.s != 4 || d.pad_h != 1 ||
       d.pad_w != 1 || d.dil_h != 1 || d.dil_w != 1 || d.out_pad_h != 0 || d.out_pad_w != 0)
     return false;
   if (d.c_in % 64 != 0 || d.w < 4) return false;
+  if (quad_env < 0) {
+    const GemmSize g = gemm_size(d, true);
+    if ((nhwc ? g.tiles32 <= 2 * kComputeUnits : g.tiles32 <= kComputeUnits && g.stages >= 64) &&
+        takes_wavek(d, true, g))
+      return false;
+  }
   const long long hw = (long long)d.h * d.w;
   const bool keven = (d.c_in / 64) % 2 == 0;
   // images and rows per workgroup for pix positions; false if the shape

@@ -24,7 +24,15 @@ FORMS = [
     (L("wk_7_stages", False, 1, 7 * 64, 4, 4, 40, 1, 1, 0, 0, 1, "NHWC", "bf16"), "wavek_kernel 64x32"),
     (L("wk_9_stages", False, 2, 70, 9, 9, 65, 3, 1, 1, 0, 1, "NCHW", "bf16"), "wavek_kernel 64x32"),
     (L("wk_listed_100", False, 1, 100, 17, 19, 33, 3, 1, 5, 0, 5, "NCHW", "bf16"), "wavek_kernel 64x32"),
-    (L("wk_wide", False, 1, 520, 13, 11, 66, 3, 1, 2, 0, 2, "NHWC", "bf16"), "phase_gemm2"),
+    (L("wk_wide", False, 1, 520, 13, 11, 66, 3, 1, 2, 0, 2, "NHWC", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_wide_staged", False, 1, 710, 13, 11, 66, 3, 1, 2, 0, 2, "NCHW", "bf16"), "phase_gemm2"),
+    (L("wk_ct_staged", True, 3, 1030, 7, 7, 72, 4, 2, 1, 0, 1, "NCHW", "bf16"), "wavek_kernel 64x32"),
+    (L("wk_ct_nhwc", True, 3, 128, 8, 8, 72, 4, 2, 1, 0, 1, "NHWC", "bf16"), "wavek_kernel 64x32"),
+    (L("quad_nhwc", True, 40, 64, 8, 8, 264, 4, 2, 1, 0, 1, "NHWC", "bf16"), "quad_kernel"),
+    # the all-taps form's output rows: the fewest that fit, more, two to a compute unit
+    (L("z_2_rows", True, 3, 24, 9, 10, 3, 4, 2, 1, 0, 1, "NCHW", "bf16"), "ztile_kernel ob2"),
+    (L("z_4_rows", True, 20, 16, 16, 18, 3, 4, 2, 1, 0, 1, "NHWC", "bf16"), "ztile_kernel ob4"),
+    (L("z_many", True, 260, 8, 6, 6, 3, 4, 2, 1, 0, 1, "NCHW", "bf16"), "ztile_kernel ob"),
     (L("wk_wide_tiles", False, 6, 264, 33, 33, 70, 3, 1, 2, 0, 2, "NHWC", "bf16"), "wavek_kernel 64x64"),
     (L("wk_f32", True, 1, 37, 5, 7, 21, 4, 2, 1, 0, 1, "NCHW", "f32"), "wavek_kernel 64x32"),
     (L("wk_f32_64", True, 9, 40, 14, 12, 100, 5, 2, 2, 1, 1, "NHWC", "f32"), "wavek_kernel 64x64"),
