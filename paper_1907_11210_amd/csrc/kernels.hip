@@ -3036,36 +3036,67 @@ hipError_t launch_wgrad_grouped(const WgArgs& a, int dtype, hipStream_t stream) 
 // channels, for NCHW inputs and for NHWC inputs whose channel count is not a
 // multiple of 16 bytes.
 
-// NCHW source: a 64-channel x 64-pixel block per workgroup through LDS.
+// NCHW sources go through an LDS tile of 64 channels x PX pixels and leave it in
+// 16-byte pieces, a channel run of one pixel each.  A wave's 64 pieces cover all
+// channels of 8 (fp32: 4) neighbouring pixels; at(c, px) must give those reads
+// banks of their own.
+template <typename T, int PX, typename At>
+__device__ __forceinline__ void write_pixel_pieces(T* __restrict__ xs, int img, int c0, int p0,
+                                                   int hw, int cs, At at) {
+  constexpr int VE = 16 / sizeof(T);  // elements per 16 bytes
+  constexpr int CC = 64 / VE;         // pieces per pixel
+#pragma unroll
+  for (int i = 0; i < PX * CC / 256; ++i) {
+    const int q = threadIdx.x + 256 * i;
+    const int cc = q % CC, px = q / CC;
+    const int p = p0 + px, c = c0 + cc * VE;
+    if (p >= hw || c >= cs) continue;
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (sizeof(T) == 2)
+        w[e] = (uint32_t)at(cc * VE + 2 * e, px) | ((uint32_t)at(cc * VE + 2 * e + 1, px) << 16);
+      else
+        w[e] = (uint32_t)at(cc * VE + e, px);
+    }
+    *(uint4*)(xs + ((size_t)img * hw + p) * cs + c) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+// Any plane size: 64 channels x 64 pixels per workgroup, read element by element
+// (rows begin anywhere) with a thread's 16 loads in flight together; one after
+// another they were the kernel's time (200 channels of 5 x 33 x 41 bf16 5.5 -> 3.3
+// us, 512 of 8 x 63 x 63 21.2 -> 15.0).
 template <typename T>
 __global__ __launch_bounds__(256) void stage_nchw_kernel(const T* __restrict__ x,
                                                          T* __restrict__ xs, int cin, int hw,
                                                          int cs) {
-  __shared__ T tile[64][65];
+  __shared__ T tile[64][65];  // odd pitch: a column's reads fall in distinct banks
   const int img = blockIdx.z, c0 = blockIdx.y * 64, p0 = blockIdx.x * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, p = p0 + tx;
-    tile[i][tx] = (c < cin && p < hw) ? x[((size_t)img * cin + c) * hw + p] : T(0);
-  }
+  const T* const plane = x + (size_t)img * cin * hw + min(p0 + tx, hw - 1);
+  T v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = plane[(size_t)min(c0 + ty + 4 * i, cin - 1) * hw];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = c0 + ty + 4 * i < cin ? v[i] : T(0);
   __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int p = p0 + i, c = c0 + tx;
-    if (p < hw && c < cs) xs[((size_t)img * hw + p) * cs + c] = tile[tx][i];
-  }
+  write_pixel_pieces<T, 64>(xs, img, c0, p0, hw, cs, [&](int c, int px) { return tile[c][px]; });
 }
 
-// NCHW source whose plane size is a multiple of 16 bytes: 64 channels x
-// 128 bytes of pixels per workgroup, read and written in 16-byte pieces (a
-// channel run of one pixel is gathered from an LDS column).
+// Planes of whole 16-byte pieces: 64 channels x 128 bytes of pixels per
+// workgroup, read in 16-byte pieces.  Row c keeps its piece j at j ^ (c / VE), and
+// fp32's upper 32 rows begin a row later, so that a wave's column reads (rows VE
+// apart) all fall in different banks; with padded rows four met in each (256
+// channels of 64 x 16 x 16 bf16 4.6 -> 3.5 us, of 8 x 64 x 64 7.3 -> 5.2).
 template <typename T>
 __global__ __launch_bounds__(256) void stage_nchw_vec_kernel(const T* __restrict__ x,
                                                              T* __restrict__ xs, int cin, int hw,
                                                              int cs) {
-  constexpr int VE = 16 / sizeof(T);  // elements per 16 bytes
-  constexpr int PX = 8 * VE;          // pixels per tile (128 bytes per channel)
-  constexpr int CC = 64 / VE;         // 16-byte channel chunks per pixel
-  __shared__ __attribute__((aligned(16))) T tile[64][PX + VE];
+  constexpr int VE = 16 / sizeof(T);
+  constexpr int PX = 8 * VE;
+  __shared__ __attribute__((aligned(16))) T tile[64 * PX + PX];
+  const auto at = [](int c, int j) { return (c + c / (8 * VE)) * PX + (j ^ (c / VE & 7)) * VE; };
   const int img = blockIdx.z, c0 = blockIdx.y * 64, p0 = blockIdx.x * PX;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -3074,26 +3105,12 @@ __global__ __launch_bounds__(256) void stage_nchw_vec_kernel(const T* __restrict
     uint4 v = make_uint4(0, 0, 0, 0);
     if (c0 + c < cin && p < hw)
       v = *(const uint4*)(x + ((size_t)img * cin + c0 + c) * hw + p);
-    *(uint4*)&tile[c][j * VE] = v;
+    *(uint4*)&tile[at(c, j)] = v;
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int q = threadIdx.x + 256 * i;
-    const int cc = q % CC, px = q / CC;
-    const int p = p0 + px, c = c0 + cc * VE;
-    if (p >= hw || c >= cs) continue;
-    uint32_t w[4];
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[e] = (uint32_t)tile[cc * VE + 2 * e][px] | ((uint32_t)tile[cc * VE + 2 * e + 1][px] << 16);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (uint32_t)tile[cc * VE + e][px];
-    }
-    *(uint4*)(xs + ((size_t)img * hw + p) * cs + c) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
+  write_pixel_pieces<T, PX>(xs, img, c0, p0, hw, cs, [&](int c, int px) {
+    return tile[at(c, px / VE) + px % VE];
+  });
 }
 
 // NHWC source with cin channels per pixel.

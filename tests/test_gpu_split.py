@@ -160,3 +160,20 @@ def test_fp32_noalloc_limit():
     with pytest.raises(h2.Huge2Error) as e:
         call(1152, h2.huge2_conv2d_transpose_noalloc)
     assert e.value.status == h2.HUGE2_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 3, 7, 9), (3, 64, 8, 8), (1, 65, 5, 13),
+                                     (2, 130, 11, 16), (1, 71, 9, 24)])
+def test_nchw_staging(n, c, h, w, dtype):
+    """A pointwise conv with the identity as weights gives back its staged
+    input, bit for bit: ragged and whole tiles of both staging kernels."""
+    P.say("case staging", n, c, h, w, dtype)
+    dt = wl.torch_dtype(dtype)
+    x = torch.randn(n, c, h, w, generator=torch.Generator().manual_seed(c)).to(dt).to(DEV)
+    eye = torch.eye(c, device=DEV, dtype=dt).reshape(c, c, 1, 1).contiguous()
+    plan = h2.Plan(eye, x.shape, False, 1, 0, 0, 1, "NCHW", "none")
+    try:
+        assert torch.equal(plan(x), x)
+    finally:
+        plan.close()
