@@ -54,8 +54,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "effective TFLOP/s (non-zero MACs) per layer + MFMA util vs peak, 1 MI355X"
-# MI355X dense peaks at 2.4 GHz (256 CUs): TFLOP/s
-PEAK = {"bf16": 2516.6, "f32": 157.3}
+# MI355X dense peaks at 2.4 GHz (256 CUs): TFLOP/s.  fp32 products run as six bf16
+# ones (three parts an operand), a sixth of the bf16 peak (the fp32 MFMA: 157.3).
+PEAK = {"bf16": 2516.6, "f32": 419.4}
 HBM_PEAK_GBS = 8000.0
 
 DESCRIPTIONS = {
