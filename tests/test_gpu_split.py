@@ -77,6 +77,28 @@ def test_forms(layer, kernel):
         plan.close()
 
 
+@pytest.mark.parametrize("n,c_in,c_out,layout", [(64, 100, 1024, "NCHW"), (64, 128, 40, "NHWC"),
+                                                 (7, 65, 300, "NCHW"), (33, 64, 96, "NHWC")])
+def test_two_stages_keep_the_order_of_one_sum(n, c_in, c_out, layout, monkeypatch):
+    """A projection of at most 128 channels gives the bits of the 32 x 256
+    tile, whose workgroup sums all channels in one accumulator."""
+    layer = L("proj", True, n, c_in, 1, 1, c_out, 4, 1, 0, 0, 1, layout, "bf16")
+    P.say("case", layer)
+    x, w = _inputs(layer, 17)
+    def run():
+        plan = P.make_plan(layer, w.to(DEV))
+        try:
+            return plan.kernel, P.run_gpu(layer, x, w, plan=plan)
+        finally:
+            plan.close()
+    kernel, y = run()
+    assert "wavek_kernel" in kernel
+    monkeypatch.setenv("HUGE2_TILE", "5")
+    kernel, want = run()
+    assert " 32x256 " in kernel
+    assert np.array_equal(y, want)
+
+
 F32 = [l for l, _ in FORMS if l.name in ("wk_f32", "f32_128x64", "f32_64x128", "f32_splitk")]
 
 
