@@ -234,15 +234,17 @@ __device__ __forceinline__ Split8 split8(uint4 lo, uint4 hi) {
 }
 
 // Weight (tap block at byte slot_b, channel ch, input channel c) of the
-// three-part fp32 packing: the exact sum of its parts.
+// three-part fp32 packing: the exact sum of its parts, or, behind a NaN in the
+// first plane, the bits in the other two.
 __device__ __forceinline__ float split_weight(const char* wp, size_t plane_b, uint32_t slot_b,
                                               int cin_pad, int ch, int c) {
   const size_t at = slot_b + ((size_t)(ch >> 5) * (cin_pad >> 5) + (c >> 5)) * 2048u +
                     ((c >> 3) & 1) * 1024u + (((c >> 4) & 1) * 32 + (ch & 31)) * 16u + (c & 7) * 2u;
-  float v = 0.f;
-  for (int p = 2; p >= 0; --p)
-    v += __uint_as_float((uint32_t) * (const uint16_t*)(wp + p * plane_b + at) << 16);
-  return v;
+  uint32_t h[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) h[p] = *(const uint16_t*)(wp + p * plane_b + at);
+  if ((h[0] & 0x7fffu) > 0x7f80u) return __uint_as_float(h[1] << 16 | h[2]);
+  return __uint_as_float(h[2] << 16) + __uint_as_float(h[1] << 16) + __uint_as_float(h[0] << 16);
 }
 
 }  // namespace huge2

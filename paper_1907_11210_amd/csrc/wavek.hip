@@ -323,14 +323,22 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const float* __restrict
         v = transposed ? w[((size_t)c * cout + k) * rs + slot] : w[((size_t)k * cin + c) * rs + slot];
       }
     }
-    // a weight that is or rounds to infinity, or is NaN, keeps a first part alone
-    const uint16_t h0 = f32_to_bf16_rne(v);
-    const bool fin = (h0 & 0x7f80u) != 0x7f80u;
-    const float v1 = fin ? v - __uint_as_float((uint32_t)h0 << 16) : 0.f;
-    const uint16_t h1 = f32_to_bf16_rne(v1);
+    // a weight that is or rounds to infinity, or is NaN, has no parts: a NaN in
+    // the first plane sends its sums to the term-by-term path, and the other
+    // two hold its bits (split_weight)
+    uint16_t h0 = f32_to_bf16_rne(v), h1, h2;
+    if ((h0 & 0x7f80u) != 0x7f80u) {
+      const float v1 = v - __uint_as_float((uint32_t)h0 << 16);
+      h1 = f32_to_bf16_rne(v1);
+      h2 = f32_to_bf16_rne(v1 - __uint_as_float((uint32_t)h1 << 16));
+    } else {
+      h0 = 0x7fc0u;
+      h1 = (uint16_t)(__float_as_uint(v) >> 16);
+      h2 = (uint16_t)__float_as_uint(v);
+    }
     wp[idx] = h0;
     wp[idx + total] = h1;
-    wp[idx + 2 * total] = f32_to_bf16_rne(v1 - __uint_as_float((uint32_t)h1 << 16));
+    wp[idx + 2 * total] = h2;
   }
 }
 

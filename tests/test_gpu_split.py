@@ -108,9 +108,9 @@ def _run(layer, x, w):
 
 @pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)
 def test_fp32_non_finite(layer):
-    """Infinities and NaN in x or w, and values that round to infinity in
-    bf16, give what fp32 arithmetic gives: infinite operands have no finite
-    parts, so these sums are formed again term by term."""
+    """Infinities and NaN in x, and values that round to infinity in bf16,
+    give what fp32 arithmetic gives: infinite operands have no finite parts,
+    so these sums are formed again term by term."""
     P.say("case", layer)
     x, w = _inputs(layer, 5)
     x, w = x.abs() + 0.1, w.abs() + 0.1  # one sign: the expected sums are known
@@ -147,6 +147,33 @@ def test_fp32_infinite_weight(layer):
     assert not np.isnan(out).any()  # infinities of one sign per channel
     rest = np.delete(y, [0, 1], axis=1)
     assert np.isfinite(rest).all()
+
+
+@pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)
+def test_fp32_large_weight(layer):
+    """Finite weights that round to infinity in bf16 give finite sums, and
+    nothing at all against a zero input."""
+    P.say("case", layer)
+    x, w = _inputs(layer, 9)
+    x, w = x.abs() * 1e-2 + 1e-3, w.abs()
+    x[0, 1] = 0
+    a = (lambda c, k: (c, k)) if layer.transposed else (lambda c, k: (k, c))
+    w[a(0, 0)] = 3.4e38  # output channel 0 alone: 3.4e36 and more
+    w[a(2, 1)][0, 0] = -torch.finfo(torch.float32).max
+    w[a(1, 2)] = 3.4e38  # meets the zeros only in the first image
+    xd, wd = x.double(), w.double()
+    f = torch.nn.functional
+    ref = (f.conv_transpose2d(xd, wd, None, layer.stride, layer.pad, layer.out_pad)
+           if layer.transposed else
+           f.conv2d(xd, wd, None, layer.stride, layer.pad, layer.dil)).numpy()
+    y = _run(layer, x, w)
+    assert np.isfinite(ref).all() and (np.abs(ref) < 3e38).all()
+    assert np.abs(ref[:, 0]).max() > 1e36 and np.abs(ref[0, 2]).max() < 1e3
+    # (one sign a channel but for one tap, and fp32's subnormals)
+    absref = (f.conv_transpose2d(xd, wd.abs(), None, layer.stride, layer.pad, layer.out_pad)
+              if layer.transposed else
+              f.conv2d(xd, wd.abs(), None, layer.stride, layer.pad, layer.dil)).numpy()
+    assert np.all(np.abs(y - ref) <= 75 * 2.0 ** -24 * absref + 1e-30)
 
 
 @pytest.mark.parametrize("scale", [1e-30, 1e-18, 1.0, 1e15])
