@@ -1063,14 +1063,14 @@ void one_shot_free(void* ptr, hipStream_t stream) {
 }
 
 // The one-shot entry points cannot be recorded: their buffers and the host
-// copy of the work list end with the call.
+// copy of the work list end with the call.  (A query that fails for another
+// reason leaves the report to the allocation behind it.)
 bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return st != hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(stream, &st);
+  if (e == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return e == hipErrorStreamCaptureImplicit;
 }
 
 void release(Buffers* b) {
@@ -2224,6 +2224,10 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
       delete p;
       return HUGE2_ERR_UNSUPPORTED;
     }
+    if (stream_ordered && capturing(stream)) {
+      delete p;
+      return HUGE2_ERR_HIP;
+    }
     p->groups = d.groups;
     p->chunk = d.n;
     p->ksplit = 1;
@@ -2300,6 +2304,10 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
       (nb_g + 63) / 64 > 65535) {
     delete p;
     return HUGE2_ERR_UNSUPPORTED;
+  }
+  if (stream_ordered && capturing(stream)) {  // behind every check of the arguments
+    delete p;
+    return HUGE2_ERR_HIP;
   }
   p->chunk = (int)chunk;
   p->kp = (int)kp;
@@ -2379,7 +2387,6 @@ huge2_status wgrad_one_shot(const huge2_conv_desc* desc, int transposed, const v
                             const void* dy, void* dw, hipStream_t stream) {
   if (!x || !dy || !dw || dw == x || dw == dy) return HUGE2_ERR_INVALID_ARG;
   huge2_wgrad_plan* p = nullptr;
-  if (capturing(stream)) return HUGE2_ERR_HIP;
   huge2_status st = wgrad_create(&p, desc, transposed, true, stream);
   if (st != HUGE2_OK) return st;
   st = wgrad_execute(p, x, dy, dw, stream);

@@ -241,3 +241,35 @@ def test_pyramid_plans_take_the_listed_form(L):
         desc = h2.make_desc(8, 2048, 64, 64, 256, 3, 3, 1, d, 0, d, h2.HUGE2_NHWC, h2.HUGE2_BF16)
         nz, issued = h2.huge2_plan_macs(desc, 0)
         assert nz <= issued <= 1.06 * nz, (d, nz, issued)
+
+
+@pytest.mark.parametrize("form", ["transpose", "dilated"])
+def test_weight_gradient_one_shots_check_arguments_first(L, form):
+    """A bad or unsupported descriptor is reported as such, before any HIP
+    call could fail for want of a GPU or on a capturing stream."""
+    call = getattr(L, "huge2_conv2d_%s_wgrad" % form)
+    x, dy, dw = (ctypes.c_void_p(4096 * i) for i in (1, 2, 3))
+
+    def status(**fields):
+        d = h2.make_desc(2, 8, 5, 5, 4, 3, 3)
+        for k, v in fields.items():
+            setattr(d, k, v)
+        return call(ctypes.byref(d), x, dy, dw, None)
+
+    assert status(h=-1) == h2.HUGE2_ERR_INVALID_ARG
+    assert status(groups=3) == h2.HUGE2_ERR_INVALID_ARG
+    assert status(layout=h2.HUGE2_NHWC) == h2.HUGE2_ERR_UNSUPPORTED
+    assert status(activation=1) == h2.HUGE2_ERR_UNSUPPORTED
+    assert status(n=64, c_in=4096, h=512, w=512) == h2.HUGE2_ERR_UNSUPPORTED
+    assert call(None, x, dy, dw, None) == h2.HUGE2_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("entry", ["huge2_conv2d_transpose_wgrad", "huge2_conv2d_dilated_wgrad",
+                                   "huge2_conv2d_transpose", "huge2_conv2d_dilated"])
+def test_one_shot_allocation_failure_is_reported(L, entry, monkeypatch):
+    """A buffer that cannot be had is HUGE2_ERR_ALLOC."""
+    monkeypatch.setenv("HUGE2_FAULT", "alloc")
+    d = h2.make_desc(2, 8, 5, 5, 4, 3, 3)
+    p = [ctypes.c_void_p(4096 * i) for i in (1, 2, 3)]
+    args = p if "wgrad" in entry else p[:2] + [None] + p[2:]
+    assert getattr(L, entry)(ctypes.byref(d), *args, None) == h2.HUGE2_ERR_ALLOC
