@@ -203,8 +203,9 @@ huge2_status huge2_conv2d_transpose(const huge2_conv_desc* desc, const void* x, 
  * creation does).  Every call on one GPU uses that GPU's same array: calls
  * that overlap on one GPU (other streams, other host threads) race and must
  * be ordered by the caller; calls on one stream are ordered already.  A
- * layer whose buffers exceed 64 MiB (fp32 weights counted at 4 bytes each)
- * returns HUGE2_ERR_UNSUPPORTED with y untouched.  Errors otherwise as huge2_conv2d_transpose. */
+ * layer whose weights (fp32 counted at 4 bytes each) and other buffers exceed
+ * 64 MiB returns HUGE2_ERR_UNSUPPORTED with y untouched.  Errors otherwise as
+ * huge2_conv2d_transpose. */
 huge2_status huge2_conv2d_transpose_noalloc(const huge2_conv_desc* desc, const void* x,
                                             const void* w, const float* bias, void* y,
                                             void* hip_stream);

@@ -694,8 +694,9 @@ bool colphase_shape(const huge2_conv_desc& d, bool transposed, CpArgs* z, int64_
 // NCHW, where that form adds a staging pass, up to 256 tiles of 64 stages: 1024
 // -> 512 on 4 x 4, batch 16 (256) 20.0 / 16.3, 32 20.0 / 20.9; with 16 stages
 // (256 -> 128 on 16 x 16, batch 4) 10.4 / 10.3, with 8 9.0 / 10.3.
-// (HUGE2_QUAD=1 keeps this kernel.)
-bool quad_shape(const huge2_conv_desc& d, bool transposed, QArgs* q, int64_t* issued) {
+// (HUGE2_QUAD=1, or keep_short, keeps this kernel.)
+bool quad_shape(const huge2_conv_desc& d, bool transposed, QArgs* q, int64_t* issued,
+                bool keep_short = false) {
   if (!transposed || d.dtype != HUGE2_BF16) return false;
   const bool nhwc = d.layout == HUGE2_NHWC;
   if (nhwc && (d.c_out % 8 != 0 || env_int("HUGE2_QUAD_NHWC", 1) == 0)) return false;
@@ -705,7 +706,7 @@ bool quad_shape(const huge2_conv_desc& d, bool transposed, QArgs* q, int64_t* is
       d.pad_w != 1 || d.dil_h != 1 || d.dil_w != 1 || d.out_pad_h != 0 || d.out_pad_w != 0)
     return false;
   if (d.c_in % 64 != 0 || d.w < 4) return false;
-  if (quad_env < 0) {
+  if (quad_env < 0 && !keep_short) {
     const GemmSize g = gemm_size(d, true);
     if ((nhwc ? g.tiles32 <= 2 * kComputeUnits : g.tiles32 <= kComputeUnits && g.stages >= 64) &&
         takes_wavek(d, true, g))
@@ -1807,12 +1808,24 @@ huge2_status create_impl(huge2_plan** out, const huge2_conv_desc* desc, int tran
 
   const size_t part_b =
       p->ksplit > 1 ? (size_t)p->ksplit * d.n * d.c_out * p->ho * p->wo * sizeof(float) : 0;
-  // (a no-allocation call's bound knows fp32 weights of 4 bytes, and not the
-  // work list and partial sums of the three-part forms' tiles)
-  const size_t extra = split_w ? 0 : SIZE_MAX;
+  // What a no-allocation call's bound counts: fp32 weights of 4 bytes, not the
+  // work list and partial sums of the wave-K and three-part forms' tiles, and
+  // for a layer that the all-phase form would take that form's weights alone.
+  size_t extra = SIZE_MAX, wp_counted = SIZE_MAX, xs_counted = SIZE_MAX;
+  if (mem.arena && kTiles[p->cfg].kind >= 4) {
+    extra = 0;
+    QArgs q;
+    int64_t q_issued;
+    if (split_w) {
+      wp_counted = wp_b / 6 * 4;
+    } else if (quad_shape(d, tr, &q, &q_issued, true)) {
+      wp_counted = (size_t)d.r * d.s * q.cout_pad * d.c_in * esz;
+      xs_counted = 0;
+    }
+  }
   st = dev_alloc(p, {{&p->meta, meta_b, extra},
-                     {&p->wp, wp_b, split_w ? wp_b / 6 * 4 : SIZE_MAX},
-                     {&p->xs, xs_b},
+                     {&p->wp, wp_b, wp_counted},
+                     {&p->xs, xs_b, xs_counted},
                      {&p->part, part_b, extra}});
   if (st != HUGE2_OK) {
     free_buffers(p);
@@ -2105,10 +2118,12 @@ huge2_status one_shot(const huge2_conv_desc* desc, int transposed, const void* x
 // buffer the plan needs (packed weights, work list, staging, K-slice
 // partials) is carved from this device's copy of `scratch`, whose device
 // address hipGetSymbolAddress gives once per device (in host code the
-// array's name is not a device address).  A call may take kScratchBudget bytes,
-// fp32 weights counted at 4 bytes each; the array also holds their third part
-// (6 bytes a weight) and such plans' work lists and K-slice partials (at most
-// 256 tiles of 64 x 128 floats, 8 MiB).
+// array's name is not a device address).  A call may take kScratchBudget bytes
+// as create_impl counts them; the array also holds what is not counted: the
+// third part of fp32 weights (6 bytes a weight), the work lists (at most twice
+// the counted ones of larger tiles), K-slice partials of fp32 tiles (at most 256
+// tiles of 64 x 128 floats, 8 MiB) and the staged inputs of short all-phase
+// layers (at most 12 MiB, by the bounds of takes_wavek).
 constexpr size_t kScratchBudget = (size_t)64 << 20;
 constexpr size_t kScratchBytes = (size_t)128 << 20;
 constexpr int kMaxDevices = 64;

@@ -211,6 +211,31 @@ def test_fp32_noalloc_limit():
     assert e.value.status == h2.HUGE2_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
+def test_short_all_phase_noalloc_limit(layout):
+    """A layer of the all-phase form's shape whose weights fill the
+    no-allocation call's 64 MiB, as that form needs no other buffer, is taken
+    where the wave-K form runs it; one channel block more is not."""
+    def call(c_out, entry):
+        layer = L("na_bf16", True, 8, 2048, 4, 4, c_out, 4, 2, 1, 0, 1, layout, "bf16")
+        P.say("case", layer)
+        g = torch.Generator(DEV).manual_seed(c_out)
+        x = torch.randn(P._x_shape(layer), generator=g, device=DEV).bfloat16()
+        w = torch.randn(2048, c_out, 4, 4, generator=g, device=DEV).bfloat16()
+        desc = h2.make_desc(8, 2048, 4, 4, c_out, 4, 4, 2, 1, 0, 1, dtype=h2.HUGE2_BF16,
+                            layout=h2.HUGE2_NCHW if layout == "NCHW" else h2.HUGE2_NHWC)
+        y = torch.full((8, c_out, 8, 8), float("nan"), device=DEV).bfloat16()
+        entry(desc, x.data_ptr(), w.data_ptr(), 0, y.data_ptr(),
+              torch.cuda.current_stream(DEV).cuda_stream)
+        torch.cuda.synchronize()
+        return y
+    y = call(1024, h2.huge2_conv2d_transpose_noalloc)
+    assert torch.equal(y, call(1024, h2.huge2_conv2d_transpose)) and torch.isfinite(y).all()
+    with pytest.raises(h2.Huge2Error) as e:
+        call(1056, h2.huge2_conv2d_transpose_noalloc)
+    assert e.value.status == h2.HUGE2_ERR_UNSUPPORTED
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 3, 7, 9), (3, 64, 8, 8), (1, 65, 5, 13),
                                      (2, 130, 11, 16), (1, 71, 9, 24)])
