@@ -2314,9 +2314,11 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   const long long g_b = p->direct_out ? 0 : ksplit * taps * p->ms * p->nb * 4;
   const long long big_b = (long long)d.n * p->nb * p->hb * p->wb * esz;
   const long long small_b = (long long)d.n * p->ms * hws * esz;
+  // (a grid of 65535 tiles a side; wide layers run on tiles 128 wide)
+  const long long side = p->ms >= 128 && nb_g >= 128 ? 128 : 64;
   if (st_b >= (1ll << 31) || bt_b >= (1ll << 31) || g_b >= (1ll << 31) || big_b >= (1ll << 40) ||
-      small_b >= (1ll << 40) || taps > 65535 || (p->ms + 63) / 64 > 65535 ||
-      (nb_g + 63) / 64 > 65535) {
+      small_b >= (1ll << 40) || taps > 65535 || (p->ms + side - 1) / side > 65535 ||
+      (nb_g + side - 1) / side > 65535) {
     delete p;
     return HUGE2_ERR_UNSUPPORTED;
   }

@@ -273,3 +273,23 @@ def test_one_shot_allocation_failure_is_reported(L, entry, monkeypatch):
     p = [ctypes.c_void_p(4096 * i) for i in (1, 2, 3)]
     args = p if "wgrad" in entry else p[:2] + [None] + p[2:]
     assert getattr(L, entry)(ctypes.byref(d), *args, None) == h2.HUGE2_ERR_ALLOC
+
+
+def test_weight_gradient_column_limit(L, monkeypatch):
+    """65535 tiles of 128 columns where both sides have 128, of 64 elsewhere:
+    a layer within that fails for want of memory here, not as unsupported."""
+    monkeypatch.setenv("HUGE2_FAULT", "alloc")
+    p = ctypes.c_void_p()
+
+    def status(c_in, c_out, k, transposed=1, dtype=h2.HUGE2_BF16):
+        d = h2.make_desc(1, c_in, 1, 1, c_out, k, k, dtype=dtype)
+        if not transposed:
+            d.h = d.w = k
+        return L.huge2_wgrad_plan_create(ctypes.byref(p), ctypes.byref(d), transposed)
+
+    assert status(128, 32768, 13) == h2.HUGE2_ERR_ALLOC  # 5.5M columns
+    assert status(24576, 128, 13, 0) == h2.HUGE2_ERR_ALLOC
+    assert status(127, 32768, 13) == h2.HUGE2_ERR_UNSUPPORTED
+    assert status(127, 32768, 11) == h2.HUGE2_ERR_ALLOC  # 4.0M
+    # (below 2^31 bytes fp32 weights of 128 rows have at most 4.19M columns)
+    assert status(128, 16384, 15, dtype=h2.HUGE2_F32) == h2.HUGE2_ERR_ALLOC

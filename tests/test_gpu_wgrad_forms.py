@@ -2,6 +2,9 @@
 GEMM's tiles, against the float64 oracle."""
 import numpy as np
 import pytest
+import torch
+
+from paper_1907_11210_amd import huge2 as h2
 
 import parity as P
 import test_gpu_wgrad as W
@@ -63,3 +66,16 @@ def test_non_finite(case):
     assert np.isnan(got[:, 2]).any()
     rest = np.delete(got, [1, 2], axis=1)
     assert np.array_equal(rest, np.delete(clean, [1, 2], axis=1))
+
+
+def test_many_columns():
+    """5.5M columns (beyond 65535 tiles of 64) of a one-pixel layer: every
+    gradient is one product, rounded once."""
+    P.say("case many columns")
+    dev = torch.device("cuda", 0)
+    g = torch.Generator(dev).manual_seed(3)
+    x = torch.randn(1, 128, 1, 1, generator=g, device=dev).bfloat16()
+    dy = torch.randn(1, 32768, 13, 13, generator=g, device=dev).bfloat16()
+    dw = h2.conv2d_transpose_wgrad(x, dy, (128, 32768, 13, 13), 1, 0)
+    want = torch.outer(x.flatten().float(), dy.flatten().float()).bfloat16()
+    assert torch.equal(dw.view(128, -1), want)
