@@ -205,9 +205,15 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const SegDev& sg, 
   }
 }
 
-// Eight floats as three bf16 parts, x = x1 + x2 + x3: each part rounds what the
-// ones before it left over, to nearest even, so with 8 bits a part the sum
-// holds all 24 (barring underflow), and part k is at most 2^-9k of x.
+// fp32 operands are multiplied by 2^24 before they are split into bf16 parts:
+// the last bit of any float (2^-149 and up) then lies above bf16's smallest
+// normal number and no part underflows.  Operands from 2^104 and sums from 2^80
+// overflow instead, and are formed again term by term.
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-24f, kSumUnscale = 0x1p-48f;
+
+// Eight floats, scaled, as three bf16 parts, x = x1 + x2 + x3: each part rounds
+// what the ones before it left over, to nearest even, so with 8 bits a part the
+// sum holds all 24, and part k is at most 2^-9k of x.
 struct Split8 {
   uint4 p[3];
 };
@@ -215,7 +221,7 @@ __device__ __forceinline__ Split8 split8(uint4 lo, uint4 hi) {
   const uint32_t u[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
   float v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(u[e]);
+  for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(u[e]) * kSplitScale;
   Split8 s;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -234,7 +240,7 @@ __device__ __forceinline__ Split8 split8(uint4 lo, uint4 hi) {
 }
 
 // Weight (tap block at byte slot_b, channel ch, input channel c) of the
-// three-part fp32 packing: the exact sum of its parts, or, behind a NaN in the
+// three-part fp32 packing: the sum of its parts, which is exact, or, behind a NaN in the
 // first plane, the bits in the other two.
 __device__ __forceinline__ float split_weight(const char* wp, size_t plane_b, uint32_t slot_b,
                                               int cin_pad, int ch, int c) {
@@ -244,7 +250,8 @@ __device__ __forceinline__ float split_weight(const char* wp, size_t plane_b, ui
 #pragma unroll
   for (int p = 0; p < 3; ++p) h[p] = *(const uint16_t*)(wp + p * plane_b + at);
   if ((h[0] & 0x7fffu) > 0x7f80u) return __uint_as_float(h[1] << 16 | h[2]);
-  return __uint_as_float(h[2] << 16) + __uint_as_float(h[1] << 16) + __uint_as_float(h[0] << 16);
+  return (__uint_as_float(h[2] << 16) + __uint_as_float(h[1] << 16) + __uint_as_float(h[0] << 16)) *
+         kSplitUnscale;
 }
 
 }  // namespace huge2

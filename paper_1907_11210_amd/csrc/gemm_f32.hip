@@ -6,8 +6,8 @@ namespace huge2 {
 
 // ---------------------------------------------------------------------------
 // Phase GEMM, fp32.  The fp32 MFMA runs at a sixteenth of the bf16 rate, so
-// every operand is split exactly into three bf16 parts (split8; the weights
-// once, when packed) and six of the nine products are summed in fp32, the
+// every operand is split exactly into three bf16 parts (split8, which scales
+// it first; the weights once, when packed) and six of the nine products are summed in fp32, the
 // smallest first; the three left out stay below 2^-25 of the product, under
 // the rounding of the sums.  A workgroup of KS groups of PW x CW waves computes a tile of
 // 32 PW TP pixels x 32 CW TC output channels; a stage is 32 input channels of
@@ -19,8 +19,8 @@ namespace huge2 {
 // gets one workgroup) take halves of the workgroup's stages; group 1's sums
 // are added to group 0's through LDS.
 //
-// An infinite operand has no finite parts, and one that rounds to infinity
-// neither: a sum that comes out infinite or NaN is formed again term by term.
+// An operand that is or becomes infinite has no finite parts: a sum that comes
+// out infinite or NaN is formed again term by term.
 template <int PW, int CW, int TP, int TC, int KS, bool NCHW_OUT, bool AP>
 __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(GemmArgs a) {
   constexpr int NTA = PW * CW * KS * 64, NT = PW * CW * 64;
@@ -292,7 +292,10 @@ __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(Ge
 #pragma unroll
     for (int j = 0; j < TC; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] *= kSumUnscale;
+        bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+      }
   if (__any(bad)) {
     // through the wave's own piece of LDS, so that the loop over the results
     // stays a loop

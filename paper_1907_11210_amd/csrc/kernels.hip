@@ -2547,8 +2547,8 @@ __device__ __forceinline__ void wgrad_block(int& bx, int& by, int& bz) {
 // the workgroups of one XCD do not stream the same power-of-two strided rows
 // at the same offsets in lockstep.
 // fp32 runs on the bf16 matrix cores: both operands are split into three
-// bf16 parts on their way into LDS (split8) and six of the nine products are
-// summed in fp32; a sum that comes out infinite or NaN is formed again.
+// bf16 parts on their way into LDS (split8, scaled) and six of the nine products
+// are summed in fp32; a sum that comes out infinite or NaN is formed again.
 template <bool BF16, int TI, int TJ>
 __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
   constexpr int ESZ = BF16 ? 2 : 4;
@@ -2677,7 +2677,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
 #pragma unroll
       for (int j = 0; j < TJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+        for (int r = 0; r < 16; ++r) {
+          acc[i][j][r] *= kSumUnscale;
+          bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+        }
     if (__any(bad)) {
       // through this wave's own piece of LDS, so that the loop over the
       // results stays a loop (every wave has left the stages behind)

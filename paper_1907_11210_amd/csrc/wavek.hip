@@ -21,11 +21,11 @@ namespace huge2 {
 // which is why large layers keep those (choose_cfg).
 //
 // fp32 runs on the bf16 matrix cores (16 times the fp32 rate): every operand
-// is split exactly into three bf16 parts (split8) and six of the nine products
-// are summed in fp32, leaving out the three that stay below 2^-25 of the
-// product; weights are split once, when packed.  A sum that comes out
-// infinite or NaN is formed again term by term in plain fp32 (an infinite
-// operand, or one that rounds to infinity, has no finite parts).
+// is split exactly into three bf16 parts (split8, which scales it first) and
+// six of the nine products are summed in fp32, leaving out the three that stay
+// below 2^-25 of the product; weights are split once, when packed.  A sum that
+// comes out infinite or NaN is formed again term by term in plain fp32 (an
+// operand that is or becomes infinite has no finite parts).
 constexpr int kWkWaves = 8;
 // Up to two bf16 stages are one wave's: there is no chain to shorten, and one
 // accumulator keeps the sum's order that of the shared tiles, bit for bit
@@ -250,6 +250,7 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
     const int4 row = s_row[px];
     if (row.w < 0 || ch >= a.cout) continue;
     if constexpr (F32) {
+      v *= kSumUnscale;
       if (!(fabsf(v) <= 3.402823466e38f)) {
         v = 0.f;
         for (int t = 0; t < ntaps; ++t) {
@@ -323,12 +324,13 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const float* __restrict
         v = transposed ? w[((size_t)c * cout + k) * rs + slot] : w[((size_t)k * cin + c) * rs + slot];
       }
     }
-    // a weight that is or rounds to infinity, or is NaN, has no parts: a NaN in
-    // the first plane sends its sums to the term-by-term path, and the other
-    // two hold its bits (split_weight)
-    uint16_t h0 = f32_to_bf16_rne(v), h1, h2;
+    // a scaled weight that is or rounds to infinity, or is NaN, has no parts: a
+    // NaN in the first plane sends its sums to the term-by-term path, and the
+    // other two hold its bits (split_weight)
+    const float vs = v * kSplitScale;
+    uint16_t h0 = f32_to_bf16_rne(vs), h1, h2;
     if ((h0 & 0x7f80u) != 0x7f80u) {
-      const float v1 = v - __uint_as_float((uint32_t)h0 << 16);
+      const float v1 = vs - __uint_as_float((uint32_t)h0 << 16);
       h1 = f32_to_bf16_rne(v1);
       h2 = f32_to_bf16_rne(v1 - __uint_as_float((uint32_t)h1 << 16));
     } else {

@@ -179,12 +179,30 @@ def test_fp32_large_weight(layer):
 @pytest.mark.parametrize("scale", [1e-30, 1e-18, 1.0, 1e15])
 @pytest.mark.parametrize("layer", F32[:2], ids=lambda l: l.name)
 def test_fp32_scales(layer, scale):
-    """The three parts span fp32's exponents: the relative error stays that
-    of fp32 sums from tiny to huge inputs."""
+    """The relative error stays that of fp32 sums from tiny to huge inputs."""
     x, w = _inputs(layer, 11)
     xs = (x.double() * scale).float()
     ref = P.oracle_full(layer, xs, w)
     y = _run(layer, xs, w)
+    err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
+    assert err <= 1e-6, err
+
+
+@pytest.mark.parametrize("small", ["x", "w"])
+@pytest.mark.parametrize("scale", [1e-34, 1e-36, 3e-38, 1e-41, 1e27])
+@pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)
+def test_fp32_ends_of_the_exponent_range(layer, scale, small):
+    """Operands at the ends of fp32's exponents (subnormal ones, and ones that
+    the scaled parts cannot hold) against operands that bring the sums back
+    to ordinary size: the three parts lose no bit, so the error is that of
+    fp32 sums all the same."""
+    P.say("case", layer, scale, small)
+    x, w = _inputs(layer, 11)
+    other = min(1 / scale, 1e36)  # (1 / 1e-41 is no float)
+    a, b = (scale, other) if small == "x" else (other, scale)
+    x, w = (x.double() * a).float(), (w.double() * b).float()
+    ref = P.oracle_full(layer, x, w)
+    y = _run(layer, x, w)
     err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
     assert err <= 1e-6, err
 

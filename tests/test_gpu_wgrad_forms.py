@@ -49,6 +49,20 @@ def test_forms(case, monkeypatch):
     assert np.array_equal(got, W._gpu(case, xq, dyq))
 
 
+@pytest.mark.parametrize("scale", [1e-36, 1e-41, 1e27])
+@pytest.mark.parametrize("case", [c for c in CASES if c[0] in ("odd_f32", "tile_f32_128")],
+                         ids=lambda c: c[0])
+def test_ends_of_the_exponent_range(case, scale):
+    """x at the ends of fp32's exponents against errors that bring the sums
+    back to ordinary size: the error is that of fp32 sums all the same."""
+    P.say("case", case, scale)
+    xq, dyq = W._inputs(case, seed=25)
+    xq, dyq = (xq.double() * scale).float(), (dyq.double() * min(1 / scale, 1e36)).float()
+    ref = W._oracle(case, xq, dyq)
+    err = np.linalg.norm(W._gpu(case, xq, dyq) - ref) / np.linalg.norm(ref)
+    assert err <= 1e-6, err
+
+
 @pytest.mark.parametrize("case", [c for c in CASES if c[0] in ("odd_f32", "tile_f32_128")],
                          ids=lambda c: c[0])
 def test_non_finite(case):
