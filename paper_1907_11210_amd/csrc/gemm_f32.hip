@@ -20,7 +20,7 @@ namespace huge2 {
 // are added to group 0's through LDS.
 //
 // An operand that is or becomes infinite has no finite parts: a sum that comes
-// out infinite or NaN is formed again term by term.
+// out infinite or NaN is formed again (mfma_f32_step).
 template <int PW, int CW, int TP, int TC, int KS, bool NCHW_OUT, bool AP>
 __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(GemmArgs a) {
   constexpr int NTA = PW * CW * KS * 64, NT = PW * CW * 64;
@@ -294,36 +294,85 @@ __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(Ge
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         acc[i][j][r] *= kSumUnscale;
-        bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+        bad |= !finite(acc[i][j][r]);
       }
   if (__any(bad)) {
-    // through the wave's own piece of LDS, so that the loop over the results
-    // stays a loop
+    // the wave's own piece of LDS keeps the sums meanwhile
 #pragma unroll
     for (int i = 0; i < TP; ++i)
 #pragma unroll
       for (int j = 0; j < TC; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[((i * TC + j) * 16 + r) * 64] = acc[i][j][r];
-    for (int e = 0; e < NREG; ++e) {
-      if (fabsf(red[e * 64]) <= 3.402823466e38f) continue;
-      const int i = e / (16 * TC), j = (e >> 4) % TC, r = e & 15;
-      const int sub = 8 * (r >> 2) + 4 * half + (r & 3);
-      const int m = pix0 + 32 * i + (NCHW_OUT ? row32 : sub);
-      const int ch = ch0 + 32 * j + (NCHW_OUT ? sub : row32);
-      if (m >= wk.m1 || ch >= a.cout) continue;
-      const PixelPos p = pixel_pos(sg, a.ptab, m);
-      float v = 0.f;
-      for (int s = s_w0; s < s_w1; ++s) {
-        const int cb = s / ntaps;
-        const TapDev tp = a.taps[wk.tap_begin + s - cb * ntaps];
-        const int ih = p.ih + tp.off_h, iw = p.iw + tp.off_w;
-        if ((unsigned)ih >= (unsigned)a.h || (unsigned)iw >= (unsigned)a.w) continue;
-        const float* const xp = (const float*)a.x + (((size_t)p.img * a.h + ih) * a.w + iw) * a.cin;
-        for (int c = 32 * cb; c < min(32 * cb + 32, a.cin); ++c)
-          v = fmaf(xp[c], split_weight(wbase, plane_b, (uint32_t)tp.slot * slot_bytes, a.cin_pad, ch, c), v);
+        for (int r = 0; r < 16; ++r) {
+          red[((i * TC + j) * 16 + r) * 64] = acc[i][j][r];
+          acc[i][j][r] = 0.f;
+        }
+    PixelPos px[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) px[i] = pixel_pos(sg, a.ptab, min(pix0 + 32 * i + row32, wk.m1 - 1));
+    bool w_fin = true;
+    for (int s = s_w0; s < s_w1; ++s) {
+      const int cb = s / ntaps;
+      const TapDev tp = a.taps[wk.tap_begin + s - cb * ntaps];
+      for (int c = 0; c < 2; ++c) {
+        float xv[TP][8], wv[TC][8];
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+          const int ih = px[i].ih + tp.off_h, iw = px[i].iw + tp.off_w;
+          const bool in = ((unsigned)ih < (unsigned)a.h) & ((unsigned)iw < (unsigned)a.w);
+          const uint32_t at = ((uint32_t)px[i].img * (uint32_t)a.h + (uint32_t)ih) * (uint32_t)a.w + (uint32_t)iw;
+#pragma unroll
+          for (int l = 0; l < 2; ++l) {
+            const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
+            const uint32_t v = in & (ch < a.cin) ? (at * (uint32_t)a.cin + (uint32_t)ch) * 4u : OOB;
+            unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, v, 0, 0)),
+                    &xv[i][4 * l]);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < TC; ++j) {
+          uint4 h[3];
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            h[p] = __builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                           wr[p], w_off[j], (uint32_t)tp.slot * slot_bytes + (uint32_t)cb * 2048u + 1024u * c, 0));
+          w_fin &= join_parts(h, wv[j]);
+        }
+        mfma_f32_step<NCHW_OUT>(acc, xv, wv);
       }
-      red[e * 64] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+      for (int j = 0; j < TC; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float* const g = &red[((i * TC + j) * 16 + r) * 64];
+          if (!finite(*g)) *g = acc[i][j][r];
+        }
+    // (until a sum is NaN, which it then stays)
+    if (__any(!w_fin)) {
+      for (int e = 0; e < NREG; ++e) {
+        if (red[e * 64] == red[e * 64]) continue;
+        const int i = e / (16 * TC), j = (e >> 4) % TC, r = e & 15;
+        const int sub = 8 * (r >> 2) + 4 * half + (r & 3);
+        const int m = pix0 + 32 * i + (NCHW_OUT ? row32 : sub);
+        const int ch = ch0 + 32 * j + (NCHW_OUT ? sub : row32);
+        if (m >= wk.m1 || ch >= a.cout) continue;
+        const PixelPos p = pixel_pos(sg, a.ptab, m);
+        float v = 0.f;
+        for (int s = s_w0; s < s_w1 && v == v; ++s) {
+          const int cb = s / ntaps;
+          const TapDev tp = a.taps[wk.tap_begin + s - cb * ntaps];
+          const int ih = p.ih + tp.off_h, iw = p.iw + tp.off_w;
+          if ((unsigned)ih >= (unsigned)a.h || (unsigned)iw >= (unsigned)a.w) continue;
+          const float* const xp = (const float*)a.x + (((size_t)p.img * a.h + ih) * a.w + iw) * a.cin;
+          for (int c = 32 * cb; c < min(32 * cb + 32, a.cin); ++c)
+            v = fmaf(xp[c], split_weight(wbase, plane_b, (uint32_t)tp.slot * slot_bytes, a.cin_pad, ch, c), v);
+        }
+        red[e * 64] = v;
+      }
     }
 #pragma unroll
     for (int i = 0; i < TP; ++i)

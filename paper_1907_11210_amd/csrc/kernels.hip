@@ -2679,39 +2679,52 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           acc[i][j][r] *= kSumUnscale;
-          bad |= !(fabsf(acc[i][j][r]) <= 3.402823466e38f);
+          bad |= !finite(acc[i][j][r]);
         }
     if (__any(bad)) {
-      // through this wave's own piece of LDS, so that the loop over the
-      // results stays a loop (every wave has left the stages behind)
+      // this wave's own piece of LDS keeps the sums meanwhile (every wave has
+      // left the stages behind)
       float* const red = (float*)smem + wave * (TI * TJ * 16 * 64) + lane;
       static_assert(4 * TI * TJ * 16 * 64 * 4 <= 2 * STAGE_B, "room for the sums");
+      size_t ar[TI], br[TJ];
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+        ar[i] = wgrad_a_row(a, min(m0 + wm * 32 * TI + 32 * i + row32, a.ms - 1), 4);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) br[j] = wgrad_b_row(a, min(n + 32 * j, a.nb - 1), 4);
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) red[((i * TJ + j) * 16 + r) * 64] = acc[i][j][r];
-      for (int e = 0; e < TI * TJ * 16; ++e) {
-        if (fabsf(red[e * 64]) <= 3.402823466e38f) continue;
-        const int i = e / (16 * TJ), j = (e >> 4) % TJ, r = e & 15;
-        const int m = mw + 32 * i + 8 * (r >> 2) + (r & 3), c = n + 32 * j;
-        if (m >= a.ms || c >= a.nb) continue;
-        const size_t ar = wgrad_a_row(a, m, 4), br = wgrad_b_row(a, c, 4);
-        float v = 0.f;
-        for (int ks = k_lo; ks < k_hi; ++ks) {
-          const float* const ap = (const float*)(st + ar + wgrad_a_stage(a, ks, KC, 4));
-          const float* const bp = (const float*)(bt + br + wgrad_b_stage(a, ks, KC, 4));
-          for (int k = 0; k < KC; ++k) v = fmaf(ap[k], bp[k], v);
+          for (int r = 0; r < 16; ++r) {
+            red[((i * TJ + j) * 16 + r) * 64] = acc[i][j][r];
+            acc[i][j][r] = 0.f;
+          }
+      for (int ks = k_lo; ks < k_hi; ++ks) {
+        const size_t as = wgrad_a_stage(a, ks, KC, 4), bs = wgrad_b_stage(a, ks, KC, 4);
+        for (int c = 0; c < 2; ++c) {
+          const size_t k = (16 * half + 8 * c) * 4;
+          float av[TI][8], bv[TJ][8];
+#pragma unroll
+          for (int l = 0; l < 2; ++l) {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) unpack4(*(const uint4*)(st + ar[i] + as + k + 16 * l), &av[i][4 * l]);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) unpack4(*(const uint4*)(bt + br[j] + bs + k + 16 * l), &bv[j][4 * l]);
+          }
+          mfma_f32_step<false>(acc, av, bv);
         }
-        red[e * 64] = v;
       }
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = red[((i * TJ + j) * 16 + r) * 64];
+          for (int r = 0; r < 16; ++r) {
+            const float v = red[((i * TJ + j) * 16 + r) * 64];
+            if (finite(v)) acc[i][j][r] = v;
+          }
     }
   }
   // one K slice and one chunk: the gradient itself, else this slice of G

@@ -24,7 +24,7 @@ namespace huge2 {
 // is split exactly into three bf16 parts (split8, which scales it first) and
 // six of the nine products are summed in fp32, leaving out the three that stay
 // below 2^-25 of the product; weights are split once, when packed.  A sum that
-// comes out infinite or NaN is formed again term by term in plain fp32 (an
+// comes out infinite or NaN is formed again in plain fp32 (mfma_f32_step: an
 // operand that is or becomes infinite has no finite parts).
 constexpr int kWkWaves = 8;
 // Up to two bf16 stages are one wave's: there is no chain to shorten, and one
@@ -239,26 +239,29 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
   }
   __syncthreads();
   void* const y = a.y[sg.plan];
-#pragma unroll 2
-  for (int k = 0; k < NREG / kWkWaves; ++k) {
+  // register rr = wave + 8 k of every lane's tile is this wave's to add and store
+  auto total = [&](int k) {
+    float v = 0.f;
+    for (int p = 0; p < nwaves; ++p) v += red[(p * NREG + wave + kWkWaves * k) * 64 + lane];
+    return v;
+  };
+  bool w_fin = true;
+  auto store = [&](int k, float v) {
     const int rr = wave + kWkWaves * k, blk = rr >> 4, r = rr & 15;
     const int i = blk / TC, j = blk % TC;
     const int sub = 8 * (r >> 2) + 4 * half + (r & 3);  // 32x32 MFMA result rows
     const int px = 32 * i + (NCHW_OUT ? row32 : sub), ch = wk.n0 + 32 * j + (NCHW_OUT ? sub : row32);
-    float v = 0.f;
-    for (int p = 0; p < nwaves; ++p) v += red[(p * NREG + rr) * 64 + lane];
     const int4 row = s_row[px];
-    if (row.w < 0 || ch >= a.cout) continue;
+    if (row.w < 0 || ch >= a.cout) return;
     if constexpr (F32) {
-      v *= kSumUnscale;
-      if (!(fabsf(v) <= 3.402823466e38f)) {
+      if (!w_fin && v != v) {
         v = 0.f;
-        for (int t = 0; t < ntaps; ++t) {
+        for (int t = 0; t < ntaps && v == v; ++t) {  // a sum that is NaN stays so
           const int4 ti = s_taps[t];
           const int ih = row.y + ti.z, iw = row.z + ti.w;
           if ((unsigned)ih >= (unsigned)a.h || (unsigned)iw >= (unsigned)a.w) continue;
           const float* const xp = (const float*)((const char*)a.x + ((uint32_t)row.x + (uint32_t)ti.x));
-          for (int c = 0; c < a.cin; ++c)
+          for (int c = 0; c < a.cin && v == v; ++c)
             v = fmaf(xp[c], split_weight(wbase, plane_b, (uint32_t)ti.y, a.cin_pad, ch, c), v);
         }
       }
@@ -269,6 +272,71 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
       ((float*)y)[off] = v;
     else
       ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
+  };
+  if constexpr (!F32) {
+#pragma unroll 2
+    for (int k = 0; k < NREG / kWkWaves; ++k) store(k, total(k));
+  } else {
+    float v[NREG / kWkWaves];
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < NREG / kWkWaves; ++k) {
+      v[k] = total(k) * kSumUnscale;
+      bad |= !finite(v[k]);
+    }
+    if (__syncthreads_or(bad)) {  // (behind it no sum is read any more)
+#pragma unroll
+      for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < TC; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int s = wave; s < nsteps; s += kWkWaves) {
+        const int cb = s / ntaps;
+        const int4 ti = s_taps[s - cb * ntaps];
+        for (int c = 0; c < 2; ++c) {
+          float xv[TP][8], wv[TC][8];
+#pragma unroll
+          for (int i = 0; i < TP; ++i) {
+            const int4 row = s_row[32 * i + row32];
+            const int ih = row.y + ti.z, iw = row.z + ti.w;
+            const bool in = ((unsigned)ih < (unsigned)a.h) & ((unsigned)iw < (unsigned)a.w);
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+              const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
+              const uint32_t at = in & (ch < a.cin) ? (uint32_t)row.x + (uint32_t)ti.x + 4u * ch : OOB;
+              unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0)),
+                      &xv[i][4 * l]);
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < TC; ++j) {
+            uint4 h[3];
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+              h[pl] = *(const uint4*)(wbase + (size_t)pl * plane_b + (uint32_t)ti.y +
+                                      (uint32_t)cb * 2048u + 1024u * c + w_off[j]);
+            w_fin &= join_parts(h, wv[j]);
+          }
+          mfma_f32_step<NCHW_OUT>(acc, xv, wv);
+        }
+      }
+      if (wave < nwaves) {
+#pragma unroll
+        for (int i = 0; i < TP; ++i)
+#pragma unroll
+          for (int j = 0; j < TC; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              red[(wave * NREG + (i * TC + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+      }
+      w_fin = __syncthreads_or(!w_fin) == 0;
+#pragma unroll
+      for (int k = 0; k < NREG / kWkWaves; ++k)
+        if (!finite(v[k])) v[k] = total(k);
+    }
+#pragma unroll
+    for (int k = 0; k < NREG / kWkWaves; ++k) store(k, v[k]);
   }
 }
 
@@ -325,8 +393,8 @@ __global__ __launch_bounds__(256) void pack_split_kernel(const float* __restrict
       }
     }
     // a scaled weight that is or rounds to infinity, or is NaN, has no parts: a
-    // NaN in the first plane sends its sums to the term-by-term path, and the
-    // other two hold its bits (split_weight)
+    // NaN in the first plane has its sums formed again in fp32, and the other
+    // two hold its bits (join_weight)
     const float vs = v * kSplitScale;
     uint16_t h0 = f32_to_bf16_rne(vs), h1, h2;
     if ((h0 & 0x7f80u) != 0x7f80u) {

@@ -110,7 +110,7 @@ def _run(layer, x, w):
 def test_fp32_non_finite(layer):
     """Infinities and NaN in x, and values that round to infinity in bf16,
     give what fp32 arithmetic gives: infinite operands have no finite parts,
-    so these sums are formed again term by term."""
+    so these sums are formed again in fp32."""
     P.say("case", layer)
     x, w = _inputs(layer, 5)
     x, w = x.abs() + 0.1, w.abs() + 0.1  # one sign: the expected sums are known
@@ -131,6 +131,60 @@ def test_fp32_non_finite(layer):
     assert np.any(fin & (np.abs(ref) > 1e33))
     # (the oracle has no infinities to work with: a relative bound instead)
     assert np.all(np.abs(y[fin] - ref[fin]) <= 75 * 2.0 ** -24 * np.abs(ref[fin]))
+
+
+@pytest.mark.parametrize("layer", [l for l, _ in FORMS if l.dtype == "f32"], ids=lambda l: l.name)
+def test_fp32_formed_again(layer):
+    """Sums beyond the scaled parts' range, every one of every fp32 tile, are
+    fp32 sums all the same; an infinite and a NaN weight meet only the outputs
+    that read them inside the input, on each of them."""
+    P.say("case", layer)
+    x, w = _inputs(layer, 19)
+    x, w = x * 1e28, w.abs() + 0.1
+    ref = P.oracle_full(layer, x, w)
+    absref = P.oracle_full(layer, x, w, absolute=True)
+    y = _run(layer, x, w)
+    assert np.all(np.abs(y - ref) <= 75 * 2.0 ** -24 * absref)
+    x = x.abs() + 1e-3
+    for k, bad in ((0, float("inf")), (min(layer.c_out, 70) - 1, float("nan"))):
+        w[(1, k) if layer.transposed else (k, 1)][-1, 0] = bad
+    hit = torch.zeros_like(w)
+    hit[~torch.isfinite(w)] = 1
+    hit = P.oracle_full(layer, torch.ones_like(x), hit) > 0
+    got = _run(layer, x, w)
+    assert np.array_equal(~np.isfinite(got), hit)
+    assert np.isposinf(got[:, 0][hit[:, 0]]).all()
+    assert np.isnan(got[:, min(layer.c_out, 70) - 1][hit[:, min(layer.c_out, 70) - 1]]).all()
+
+
+def _us(f):
+    f()
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    a.record()
+    for _ in range(4):
+        f()
+    b.record()
+    torch.cuda.synchronize()
+    return a.elapsed_time(b) * 250
+
+
+@pytest.mark.parametrize("fill", [float("nan"), float("inf"), 1e30])
+@pytest.mark.parametrize("n,c_in,hw,c_out", [(64, 512, 8, 256), (9, 264, 40, 40), (9, 128, 40, 24)])
+def test_fp32_formed_again_in_time(n, c_in, hw, c_out, fill):
+    """A layer all of whose sums are formed again takes about four times as
+    long (64 x 128, 128 x 64 and wave-K tiles), not hundreds of times."""
+    x = torch.randn(n, c_in, hw, hw, device=DEV)
+    w = torch.rand(c_in, c_out, 4, 4, device=DEV) + 0.1
+    bad = torch.full_like(x, fill)
+    plan = h2.Plan(w, x.shape, True, 2, 1)
+    try:
+        y = plan(x)
+        usual, redone = _us(lambda: plan(x, None, y)), _us(lambda: plan(bad, None, y))
+        assert torch.isnan(y).all() if fill != fill else (y > 1e30).all()
+        P.say("us", plan.kernel, usual, redone)
+        assert redone <= 12 * usual
+    finally:
+        plan.close()
 
 
 @pytest.mark.parametrize("layer", F32, ids=lambda l: l.name)

@@ -82,6 +82,35 @@ def test_non_finite(case):
     assert np.array_equal(rest, np.delete(clean, [1, 2], axis=1))
 
 
+def test_non_finite_in_time():
+    """Gradients whose sums are all formed again (errors of NaN) take a few
+    times as long, not tens of times."""
+    dev = torch.device("cuda", 0)
+    n, ci, h, co = 64, 512, 8, 256
+    x, dy = torch.randn(n, ci, h, h, device=dev), torch.randn(n, co, 2 * h, 2 * h, device=dev)
+    bad = torch.full_like(dy, float("nan"))
+    dw = torch.empty(ci, co, 4, 4, device=dev)
+    plan = h2.huge2_wgrad_plan_create(h2.make_desc(n, ci, h, h, co, 4, 4, 2, 1), True)
+
+    def us(e):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        for i in range(5):
+            if i == 1:
+                a.record()
+            h2.huge2_wgrad_execute(plan, x.data_ptr(), e.data_ptr(), dw.data_ptr(),
+                                   torch.cuda.current_stream(dev).cuda_stream)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) * 250
+    try:
+        usual, redone = us(dy), us(bad)
+        P.say("us", usual, redone)
+        assert torch.isnan(dw).all()
+        assert redone <= 12 * usual
+    finally:
+        h2.huge2_wgrad_plan_destroy(plan)
+
+
 def test_many_columns():
     """5.5M columns (beyond 65535 tiles of 64) of a one-pixel layer: every
     gradient is one product, rounded once."""
