@@ -207,8 +207,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const SegDev& sg, 
 
 // fp32 operands are multiplied by 2^24 before they are split into bf16 parts:
 // the last bit of any float (2^-149 and up) then lies above bf16's smallest
-// normal number and no part underflows.  Operands from 2^104 and sums from 2^80
-// overflow instead, and such sums are formed again (mfma_f32_step).
+// normal number and no part underflows.  Operands from 2^104 and sums from 2^76 to
+// 2^80 are too large instead, and such sums are formed again (mfma_f32_step).
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-24f, kSumUnscale = 0x1p-48f;
 
 // Eight floats, scaled, as three bf16 parts, x = x1 + x2 + x3: each part rounds

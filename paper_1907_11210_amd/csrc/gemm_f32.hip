@@ -286,7 +286,7 @@ __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(Ge
   }
 
   const int pix0 = wk.m0 + wp_i * 32 * TP, ch0 = wk.n0 + wc_i * 32 * TC;
-  bool bad = false;
+  float most[4] = {};  // (finite sums lie below 2^80: so does their total, about)
 #pragma unroll
   for (int i = 0; i < TP; ++i)
 #pragma unroll
@@ -294,9 +294,9 @@ __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(Ge
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         acc[i][j][r] *= kSumUnscale;
-        bad |= !finite(acc[i][j][r]);
+        most[r & 3] += fabsf(acc[i][j][r]);
       }
-  if (__any(bad)) {
+  if (__builtin_expect(__any(!finite(most[0] + most[1] + (most[2] + most[3]))), 0)) {
     // the wave's own piece of LDS keeps the sums meanwhile
 #pragma unroll
     for (int i = 0; i < TP; ++i)

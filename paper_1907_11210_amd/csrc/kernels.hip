@@ -2671,7 +2671,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
   const int n = n0 + wn * 32 * TJ + row32;
   const int mw = m0 + wm * 32 * TI + 4 * half;
   if constexpr (!BF16) {
-    bool bad = false;
+    float most[4] = {};  // (finite sums lie below 2^80: so does their total, about)
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -2679,9 +2679,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           acc[i][j][r] *= kSumUnscale;
-          bad |= !finite(acc[i][j][r]);
+          most[r & 3] += fabsf(acc[i][j][r]);
         }
-    if (__any(bad)) {
+    if (__builtin_expect(__any(!finite(most[0] + most[1] + (most[2] + most[3]))), 0)) {
       // this wave's own piece of LDS keeps the sums meanwhile (every wave has
       // left the stages behind)
       float* const red = (float*)smem + wave * (TI * TJ * 16 * 64) + lane;

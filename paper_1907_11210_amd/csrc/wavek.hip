@@ -53,6 +53,7 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
   __shared__ int4 s_row[BM];           // input byte offset, ih, iw, output offset (-1: none)
   __shared__ int4 s_taps[kMaxLdsTaps];
   __shared__ float s_bias[BN];
+  __shared__ int s_bad;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -85,6 +86,7 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
     const int t = tid - 256;
     s_bias[t] = (bias && wk.n0 + t < a.cout) ? bias[bias_index(a, wk.n0 + t)] : 0.f;
   }
+  if (F32 && tid == 0) s_bad = 0;
   const uint32_t plane_b = a.wp_bytes / NPL;
   const __amdgpu_buffer_rsrc_t xr =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, a.x_bytes, 0x00020000);
@@ -236,6 +238,16 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           red[(wave * NREG + (i * TC + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    if constexpr (F32) {  // below 2^124 the eight add up to a finite sum
+      float most[4] = {};
+#pragma unroll
+      for (int i = 0; i < TP; ++i)
+#pragma unroll
+        for (int j = 0; j < TC; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) most[r & 3] += fabsf(acc[i][j][r]);
+      if (!(most[0] + most[1] + (most[2] + most[3]) <= 0x1p124f)) s_bad = 1;
+    }
   }
   __syncthreads();
   void* const y = a.y[sg.plan];
@@ -273,68 +285,63 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
     else
       ((uint16_t*)y)[off] = f32_to_bf16_rne(v);
   };
-  if constexpr (!F32) {
+  if (!F32 || __builtin_expect(s_bad == 0, 1)) {
 #pragma unroll 2
-    for (int k = 0; k < NREG / kWkWaves; ++k) store(k, total(k));
-  } else {
+    for (int k = 0; k < NREG / kWkWaves; ++k) store(k, F32 ? total(k) * kSumUnscale : total(k));
+  } else if constexpr (F32) {
     float v[NREG / kWkWaves];
-    bool bad = false;
 #pragma unroll
-    for (int k = 0; k < NREG / kWkWaves; ++k) {
-      v[k] = total(k) * kSumUnscale;
-      bad |= !finite(v[k]);
+    for (int k = 0; k < NREG / kWkWaves; ++k) v[k] = total(k) * kSumUnscale;
+    __syncthreads();  // no sum is read any more
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+      for (int j = 0; j < TC; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int s = wave; s < nsteps; s += kWkWaves) {
+      const int cb = s / ntaps;
+      const int4 ti = s_taps[s - cb * ntaps];
+      for (int c = 0; c < 2; ++c) {
+        float xv[TP][8], wv[TC][8];
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+          const int4 row = s_row[32 * i + row32];
+          const int ih = row.y + ti.z, iw = row.z + ti.w;
+          const bool in = ((unsigned)ih < (unsigned)a.h) & ((unsigned)iw < (unsigned)a.w);
+#pragma unroll
+          for (int l = 0; l < 2; ++l) {
+            const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
+            const uint32_t at = in & (ch < a.cin) ? (uint32_t)row.x + (uint32_t)ti.x + 4u * ch : OOB;
+            unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0)),
+                    &xv[i][4 * l]);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < TC; ++j) {
+          uint4 h[3];
+#pragma unroll
+          for (int pl = 0; pl < 3; ++pl)
+            h[pl] = *(const uint4*)(wbase + (size_t)pl * plane_b + (uint32_t)ti.y +
+                                    (uint32_t)cb * 2048u + 1024u * c + w_off[j]);
+          w_fin &= join_parts(h, wv[j]);
+        }
+        mfma_f32_step<NCHW_OUT>(acc, xv, wv);
+      }
     }
-    if (__syncthreads_or(bad)) {  // (behind it no sum is read any more)
+    if (wave < nwaves) {
 #pragma unroll
       for (int i = 0; i < TP; ++i)
 #pragma unroll
         for (int j = 0; j < TC; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      for (int s = wave; s < nsteps; s += kWkWaves) {
-        const int cb = s / ntaps;
-        const int4 ti = s_taps[s - cb * ntaps];
-        for (int c = 0; c < 2; ++c) {
-          float xv[TP][8], wv[TC][8];
-#pragma unroll
-          for (int i = 0; i < TP; ++i) {
-            const int4 row = s_row[32 * i + row32];
-            const int ih = row.y + ti.z, iw = row.z + ti.w;
-            const bool in = ((unsigned)ih < (unsigned)a.h) & ((unsigned)iw < (unsigned)a.w);
-#pragma unroll
-            for (int l = 0; l < 2; ++l) {
-              const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
-              const uint32_t at = in & (ch < a.cin) ? (uint32_t)row.x + (uint32_t)ti.x + 4u * ch : OOB;
-              unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0)),
-                      &xv[i][4 * l]);
-            }
-          }
-#pragma unroll
-          for (int j = 0; j < TC; ++j) {
-            uint4 h[3];
-#pragma unroll
-            for (int pl = 0; pl < 3; ++pl)
-              h[pl] = *(const uint4*)(wbase + (size_t)pl * plane_b + (uint32_t)ti.y +
-                                      (uint32_t)cb * 2048u + 1024u * c + w_off[j]);
-            w_fin &= join_parts(h, wv[j]);
-          }
-          mfma_f32_step<NCHW_OUT>(acc, xv, wv);
-        }
-      }
-      if (wave < nwaves) {
-#pragma unroll
-        for (int i = 0; i < TP; ++i)
-#pragma unroll
-          for (int j = 0; j < TC; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              red[(wave * NREG + (i * TC + j) * 16 + r) * 64 + lane] = acc[i][j][r];
-      }
-      w_fin = __syncthreads_or(!w_fin) == 0;
-#pragma unroll
-      for (int k = 0; k < NREG / kWkWaves; ++k)
-        if (!finite(v[k])) v[k] = total(k);
+          for (int r = 0; r < 16; ++r)
+            red[(wave * NREG + (i * TC + j) * 16 + r) * 64 + lane] = acc[i][j][r];
     }
+    w_fin = __syncthreads_or(!w_fin) == 0;
+#pragma unroll
+    for (int k = 0; k < NREG / kWkWaves; ++k)
+      if (!finite(v[k])) v[k] = total(k);
 #pragma unroll
     for (int k = 0; k < NREG / kWkWaves; ++k) store(k, v[k]);
   }
