@@ -898,7 +898,13 @@ long long count_works(const huge2_conv_desc& d, bool transposed, int class_split
 // at once and the split's ragged segments add works beyond the resident
 // slots, form 0 wins: such a straggler starts only when a unit frees and
 // adds its whole latency (measured on the odd-kernel layer, 512 against 514
-// works: 21.3 against 25.1 us).  Both forms are built once, here.
+// works: 21.3 against 25.1 us).  Both forms are built once, here.  That line lies
+// at the slots there are (tile_per_cu: one wave-K workgroup of fp32 to a unit;
+// 64 -> 30 channels 5x5 on 10 x 39 x 42, 256 works whole 15.9 us, split into more
+// 23.4).  The schedule model keeps two to a unit for them: beyond one round its choices then measured faster (200
+// -> 5 channels, dilation 4, on 12 x 45 x 33, 288 works 25.2 against 34.5 us), and
+// the order of works by it too (256 -> 19 5x5 on 9 x 24 x 24, 324 works, 26.2
+// against 38.7).
 bool choose_shape(const huge2_conv_desc& d, bool transposed, int cfg, PlanShape* shape) {
   const int bm = tile_bm(cfg);
   const int forced = env_int("HUGE2_CLASS_SPLIT", -1);
@@ -906,7 +912,7 @@ bool choose_shape(const huge2_conv_desc& d, bool transposed, int cfg, PlanShape*
   PlanShape s0;
   if (!build_shape(d, transposed, 2, bm, shape)) return false;
   if (!build_shape(d, transposed, 0, bm, &s0)) return true;
-  const long long slots = (long long)kComputeUnits * kTiles[cfg].wg_per_cu;
+  const long long slots = (long long)kComputeUnits * tile_per_cu(cfg, d.dtype);
   const long long w0 = count_works(d, s0, cfg), w2 = count_works(d, *shape, cfg);
   if ((w0 <= slots && w2 > slots) || makespan_stages(d, s0, cfg) < makespan_stages(d, *shape, cfg))
     std::swap(*shape, s0);
@@ -926,6 +932,14 @@ int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* l
   const int force = env_int("HUGE2_LISTED", -1);
   if (!tr && force != 0 && build_listed(d, tile_bm(cfg), ls))
     *listed = force == 1 || makespan_listed(d, *ls, cfg) <= makespan_stages(d, *shape, cfg);
+  // the segment form alone fits one round of the slots there are: the line that
+  // the model, with two wave-K workgroups of fp32 to a unit, does not see (32 ->
+  // 20 channels 4x4 on 10 x 38 x 47: 12.1 against 16.8 us listed)
+  const long long slots = (long long)kComputeUnits * tile_per_cu(cfg, d.dtype);
+  if (*listed && force != 1 && tile_per_cu(cfg, d.dtype) != kTiles[cfg].wg_per_cu &&
+      count_works(d, *shape, cfg) <= slots &&
+      (long long)d.n * ls->tile_taps.size() * ((d.c_out + tile_bn(cfg) - 1) / tile_bn(cfg)) > slots)
+    *listed = false;
   return cfg;
 }
 

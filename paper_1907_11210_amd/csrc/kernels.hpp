@@ -108,8 +108,8 @@ struct GemmArgs {
 // depth: stages of global loads in flight ahead of the MFMAs (1 or 2; each
 // in-flight stage costs one register buffer).
 // wg_per_cu: workgroups of this shape that fit on one compute unit at once
-// (the tighter of the register and LDS limits; the same for both dtypes and
-// layouts), used by the host's schedule model.
+// (the tighter of the register and LDS limits), used by the host's schedule
+// model through tile_per_cu.
 // kind 0: both operands through LDS, PW x CW waves of (BM/PW) x (BN/CW).
 // kind 1: split-wave form, the pixel tile through LDS, CW waves each loading
 //         BN/CW weight rows itself (PW = 1) from lane-ordered packed weights.
@@ -184,6 +184,10 @@ constexpr int kPackKB = 64;
 // Byte offset, inside a K stage, of MFMA K chunk c for lane half `half`.
 __host__ __device__ constexpr int pack_chunk_byte(int c, int half) {
   return (c / (kPackKB / 32)) * kPackKB + half * (kPackKB / 2) + (c % (kPackKB / 32)) * 16;
+}
+// (the wave-K forms of fp32 hold 122 KiB of LDS and more, one to a unit)
+inline int tile_per_cu(int cfg, int dtype) {
+  return kTiles[cfg].kind == 4 && dtype != 1 ? 1 : kTiles[cfg].wg_per_cu;
 }
 inline int tile_bm(int cfg) { return kTiles[cfg].bm; }
 inline int tile_bn(int cfg) { return kTiles[cfg].bn; }

@@ -212,3 +212,19 @@ def test_mac_counts_of_the_special_forms():
         nz, issued = h2.huge2_plan_macs(d, 1)
         assert nz == expect
         assert issued >= nz
+
+
+# fp32, wave-K tiles of 64 x 32, one workgroup to a compute unit: transposed, n,
+# c_in, h, w, c_out, k, dilation (stride 1, 'same' size), layout, tiles
+@pytest.mark.parametrize("tr,n,ci,h,w,co,k,dl,layout,tiles", [
+    (1, 10, 64, 39, 42, 30, 5, 1, 1, 256),
+    (1, 12, 32, 37, 33, 11, 4, 2, 1, 256),
+    (0, 10, 32, 38, 47, 20, 4, 2, 0, 254),  # listed, it would have more tiles
+])
+def test_one_round_of_fp32_wave_k_works(tr, n, ci, h, w, co, k, dl, layout, tiles):
+    """Works that fit the 256 compute units unsplit stay so: with two to a
+    unit counted, the border classes' extra works looked free."""
+    desc = h2.make_desc(n, ci, h, w, co, k, k, 1, (k - 1) // 2 * dl, 0, dl, layout,
+                        h2.HUGE2_F32)
+    _, issued = h2.huge2_plan_macs(desc, tr)
+    assert issued == tiles * 64 * 32 * k * k * ((ci + 31) // 32 * 32)
