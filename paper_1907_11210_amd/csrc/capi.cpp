@@ -285,11 +285,12 @@ void order_works_for_xcds(std::vector<WorkDev>& works, const std::vector<SegDev>
   const int b = best_b, a = 8 / best_b;
   struct Key {
     int64_t cell, pos;
-    WorkDev w;
+    int work;
   };
   std::vector<Key> keys;
   keys.reserve(works.size());
-  for (const WorkDev& w : works) {
+  for (size_t i = 0; i < works.size(); ++i) {
+    const WorkDev& w = works[i];
     const SegDev& sg = segs[w.seg];
     int64_t j = w.m0;
     j /= sg.qn_w;
@@ -304,18 +305,24 @@ void order_works_for_xcds(std::vector<WorkDev>& works, const std::vector<SegDev>
     Key k;
     k.cell = row * b + col;
     k.pos = pos;
-    k.w = w;
+    k.work = (int)i;
     keys.push_back(k);
   }
-  std::stable_sort(keys.begin(), keys.end(), [](const Key& x, const Key& y) {
+  const auto before = [&](const Key& x, const Key& y) {
     if (x.cell != y.cell) return x.cell < y.cell;
     if (x.pos != y.pos) return x.pos < y.pos;
-    if (x.w.seg != y.w.seg) return x.w.seg < y.w.seg;
-    if (x.w.m0 != y.w.m0) return x.w.m0 < y.w.m0;
-    if (x.w.n0 != y.w.n0) return x.w.n0 < y.w.n0;
-    return x.w.ks < y.w.ks;
-  });
-  for (size_t i = 0; i < works.size(); ++i) works[i] = keys[i].w;
+    const WorkDev &p = works[x.work], &q = works[y.work];
+    if (p.seg != q.seg) return p.seg < q.seg;
+    if (p.m0 != q.m0) return p.m0 < q.m0;
+    if (p.n0 != q.n0) return p.n0 < q.n0;
+    return p.ks < q.ks;
+  };
+  if (std::is_sorted(keys.begin(), keys.end(), before)) return;
+  std::stable_sort(keys.begin(), keys.end(), before);
+  std::vector<WorkDev> out;
+  out.reserve(works.size());
+  for (const Key& k : keys) out.push_back(works[k.work]);
+  works.swap(out);
 }
 
 // Works that are all resident at once (at most 32 x wg_per_cu per XCD).  The
@@ -335,38 +342,51 @@ void order_works_resident(std::vector<WorkDev>& works, int cblocks, int ksplit, 
   const int g8 = (g + 7) / 8, r = g % 8;
   constexpr int kUnits = kComputeUnits / 8;
   if (g8 > kUnits * wg_per_cu + kUnits) return;  // several rounds: the dispatcher balances
-  auto cost = [&](const WorkDev& w) {
+  std::vector<int64_t> cost(g);
+  for (int i = 0; i < g; ++i) {
+    const WorkDev& w = works[i];
     const int cb = (w.ks + 1) * cblocks / ksplit - w.ks * cblocks / ksplit;
-    return (int64_t)w.tap_count * cb + 2;
-  };
+    cost[i] = (int64_t)w.tap_count * cb + 2;
+  }
   std::vector<WorkDev> out(works.size());
+  std::vector<int> idx, held, count, by_size;
   for (int x = 0; x < 8; ++x) {
     const int start = (r == 0 || x < r) ? x * g8 : r * g8 + (x - r) * (g8 - 1);
     const int len = (r == 0 || x < r) ? g8 : g8 - 1;
-    std::vector<int> idx(len);
-    for (int i = 0; i < len; ++i) idx[i] = start + i;
-    std::stable_sort(idx.begin(), idx.end(),
-                     [&](int a, int b) { return cost(works[a]) > cost(works[b]); });
     const int resident = std::min(len, kUnits * wg_per_cu);
     const int units = std::min(len, kUnits);
-    std::vector<int64_t> load(units, 0);
-    std::vector<std::vector<int>> held(units);
-    for (int i = 0; i < resident; ++i) {
-      int best = -1;
-      for (int u = 0; u < units; ++u)
-        if ((int)held[u].size() < wg_per_cu && (best < 0 || load[u] < load[best])) best = u;
-      held[best].push_back(idx[i]);
-      load[best] += cost(works[idx[i]]);
-    }
-    // units holding more works first, so that every level is a prefix
-    std::stable_sort(held.begin(), held.end(), [](const std::vector<int>& a,
-                                                  const std::vector<int>& b) {
-      return a.size() > b.size();
-    });
+    idx.resize(len);
+    for (int i = 0; i < len; ++i) idx[i] = start + i;
     int pos = start;
-    for (int level = 0; level < wg_per_cu; ++level)
-      for (int u = 0; u < units; ++u)
-        if ((int)held[u].size() > level) out[pos++] = works[held[u][level]];
+    const auto c0 = cost.begin() + start;
+    if (std::all_of(c0, c0 + len, [&](int64_t c) { return c == *c0; })) {
+      // equal works (a pointwise layer's 512) are dealt in order: unit k gets
+      // works k, k + 32, ..., which is where they are
+      for (int i = 0; i < resident; ++i) out[pos++] = works[idx[i]];
+    } else {
+      std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+      // (load, unit) of the units with a free slot, the least loaded first
+      typedef std::pair<int64_t, int> Unit;
+      std::priority_queue<Unit, std::vector<Unit>, std::greater<Unit>> open;
+      for (int u = 0; u < units; ++u) open.push({0, u});
+      held.assign(units * wg_per_cu, 0);
+      count.assign(units, 0);
+      for (int i = 0; i < resident; ++i) {
+        const Unit at = open.top();
+        open.pop();
+        const int u = at.second;
+        held[u * wg_per_cu + count[u]++] = idx[i];
+        if (count[u] < wg_per_cu) open.push({at.first + cost[idx[i]], u});
+      }
+      // units holding more works first, so that every level is a prefix
+      by_size.resize(units);
+      for (int u = 0; u < units; ++u) by_size[u] = u;
+      std::stable_sort(by_size.begin(), by_size.end(),
+                       [&](int a, int b) { return count[a] > count[b]; });
+      for (int level = 0; level < wg_per_cu; ++level)
+        for (int u : by_size)
+          if (count[u] > level) out[pos++] = works[held[u * wg_per_cu + level]];
+    }
     for (int i = len - 1; i >= resident; --i) out[pos++] = works[idx[i]];
   }
   works.swap(out);

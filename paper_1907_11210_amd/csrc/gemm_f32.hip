@@ -324,7 +324,7 @@ __global__ __launch_bounds__(PW * CW * KS * 64, 2) void phase_gemm_f32_kernel(Ge
 #pragma unroll
           for (int l = 0; l < 2; ++l) {
             const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
-            const uint32_t v = in & (ch < a.cin) ? (at * (uint32_t)a.cin + (uint32_t)ch) * 4u : OOB;
+            const uint32_t v = (in & (ch < a.cin)) ? (at * (uint32_t)a.cin + (uint32_t)ch) * 4u : OOB;
             unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, v, 0, 0)),
                     &xv[i][4 * l]);
           }

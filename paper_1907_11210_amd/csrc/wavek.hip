@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kWkWaves * 64) void wavek_kernel(GemmArgs a) {
 #pragma unroll
           for (int l = 0; l < 2; ++l) {
             const int ch = 32 * cb + 16 * half + 8 * c + 4 * l;
-            const uint32_t at = in & (ch < a.cin) ? (uint32_t)row.x + (uint32_t)ti.x + 4u * ch : OOB;
+            const uint32_t at = (in & (ch < a.cin)) ? (uint32_t)row.x + (uint32_t)ti.x + 4u * ch : OOB;
             unpack4(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0)),
                     &xv[i][4 * l]);
           }

@@ -1,4 +1,6 @@
 """GPU tests of the wave-K form and of fp32 on the bf16 matrix cores."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -97,6 +99,30 @@ def test_two_stages_keep_the_order_of_one_sum(n, c_in, c_out, layout, monkeypatc
     kernel, want = run()
     assert " 32x256 " in kernel
     assert np.array_equal(y, want)
+
+
+def test_projection_plan_in_time(monkeypatch):
+    """A plan of 512 equal works is laid out about as fast as one of 64: a
+    program with new weights pays for it."""
+    layer = L("proj", True, 1, 100, 1, 1, 1024, 4, 1, 0, 0, 1, "NCHW", "bf16")
+    P.say("case", layer)
+    w = torch.zeros(100, 1024, 4, 4, dtype=torch.bfloat16, device=DEV)
+
+    def us():
+        t = []
+        for _ in range(40):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            plan = P.make_plan(layer, w)
+            t.append(time.perf_counter() - t0)
+            plan.close()
+        return sorted(t)[len(t) // 2] * 1e6
+    us()
+    many = us()
+    monkeypatch.setenv("HUGE2_TILE", "5")
+    few = us()
+    P.say("us", many, few)
+    assert many <= 1.4 * few
 
 
 F32 = [l for l, _ in FORMS if l.name in ("wk_f32", "f32_128x64", "f32_64x128", "f32_splitk")]
