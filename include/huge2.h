@@ -317,6 +317,13 @@ huge2_status huge2_wgrad_plan_create(huge2_wgrad_plan** out, const huge2_conv_de
 huge2_status huge2_wgrad_execute(const huge2_wgrad_plan* plan, const void* x, const void* dy,
                                  void* dw, void* hip_stream);
 
+/* Name of the main kernel a weight-gradient plan launches: its tile, its K
+ * slices and how the large tensor's copies are made, e.g. "wgrad_gemm_kernel
+ * 64x128 k8 gather2" (workgroups of 2 images; gather0: the plain staging
+ * kernel; " phase": in phase planes).  Storage and errors as
+ * huge2_plan_kernel. */
+const char* huge2_wgrad_plan_kernel(const huge2_wgrad_plan* plan);
+
 /* Release a weight-gradient plan; waits for the device first.  NULL is
  * accepted.  Errors: HIP. */
 huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan);

@@ -2226,6 +2226,7 @@ struct huge2_wgrad_plan {
   int bt_phase;        // Bt in phase planes (WgArgs::bt_phase)
   int hr, sh_min;
   int direct;          // St read in place from the small tensor (WgArgs::direct)
+  char kernel_name[64];
   Buffers bufs;  // the three below
   void* st;
   void* bt;
@@ -2280,6 +2281,7 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
     p->groups = d.groups;
     p->chunk = d.n;
     p->ksplit = 1;
+    std::snprintf(p->kernel_name, sizeof(p->kernel_name), "wgrad_grouped_kernel g%d", d.groups);
     *out = p;
     return HUGE2_OK;
   }
@@ -2296,10 +2298,12 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   // (HUGE2_WGRAD_DIRECT=0: always staged)
   p->direct = hws % 64 == 0 && env_int("HUGE2_WGRAD_DIRECT", 1) != 0;
   // the large tensor's copies through LDS where its planes fit
-  // (HUGE2_WGRAD_GATHER=0: the plain staging kernel gathers them)
-  p->gather_ib = env_int("HUGE2_WGRAD_GATHER", 1) != 0
+  // (HUGE2_WGRAD_GATHER=0: the plain staging kernel gathers them; 2: through
+  // LDS also below wgrad_gather_images' line)
+  const int gather = env_int("HUGE2_WGRAD_GATHER", 1);
+  p->gather_ib = gather != 0
                      ? wgrad_gather_images(p->hs, p->ws, p->hb, p->wb, (int)esz, (int)chunk, p->nb,
-                                           (int)taps)
+                                           (int)taps, gather == 2)
                      : 0;
   // phase planes instead of per-tap copies where a K stage lies in one image
   // and the planes (hr rows each) are smaller than the taps' copies
@@ -2364,6 +2368,8 @@ huge2_status wgrad_create(huge2_wgrad_plan** out, const huge2_conv_desc* desc, i
   p->kp = (int)kp;
   p->tile = wt;
   p->ksplit = (int)ksplit;
+  std::snprintf(p->kernel_name, sizeof(p->kernel_name), "wgrad_gemm_kernel %dx%d k%d gather%d%s",
+                wt.m, wt.n, p->ksplit, p->gather_ib, p->bt_phase ? " phase" : "");
   Mem mem;
   mem.stream_ordered = stream_ordered;
   st = allocate(&p->bufs, {{&p->st, (size_t)st_b}, {&p->bt, (size_t)bt_b}, {(void**)&p->g, (size_t)g_b}},
@@ -2843,6 +2849,10 @@ huge2_status huge2_wgrad_execute(const huge2_wgrad_plan* plan, const void* x, co
   } catch (...) {
     return HUGE2_ERR_ALLOC;
   }
+}
+
+const char* huge2_wgrad_plan_kernel(const huge2_wgrad_plan* plan) {
+  return plan ? plan->kernel_name : "";
 }
 
 huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan) {

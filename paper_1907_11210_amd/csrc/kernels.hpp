@@ -522,9 +522,10 @@ hipError_t launch_wgrad_grouped(const WgArgs& a, int dtype, hipStream_t stream);
 // shares a launch with the small tensor's, so it keeps less than 6M elements
 // (2.8M: 12.8 us against 11.2 and the other launch's 4).
 constexpr int kWgGatherLds = 32 * 1024;
-inline int wgrad_gather_images(int hs, int ws, int hb, int wb, int esz, int nimg, int nb, int taps) {
+inline int wgrad_gather_images(int hs, int ws, int hb, int wb, int esz, int nimg, int nb, int taps,
+                               bool any_size) {
   const long long plane = (long long)hb * wb * esz;
-  if ((hs * ws) % 8 != 0 && (long long)hs * ws * nimg * nb * taps < (6 << 20)) return 0;
+  if (!any_size && (hs * ws) % 8 != 0 && (long long)hs * ws * nimg * nb * taps < (6 << 20)) return 0;
   const bool pairs = esz == 2 && ((long long)hs * ws) % 2 != 0 && nimg > 1;
   if (plane > kWgGatherLds) return 0;
   long long ib = (long long)nimg * nb / 1024;

@@ -31,6 +31,7 @@ EXPORTED = (
     "huge2_plan_destroy", "huge2_conv2d_transpose", "huge2_conv2d_dilated",
     "huge2_plan_describe", "huge2_plan_macs",
     "huge2_wgrad_plan_create", "huge2_wgrad_execute", "huge2_wgrad_plan_destroy",
+    "huge2_wgrad_plan_kernel",
     "huge2_conv2d_transpose_wgrad", "huge2_conv2d_dilated_wgrad",
     "huge2_group_create", "huge2_group_execute", "huge2_group_destroy", "huge2_group_kernel",
     "huge2_conv2d_transpose_noalloc", "huge2_dgrad_output_padding",
@@ -94,6 +95,7 @@ def lib():
         L.huge2_wgrad_plan_create.argtypes = [ctypes.POINTER(vp), dp, i32]
         L.huge2_wgrad_execute.argtypes = [vp, vp, vp, vp, vp]
         L.huge2_wgrad_plan_destroy.argtypes = [vp]
+        L.huge2_wgrad_plan_kernel.argtypes = [vp]
         L.huge2_conv2d_transpose_wgrad.argtypes = [dp, vp, vp, vp, vp]
         L.huge2_conv2d_dilated_wgrad.argtypes = [dp, vp, vp, vp, vp]
         L.huge2_group_create.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp), i32, vp]
@@ -105,6 +107,7 @@ def lib():
         for name in EXPORTED[1:]:
             getattr(L, name).restype = ctypes.c_int
         L.huge2_plan_kernel.restype = ctypes.c_char_p
+        L.huge2_wgrad_plan_kernel.restype = ctypes.c_char_p
         L.huge2_group_kernel.restype = ctypes.c_char_p
         _lib = L
     return _lib
@@ -243,6 +246,10 @@ def huge2_wgrad_execute(plan, x_ptr, dy_ptr, dw_ptr, stream=0):
     _check(lib().huge2_wgrad_execute(plan, ctypes.c_void_p(x_ptr), ctypes.c_void_p(dy_ptr),
                                      ctypes.c_void_p(dw_ptr), ctypes.c_void_p(stream)),
            "huge2_wgrad_execute")
+
+
+def huge2_wgrad_plan_kernel(plan):
+    return lib().huge2_wgrad_plan_kernel(plan).decode()
 
 
 def huge2_wgrad_plan_destroy(plan):

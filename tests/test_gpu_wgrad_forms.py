@@ -20,16 +20,34 @@ CASES = [
     ("odd_many_channels", False, 7, 520, 5, 5, 24, 3, 3, 1, 1, 0, 1, "bf16"),
     ("even_pixels", True, 3, 33, 5, 6, 10, 4, 4, 2, 1, 0, 1, "bf16"),
     ("odd_f32", False, 3, 10, 11, 13, 33, 5, 5, 2, 2, 0, 1, "f32"),
-    # tiles: 64 x 64, 64 x 128, 128 x 64, 128 x 128 with remainders
+    # a plane of almost 32 KiB, doubled to a pair of images
+    ("odd_large_plane", False, 3, 5, 127, 127, 6, 3, 3, 1, 1, 0, 1, "bf16"),
+    # few columns or rows, all on 64 x 64 tiles; 128 x 64 and more of both
     ("tile_64_64", False, 2, 60, 8, 9, 64, 1, 1, 1, 0, 0, 1, "bf16"),
-    ("tile_64_128", True, 2, 61, 6, 7, 17, 3, 3, 2, 1, 1, 1, "bf16"),
-    ("tile_128_64", True, 2, 130, 6, 7, 3, 4, 4, 2, 1, 0, 1, "bf16"),
-    ("tile_128_128", False, 3, 30, 12, 11, 129, 3, 3, 1, 1, 0, 1, "bf16"),
+    ("short_64_128", True, 2, 61, 6, 7, 17, 3, 3, 2, 1, 1, 1, "bf16"),
+    ("short_128_64", True, 2, 130, 6, 7, 3, 4, 4, 2, 1, 0, 1, "bf16"),
+    ("short_128_128", False, 3, 30, 12, 11, 129, 3, 3, 1, 1, 0, 1, "bf16"),
     ("tile_f32_128", False, 2, 30, 12, 11, 129, 3, 3, 1, 1, 0, 1, "f32"),
     ("tile_f32_64", False, 2, 66, 9, 9, 40, 1, 1, 1, 0, 0, 1, "f32"),
     # one K slice, fewer stages than the loads run ahead
     ("short_k", False, 1, 66, 4, 4, 66, 2, 2, 1, 0, 0, 1, "f32"),
 ]
+
+
+# of an odd pixel count in 16 bits and several images: pairs of images
+PAIRS = ("odd_pixels", "odd_many_channels", "odd_large_plane")
+
+
+def _kernel(case):
+    """The kernel that the case's plan names."""
+    _, tr, n, ci, h, w, co, r, s, st, pd, op, dl, dt = case
+    plan = h2.huge2_wgrad_plan_create(
+        h2.make_desc(n, ci, h, w, co, r, s, st, pd, op, dl,
+                     dtype=h2.HUGE2_BF16 if dt == "bf16" else h2.HUGE2_F32), tr)
+    try:
+        return h2.huge2_wgrad_plan_kernel(plan)
+    finally:
+        h2.huge2_wgrad_plan_destroy(plan)
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: c[0])
@@ -39,6 +57,8 @@ def test_forms(case, monkeypatch):
     P.say("case", case)
     xq, dyq = W._inputs(case, seed=21)
     ref, absref = W._oracle(case, xq, dyq), W._oracle(case, xq, dyq, absolute=True)
+    monkeypatch.setenv("HUGE2_WGRAD_GATHER", "2")
+    assert int(_kernel(case).split("gather")[1]) >= (2 if case[0] in PAIRS else 1)
     got = W._gpu(case, xq, dyq)
     P.check(got, ref, absref, case[-1], case[0])
     if case[-1] == "f32":
@@ -46,7 +66,56 @@ def test_forms(case, monkeypatch):
         # most 512 terms round within 2^-24 of the largest partial sum each
         assert np.all(np.abs(got - ref) <= 24 * 2.0 ** -24 * absref + 1e-30)
     monkeypatch.setenv("HUGE2_WGRAD_GATHER", "0")
+    assert "gather0" in _kernel(case)
     assert np.array_equal(got, W._gpu(case, xq, dyq))
+
+
+@pytest.mark.parametrize("case", [c for c in CASES if c[0] in ("odd_pixels", "odd_large_plane")],
+                         ids=lambda c: c[0])
+def test_gather_of_a_last_single_image(case, monkeypatch):
+    """Chunks of two images of an odd pixel count, the last of one: the pair's
+    second half is not there to read."""
+    P.say("case", case)
+    xq, dyq = W._inputs(case, seed=22)
+    monkeypatch.setenv("HUGE2_WGRAD_CHUNK", "2")
+    monkeypatch.setenv("HUGE2_WGRAD_GATHER", "2")
+    assert "gather2" in _kernel(case)
+    got = W._gpu(case, xq, dyq)
+    P.check(got, W._oracle(case, xq, dyq), W._oracle(case, xq, dyq, absolute=True), case[-1], case[0])
+    monkeypatch.setenv("HUGE2_WGRAD_GATHER", "0")
+    assert np.array_equal(got, W._gpu(case, xq, dyq))
+
+
+# enough work for wide tiles (from 4096 tiles of 64 x 64 times 128-byte stages)
+TILES = [
+    ("64x128", False, 8, 61, 60, 61, 60, 3, 3, 1, 1, 0, 1, "bf16"),
+    ("128x64", False, 4, 3, 124, 124, 1030, 4, 4, 2, 1, 0, 1, "bf16"),
+    ("128x128", True, 6, 100, 49, 50, 61, 3, 3, 1, 1, 0, 1, "bf16"),
+]
+
+
+@pytest.mark.parametrize("case", TILES, ids=lambda c: c[0])
+def test_wide_tiles(case):
+    """The 64 x 128, 128 x 64 and 128 x 128 tiles with remainders on both
+    sides, against sums in float64."""
+    P.say("case", case)
+    assert "kernel " + case[0] + " " in _kernel(case)
+    name, tr, n, ci, h, w, co, r, s, st, pd, op, dl, dt = case
+    xq, dyq = W._inputs(case, seed=27)
+    # per tap, a product of two matrices: the small tensor and the large one's tap
+    sm, bg = (xq, dyq) if tr else (dyq, xq)
+    bg = torch.nn.functional.pad(bg.double(), (pd, r, pd, r))
+    hs, ws = sm.shape[2:]
+    a = sm.double().transpose(0, 1).flatten(1)
+    ref = np.empty(tuple(W._w_shape(case)))
+    absref = np.empty_like(ref)
+    for kh in range(r):
+        for kw in range(s):
+            b = bg[:, :, kh:kh + (hs - 1) * st + 1:st, kw:kw + (ws - 1) * st + 1:st]
+            b = b.transpose(0, 1).flatten(1).t().contiguous()
+            ref[:, :, kh, kw] = (a @ b).numpy()
+            absref[:, :, kh, kw] = (a.abs() @ b.abs()).numpy()
+    P.check(W._gpu(case, xq, dyq), ref, absref, case[-1], case[0])
 
 
 @pytest.mark.parametrize("scale", [1e-36, 1e-41, 1e27])
