@@ -20,8 +20,9 @@ from paper_1907_11210_amd import workloads as wl
 TOL = {"f32": 1e-4, "bf16": 2e-2}
 
 
-def tile_count():
-    """Number of GEMM tile configurations (entries of kTiles in kernels.hpp)."""
+def tiles():
+    """The GEMM tile configurations, (pixels, channels, kind) of every entry of
+    kTiles in kernels.hpp."""
     import os
     import re
     src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
@@ -29,7 +30,8 @@ def tile_count():
     text = open(src).read()
     body = text[text.index("kTiles[] = {"):]
     body = body[:body.index("};")]
-    return len(re.findall(r"\{\s*\d+\s*,", body))
+    return [(v[0], v[1], v[7]) for v in
+            ([int(n) for n in m.split(",")] for m in re.findall(r"\{([\d, ]+)\}", body))]
 
 
 def say(*a):

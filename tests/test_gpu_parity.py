@@ -305,21 +305,28 @@ def test_workload_full_size_sampled(wname):
         assert np.all(np.isfinite(y))
 
 
-TILE_CONFIGS = list(range(P.tile_count()))  # every GEMM tile configuration
+TILES = P.tiles()  # every GEMM tile configuration
 
 
-@pytest.mark.parametrize("tile", TILE_CONFIGS)
+@pytest.mark.parametrize("tile", range(len(TILES)))
 def test_every_tile_configuration(tile, monkeypatch):
     """Each tile shape (forced through HUGE2_TILE at plan creation) matches the
-    oracle on ragged transposed and dilated cases in both layouts and dtypes."""
+    oracle on ragged transposed and dilated cases in both layouts and in the
+    dtypes that it takes (kind 4 both, kind 5 fp32, the others bf16)."""
     monkeypatch.setenv("HUGE2_TILE", str(tile))
-    for layer in [SMALL[0], SMALL[2], SMALL[4], SMALL[7], SMALL[14], SMALL[19]]:
+    bm, bn, kind = TILES[tile]
+    dtypes = {4: ("bf16", "f32"), 5: ("f32",)}.get(kind, ("bf16",))
+    for layer, dtype in [(SMALL[i], dt) for i in (0, 2, 4, 7, 14, 19) for dt in dtypes]:
+        layer = layer.with_(dtype=dtype)
         P.say("case tile", tile, layer)
         xq, wq = _inputs(layer, seed=31 + tile)
         bias = torch.linspace(-0.25, 0.75, layer.c_out)
         ref = P.oracle_full(layer, xq, wq, bias)
         absref = P.oracle_full(layer, xq, wq, bias, absolute=True)
-        y = P.run_gpu(layer, xq, wq, bias)
+        plan = P.make_plan(layer, wq.to(torch.device("cuda", 0)))
+        assert " %dx%d" % (bm, bn) in plan.kernel, plan.kernel
+        y = P.run_gpu(layer, xq, wq, bias, plan=plan)
+        plan.close()
         P.check(y, ref, absref, layer.dtype, "%s tile %d" % (layer.name, tile))
 
 
