@@ -970,10 +970,11 @@ int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* l
 // than the kernels of a short layer.  Blocks are therefore kept between calls:
 // a call takes an idle block of its device and leaves it with an event
 // recorded behind its work; the next call, on any stream and thread, orders
-// its own work behind that event.  At most 512 MiB a GPU are kept (the largest
-// weight gradient's workspace is under 320), in at most 16 blocks in all; larger or further buffers are stream-ordered allocations.
-// Destroying any plan gives idle blocks back, and so does an allocation that
-// fails or would exceed the bound.
+// its own work behind that event.  At most 512 MiB a GPU are kept (a weight
+// gradient's workspace is under 320 unless one image's copies exceed its chunk
+// budget), in at most 16 blocks in all; larger or further buffers are
+// stream-ordered allocations.  Destroying any plan gives idle blocks back, and so does an allocation that fails or would exceed the
+// bound.
 constexpr size_t kBlockKeepBytes = (size_t)512 << 20;
 constexpr int kMaxBlocks = 16;
 struct Block {
@@ -986,16 +987,28 @@ struct Block {
 std::mutex g_blocks_mutex;
 Block g_blocks[kMaxBlocks];
 
+// Allocating, freeing and asking for an event end a capture that any thread of
+// the process runs in the global mode, unless the calling thread takes the
+// relaxed one: none of them touches a captured stream here.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { swap(); }
+  ~RelaxedCapture() { swap(); }
+  void swap() {
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError();
+  }
+};
+
 // Frees idle blocks (of device dev, or of all with dev < 0) whose work has
 // completed.  With the lock held.
 void drop_idle_blocks(int dev) {
   for (Block& b : g_blocks) {
     if (!b.ptr || b.busy || (dev >= 0 && b.dev != dev)) continue;
-    if (hipEventQuery(b.done) != hipSuccess) {
+    RelaxedCapture relaxed;
+    if (hipEventQuery(b.done) != hipSuccess || hipFree(b.ptr) != hipSuccess) {
       (void)hipGetLastError();
       continue;
     }
-    (void)hipFree(b.ptr);
     (void)hipEventDestroy(b.done);
     b = Block{};
   }
@@ -1016,6 +1029,7 @@ void* take_block(size_t bytes, hipStream_t stream) {
     (void)hipGetLastError();
     return nullptr;
   }
+  RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(g_blocks_mutex);
   auto find = [&](Block** entry, size_t* held) {
     Block* best = nullptr;

@@ -96,6 +96,34 @@ def test_memory_is_bounded_and_given_back():
     assert free0 <= free1 <= free0 + (512 << 20) + (4 << 20), (free0, free1)
 
 
+def test_giving_back_under_capture():
+    """Destroying a plan without buffers while a stream captures gives
+    kept blocks back and leaves the capture whole."""
+    x, w, _ = _case(2)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    y = h2.conv2d_transpose(x, w, None, 2, 1)
+    big = torch.randn(96, 64, 40, 40, device=DEV)  # 37 MiB staged
+    h2.conv2d_transpose(big, torch.randn(64, 64, 4, 4, device=DEV), None, 2, 1)
+    del big
+    z = torch.zeros(8, device=DEV)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    kept, _ = torch.cuda.mem_get_info(DEV)
+    grouped = h2.huge2_wgrad_plan_create(
+        h2.make_desc(1, 8, 6, 6, 8, 3, 3, 1, 1, groups=8), False)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        z.add_(1)
+        h2.huge2_wgrad_plan_destroy(grouped)
+    assert torch.cuda.mem_get_info(DEV)[0] >= kept + (16 << 20)  # (less the graph's own)
+    for i in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert z.tolist() == [i + 1.0] * 8
+    assert torch.equal(h2.conv2d_transpose(x, w, None, 2, 1), y)
+
+
 def test_refused_under_capture():
     """A one-shot call cannot be recorded: it reports an error and the
     graph's own work is unharmed."""
