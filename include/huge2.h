@@ -177,15 +177,16 @@ int32_t huge2_plan_stages_input(const huge2_plan* plan);
 const char* huge2_plan_kernel(const huge2_plan* plan);
 
 /* Release a plan and its device buffers.  Waits for the device to finish
- * work that may still use them.  NULL is accepted.  Errors: HIP. */
+ * work that may still use them.  NULL is accepted and releases only what the
+ * one-shot entry points keep.  Errors: HIP. */
 huge2_status huge2_plan_destroy(huge2_plan* plan);
 
 /* One-shot transposed convolution (Algorithm 1 semantics, computed by the
  * phase decomposition): plan_create + plan_execute + stream-ordered release
  * of the plan's buffers.  The one-shot entry points keep up to 512 MiB of
  * released buffers per GPU for later calls (any stream or thread; a later
- * call's work is ordered behind the last use), which destroying any plan
- * frees; they cannot be recorded into a HIP graph (HUGE2_ERR_HIP on a
+ * call's work is ordered behind the last use), which destroying any plan, or
+ * huge2_plan_destroy(NULL), frees where their work has ended; they cannot be recorded into a HIP graph (HUGE2_ERR_HIP on a
  * capturing stream).  w is [c_in][c_out][r][s].  desc->out_pad_* obey
  * 0 <= out_pad < max(stride, dil).  Errors as plan_create/plan_execute. */
 huge2_status huge2_conv2d_transpose(const huge2_conv_desc* desc, const void* x, const void* w,
@@ -324,8 +325,8 @@ huge2_status huge2_wgrad_execute(const huge2_wgrad_plan* plan, const void* x, co
  * huge2_plan_kernel. */
 const char* huge2_wgrad_plan_kernel(const huge2_wgrad_plan* plan);
 
-/* Release a weight-gradient plan; waits for the device first.  NULL is
- * accepted.  Errors: HIP. */
+/* Release a weight-gradient plan; waits for the device first.  NULL as in
+ * huge2_plan_destroy.  Errors: HIP. */
 huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan);
 
 /* One-shot forms: plan_create + execute + destroy (synchronises the

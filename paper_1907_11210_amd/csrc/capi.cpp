@@ -973,7 +973,8 @@ int plan_gemm_shape(const huge2_conv_desc& d, bool tr, PlanShape* shape, bool* l
 // its own work behind that event.  At most 512 MiB a GPU are kept (a weight
 // gradient's workspace is under 320 unless one image's copies exceed its chunk
 // budget), in at most 16 blocks in all; larger or further buffers are
-// stream-ordered allocations.  Destroying any plan gives idle blocks back, and so does an allocation that fails or would exceed the
+// stream-ordered allocations.  Destroying any plan, or none (a null plan), gives
+// idle blocks back, and so does an allocation that fails or would exceed the
 // bound.
 constexpr size_t kBlockKeepBytes = (size_t)512 << 20;
 constexpr int kMaxBlocks = 16;
@@ -2729,8 +2730,7 @@ int32_t huge2_plan_stages_input(const huge2_plan* plan) {
 }
 
 huge2_status huge2_plan_destroy(huge2_plan* plan) {
-  if (!plan) return HUGE2_OK;
-  free_buffers(plan);
+  if (plan) free_buffers(plan);
   delete plan;
   give_back_blocks();
   return HUGE2_OK;
@@ -2870,8 +2870,7 @@ const char* huge2_wgrad_plan_kernel(const huge2_wgrad_plan* plan) {
 }
 
 huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan) {
-  if (!plan) return HUGE2_OK;
-  wgrad_free(plan);
+  if (plan) wgrad_free(plan);
   delete plan;
   give_back_blocks();
   return HUGE2_OK;
