@@ -144,8 +144,9 @@ long long count_works(const huge2_conv_desc& d, bool transposed, int class_split
 // and K stages (128 bytes of channels) of a tile, the mean over the phases of a
 // transposed conv.  Only fields that the plans of one group share enter, so
 // that branches of one input take the same form.
+// blocks: channel blocks; longest: the stages of the phase with the most taps.
 struct GemmSize {
-  long long tiles, tiles32, stages;
+  long long tiles, tiles32, stages, blocks, longest;
 };
 GemmSize gemm_size(const huge2_conv_desc& d, bool transposed) {
   int ho = 1, wo = 1;
@@ -156,8 +157,12 @@ GemmSize gemm_size(const huge2_conv_desc& d, bool transposed) {
   const long long rows = ((long long)d.n * out + 63) / 64;
   g.tiles = rows * ((d.c_out + 63) / 64);
   g.tiles32 = rows * ((d.c_out + 31) / 32);
-  g.stages = (long long)d.r * d.s * cb;
-  if (transposed) g.stages = std::max(1ll, (g.stages * d.h * d.w + out - 1) / out);
+  g.blocks = cb;
+  g.stages = g.longest = (long long)d.r * d.s * cb;
+  if (transposed) {
+    g.longest = cb * ((d.r + d.stride_h - 1) / d.stride_h) * ((d.s + d.stride_w - 1) / d.stride_w);
+    g.stages = std::max(1ll, (g.stages * d.h * d.w + out - 1) / out);
+  }
   return g;
 }
 
@@ -186,13 +191,27 @@ bool takes_wavek(const huge2_conv_desc& d, bool transposed, const GemmSize& g) {
     const bool in_place = d.layout == HUGE2_NHWC && d.c_in % 8 == 0;
     return in_place ? g.stages <= 192 : g.stages < 96 && (!transposed || g.tiles >= 16);
   }
-  // fp32 (three bf16 parts, against its shared tiles): 264 -> 40 3x3 on
-  // 9 x 41 x 50 87 / 58 (289, 81), 504 -> 456 on 21 x 21 57 / 38 (56, 144), 288
-  // -> 72 4x4 on 45 x 28 x 20 54 / 63 (788, 36), 48 -> 64 on 32 x 21 x 27 25 / 31
-  // (284, 18), 208 -> 40 4x4 on 2 x 7 x 33 27 / 33 (8, 112)
-  if (d.c_out <= 32) return g.tiles32 <= 512 || g.stages > 12;
-  if (d.c_out <= 64 && g.tiles > 256 && g.stages <= 24) return false;
-  return g.tiles <= 512 && (g.stages <= 96 || g.tiles >= 32);
+  // fp32 (three bf16 parts, against its shared tiles; time in units of theirs, means
+  // of 1400 layers).  Up to 512 tiles 0.5 to 0.9, but
+  //  - not few tiles with a long K, which the shared tiles split across workgroups by
+  //    channel blocks (1836 -> 14 channels 4x4 on 10 x 17 x 5, 2 tiles and 928 stages,
+  //    238 / 95 us; 912 -> 8 5x5 on 5 x 17 x 6, 32 and 181, 62 / 38).  Up to 32
+  //    channels 1.1 from 48 to 64 stages, 1.3 to 96, 1.6 beyond; more channels 1.3 from
+  //    96 to 144 and 1.7 beyond, from 64 tiles on 0.95 and 1.15; from 128 tiles on 0.7 to
+  //    0.9.  With up to 6 blocks 0.8 to 1.1, and convs that read NHWC in place are
+  //    split by an eighth of their blocks where they are listed (6 blocks 0.4);
+  //  - not many tiles with a short K in their longest phase: up to 64 channels below,
+  //    more 1.0 to 1.3 with up to 16 stages (93 -> 348 3x3 on 2 x 6 x 36 16.9 / 13.0).
+  // Up to 32 channels beyond 512 tiles too where K is long (1581 -> 5 4x4 on 13 x 35
+  // x 14, 926 and 87, 144 / 169; from 24 stages 0.8 to 1.1, below 1.0 to 1.4).
+  const bool listable = !transposed && d.stride_h == 1 && d.stride_w == 1 &&
+                        d.layout == HUGE2_NHWC && d.c_in % 4 == 0;
+  if (g.tiles < 128 && g.blocks > (listable ? 16 : 6) &&
+      g.stages > (d.c_out <= 32 ? 56 : g.tiles < 64 ? 96 : 144))
+    return false;
+  if (d.c_out <= 32) return g.tiles <= 512 || g.stages > 24;
+  if (g.tiles > 256 && (d.c_out <= 64 ? g.stages <= 24 : g.longest <= 16)) return false;
+  return g.tiles <= 512;
 }
 
 // Tile choice, from measurements on MI355X.  bf16: many pixels and at most
@@ -219,7 +238,9 @@ bool takes_wavek(const huge2_conv_desc& d, bool transposed, const GemmSize& g) {
 // 38.0 us for the 112 stages above, 19.1 against 21.3 for 64 stages of 512).
 // fp32 (512 -> 256 4x4 on 64 x 8 x 8, 148 us on the fp32 MFMA): 64 x 128 of two
 // 64 x 64 waves in two K groups 87.7, 128 x 128 in two groups 90.3, in one 89.9
-// us; at most 64 channels 128 x 64; fp32's wave-K tile fits a compute unit once,
+// us; at most 64 channels 128 x 64, and more where up to 16 stages leave its
+// smaller groups to hide the first loads (16 -> 200 channels 4x4 on 5 x 8 x 29 16.8 ->
+// 12.4, 36 -> 176 2x2 on 5 x 38 x 34 36.2 -> 24.6; beyond as fast or slower); fp32's wave-K tile fits a compute unit once,
 // so it is 32 wide only while every unit gets at most one.
 int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
   const bool bf16 = d.dtype == HUGE2_BF16;
@@ -236,7 +257,8 @@ int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
   }
   if (!bf16) {
     if (d.c_out <= 32) return TILE_F32_128x32;
-    if (d.c_out <= 64) return TILE_F32_128x64;
+    if (d.c_out <= 64 || (g.tiles > 256 && g.tiles < 8 * kComputeUnits && g.longest <= 16))
+      return TILE_F32_128x64;
     return g.tiles >= 8 * kComputeUnits ? TILE_F32_128x128 : TILE_F32_64x128_K2;
   }
   if (d.c_out <= 32) return TILE_128x32;

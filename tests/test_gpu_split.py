@@ -41,10 +41,17 @@ FORMS = [
     (L("wk_no_taps", True, 1, 16, 4, 5, 24, 2, 3, 0, 2, 1, "NHWC", "f32"), "wavek_kernel"),
     (L("f32_128x64", False, 3, 20, 81, 75, 50, 3, 1, 2, 0, 2, "NCHW", "f32"), "f32_kernel 128x64"),
     (L("f32_128x32", True, 3, 10, 61, 59, 9, 3, 2, 1, 1, 1, "NHWC", "f32"), "f32_kernel 128x32"),
-    (L("f32_64x128", True, 5, 33, 29, 31, 130, 4, 2, 1, 0, 1, "NCHW", "f32"), "f32_kernel 64x128"),
+    (L("f32_64x128", True, 5, 165, 29, 31, 130, 4, 2, 1, 0, 1, "NCHW", "f32"), "f32_kernel 64x128"),
     (L("f32_128x128", True, 8, 20, 41, 43, 150, 3, 2, 1, 1, 1, "NHWC", "f32"), "f32_kernel 128x128"),
     # a K split across workgroups, more taps than the wave-K form holds
     (L("f32_splitk", False, 1, 600, 9, 9, 70, 3, 1, 1, 0, 1, "NCHW", "f32"), "f32_kernel 64x128"),
+    # few tiles: K too long for the wave-K form, with and without enough channel
+    # blocks to split it by, on both sides of 128 tiles; many tiles of a short K
+    (L("f32_long_k", True, 5, 912, 17, 6, 8, 5, 2, 2, 1, 1, "NHWC", "f32"), "f32_kernel 128x32"),
+    (L("f32_long_k64", False, 2, 330, 9, 7, 40, 4, 1, 1, 0, 1, "NCHW", "f32"), "f32_kernel 128x64"),
+    (L("wk_f32_few_blocks", False, 2, 84, 18, 7, 14, 5, 2, 0, 0, 1, "NHWC", "f32"), "wavek_kernel 64x32"),
+    (L("wk_f32_128_tiles", False, 2, 230, 65, 64, 9, 3, 1, 1, 0, 1, "NHWC", "f32"), "wavek_kernel 64x32"),
+    (L("f32_short_k", True, 5, 16, 8, 29, 200, 4, 2, 1, 0, 1, "NCHW", "f32"), "f32_kernel 128x64"),
     (L("f32_9x9", False, 1, 20, 21, 22, 40, 9, 1, 4, 0, 1, "NHWC", "f32"), "f32_kernel 128x64"),
 ]
 
@@ -122,7 +129,7 @@ def test_projection_plan_in_time(monkeypatch):
     monkeypatch.setenv("HUGE2_TILE", "5")
     few = us()
     P.say("us", many, few)
-    assert many <= 1.4 * few
+    assert many <= 1.8 * few  # (2.0 to 2.3 where each of them was placed by a scan)
 
 
 F32 = [l for l, _ in FORMS if l.name in ("wk_f32", "f32_128x64", "f32_64x128", "f32_splitk")]
