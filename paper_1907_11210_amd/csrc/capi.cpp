@@ -247,7 +247,8 @@ int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
   int forced = env_int("HUGE2_TILE", -1);
   if (forced >= 0 && forced < TILE_COUNT &&
       (kTiles[forced].kind == 4 ? (long long)d.r * d.s <= kMaxLdsTaps
-                                : (kTiles[forced].kind == 5) == !bf16))
+                                : (kTiles[forced].kind == 5) == !bf16 || forced == TILE_128x32 ||
+                                      forced == TILE_128x128))
     return forced;
   const GemmSize g = gemm_size(d, transposed);
   if (takes_wavek(d, transposed, g)) {
@@ -256,7 +257,16 @@ int choose_cfg(const huge2_conv_desc& d, bool transposed, int class_split) {
     return TILE_WK_64x64;
   }
   if (!bf16) {
-    if (d.c_out <= 32) return TILE_F32_128x32;
+    // Many tiles of a short K are bound by their first loads and their stores:
+    // the fp32 MFMA tiles, whose LDS lets six (128 x 32) workgroups to a unit for
+    // two, are faster there (time in units of the three-part tile's, means of 1700
+    // layers): up to 32 channels from 1024 to 4096 tiles 0.65 to 0.85 below 12 stages,
+    // 0.8 to 0.97 to 24, 1.1 beyond (49 -> 24 channels 2x2 stride 3 on 23 x 51 x 14 18.0 /
+    // 31.5 us), at 512 tiles 1.1, from 4096 1.05; more channels 0.72 to 0.91 with a
+    // single stage (32 -> 384 1x1 stride 2 on 3 x 63 x 48 28.6 / 35.0), 1.1 with two.
+    if (d.c_out > 64 && g.tiles >= 1024 && g.longest == 1) return TILE_128x128;
+    if (d.c_out <= 32)
+      return g.tiles >= 1024 && g.tiles < 4096 && g.stages <= 24 ? TILE_128x32 : TILE_F32_128x32;
     if (d.c_out <= 64 || (g.tiles > 256 && g.tiles < 8 * kComputeUnits && g.longest <= 16))
       return TILE_F32_128x64;
     return g.tiles >= 8 * kComputeUnits ? TILE_F32_128x128 : TILE_F32_64x128_K2;

@@ -96,10 +96,10 @@ __device__ __forceinline__ void store_rows_nhwc(const GemmArgs& a, int n0, void*
 // NCHW output puts pixels on MFMA columns (lanes hold consecutive pixels, so
 // a channel's stores coalesce); NHWC output puts pixels on MFMA rows (lanes
 // hold consecutive channels of a pixel).
-template <int BM, int BN, int PWAVES, int CWAVES, int KB, int DEPTH, bool NCHW_OUT>
+template <bool BF16, int BM, int BN, int PWAVES, int CWAVES, int KB, int DEPTH, bool NCHW_OUT>
 __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmArgs a) {
   constexpr int NT = PWAVES * CWAVES * 64;  // threads per workgroup
-  constexpr int ESZ = 2;
+  constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int KC = KB / ESZ;    // K elements per stage
   constexpr int VE = 16 / ESZ;    // elements per 16-byte chunk
   constexpr int CPR = KB / 16;    // 16-byte chunks per row
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
   constexpr int TP = WP / 32, TC = WC / 32;
   constexpr int A_LD = BM * CPR / NT;
   constexpr int B_LD = (BN * CPR + NT - 1) / NT;  // the last may be partial
-  constexpr int KSUB = KB / 32;  // MFMAs per operand pair and stage
+  constexpr int KSUB = BF16 ? KB / 32 : KB / 8;  // MFMAs per operand pair and stage
   static_assert(BM * CPR % NT == 0, "whole A loads per thread");
   static_assert(TP >= 1 && TC >= 1 && WP % 32 == 0 && WC % 32 == 0, "32x32 MFMA blocks");
   constexpr int STAGE_B = (BM + BN) * ROWB;
@@ -275,24 +275,43 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
   auto compute = [&](int buf) {
     const char* as = smem + buf * STAGE_B + (wp_i * WP + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
     const char* bs = smem + buf * STAGE_B + (BM + wc_i * WC + (lane & 31)) * ROWB + (lane >> 5) * (KB / 2);
+    constexpr int NCHUNK = BF16 ? KSUB : KSUB / 4;  // 16-byte pieces of a lane's row
 #pragma unroll
-    for (int t = 0; t < KSUB; ++t) {
+    for (int t = 0; t < NCHUNK; ++t) {
       uint4 fp[TP], fc[TC];
 #pragma unroll
       for (int i = 0; i < TP; ++i) fp[i] = *(const uint4*)(as + 32 * i * ROWB + 16 * t);
 #pragma unroll
       for (int j = 0; j < TC; ++j) fc[j] = *(const uint4*)(bs + 32 * j * ROWB + 16 * t);
+      if constexpr (BF16) {
 #pragma unroll
-      for (int i = 0; i < TP; ++i)
+        for (int i = 0; i < TP; ++i)
 #pragma unroll
-        for (int j = 0; j < TC; ++j) {
-          const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
-          const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
-          if constexpr (NCHW_OUT)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
-          else
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
-        }
+          for (int j = 0; j < TC; ++j) {
+            const bf16x8 vp = __builtin_bit_cast(bf16x8, fp[i]);
+            const bf16x8 vc = __builtin_bit_cast(bf16x8, fc[j]);
+            if constexpr (NCHW_OUT)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vc, vp, acc[i][j], 0, 0, 0);
+            else
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp, vc, acc[i][j], 0, 0, 0);
+          }
+      } else {
+        float xv[TP][4], wv[TC][4];
+#pragma unroll
+        for (int i = 0; i < TP; ++i) unpack4(fp[i], xv[i]);
+#pragma unroll
+        for (int j = 0; j < TC; ++j) unpack4(fc[j], wv[j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < TP; ++i)
+#pragma unroll
+            for (int j = 0; j < TC; ++j)
+              if constexpr (NCHW_OUT)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[j][e], xv[i][e], acc[i][j], 0, 0, 0);
+              else
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[i][e], wv[j][e], acc[i][j], 0, 0, 0);
+      }
     }
   };
 
@@ -339,7 +358,7 @@ __global__ __launch_bounds__(PWAVES * CWAVES * 64) void phase_gemm_kernel(GemmAr
     store_tile<false, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.part + (size_t)wk.ks * a.part_stride, acc,
                                         wk.m0 + wp_i * WP, wk.n0 + wc_i * WC, lane, s_bias - wk.n0);
   } else {
-    store_tile<true, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0 + wp_i * WP,
+    store_tile<BF16, NCHW_OUT, TP, TC>(a, sg, wk.m1, a.y[sg.plan], acc, wk.m0 + wp_i * WP,
                                        wk.n0 + wc_i * WC, lane, s_bias - wk.n0);
   }
 }
@@ -957,11 +976,11 @@ __global__ __launch_bounds__(W * 64 * KS, 2) void phase_gemm3_kernel(GemmArgs a)
   }
 }
 
-template <bool NCHW_OUT, int CFG>
+template <bool BF16, bool NCHW_OUT, int CFG>
 static void launch_one(const GemmArgs& a, hipStream_t stream) {
   constexpr TileShape t = kTiles[CFG];
   if constexpr (t.kind == 0)
-    hipLaunchKernelGGL((phase_gemm_kernel<t.bm, t.bn, t.pw, t.cw, t.kb, t.depth, NCHW_OUT>),
+    hipLaunchKernelGGL((phase_gemm_kernel<BF16, t.bm, t.bn, t.pw, t.cw, t.kb, t.depth, NCHW_OUT>),
                        dim3(a.n_works), dim3(t.pw * t.cw * 64), 0, stream, a);
   else if constexpr (t.kind == 3)
     hipLaunchKernelGGL((phase_gemm3_kernel<t.bm, t.bn, t.pw * t.cw, t.kb, t.depth % 10,
@@ -978,7 +997,7 @@ static hipError_t launch_cfg(const GemmArgs& a, int cfg, hipStream_t stream) {
   if constexpr (CFG < TILE_COUNT) {
     if constexpr (kTiles[CFG].kind < 4) {
       if (cfg == CFG) {
-        launch_one<NCHW_OUT, CFG>(a, stream);
+        launch_one<true, NCHW_OUT, CFG>(a, stream);
         return hipGetLastError();
       }
     }
@@ -988,11 +1007,23 @@ static hipError_t launch_cfg(const GemmArgs& a, int cfg, hipStream_t stream) {
   }
 }
 
-// (the wave-K tiles take both dtypes, the three-part ones fp32, the rest bf16)
+template <int CFG>
+static hipError_t launch_f32_mfma(const GemmArgs& a, bool nchw_out, hipStream_t stream) {
+  if (nchw_out)
+    launch_one<false, true, CFG>(a, stream);
+  else
+    launch_one<false, false, CFG>(a, stream);
+  return hipGetLastError();
+}
+
+// (the wave-K tiles, TILE_128x128 and TILE_128x32 take both dtypes, the
+// three-part ones fp32, the rest bf16)
 hipError_t launch_phase_gemm(const GemmArgs& a, int dtype, int cfg, bool nchw_out,
                              hipStream_t stream) {
   if (a.n_works <= 0) return hipSuccess;
   if (kTiles[cfg].kind == 4) return launch_wavek(a, dtype, kTiles[cfg].bn, nchw_out, stream);
+  if (dtype != 1 && cfg == TILE_128x32) return launch_f32_mfma<TILE_128x32>(a, nchw_out, stream);
+  if (dtype != 1 && cfg == TILE_128x128) return launch_f32_mfma<TILE_128x128>(a, nchw_out, stream);
   if (dtype != 1) return launch_gemm_f32(a, cfg, nchw_out, stream);
   return nchw_out ? launch_cfg<true>(a, cfg, stream) : launch_cfg<false>(a, cfg, stream);
 }

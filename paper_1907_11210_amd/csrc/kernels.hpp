@@ -110,7 +110,8 @@ struct GemmArgs {
 // wg_per_cu: workgroups of this shape that fit on one compute unit at once
 // (the tighter of the register and LDS limits), used by the host's schedule
 // model through tile_per_cu.
-// kind 0: both operands through LDS, PW x CW waves of (BM/PW) x (BN/CW).
+// kind 0: both operands through LDS, PW x CW waves of (BM/PW) x (BN/CW); 128 x 128
+//         and 128 x 32 also for fp32, on the fp32 MFMA.
 // kind 1: split-wave form, the pixel tile through LDS, CW waves each loading
 //         BN/CW weight rows itself (PW = 1) from lane-ordered packed weights.
 // kind 4: wave-K form (wavek_kernel), every wave the whole tile.

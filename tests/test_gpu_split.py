@@ -52,6 +52,10 @@ FORMS = [
     (L("wk_f32_few_blocks", False, 2, 84, 18, 7, 14, 5, 2, 0, 0, 1, "NHWC", "f32"), "wavek_kernel 64x32"),
     (L("wk_f32_128_tiles", False, 2, 230, 65, 64, 9, 3, 1, 1, 0, 1, "NHWC", "f32"), "wavek_kernel 64x32"),
     (L("f32_short_k", True, 5, 16, 8, 29, 200, 4, 2, 1, 0, 1, "NCHW", "f32"), "f32_kernel 128x64"),
+    # many tiles of a short K: the fp32 MFMA tiles
+    (L("f32_mfma_narrow", True, 9, 20, 60, 41, 12, 3, 2, 1, 1, 1, "NHWC", "f32"), "phase_gemm_kernel 128x32"),
+    (L("f32_mfma_narrow_nchw", False, 17, 70, 71, 69, 30, 1, 1, 0, 0, 1, "NCHW", "f32"), "phase_gemm_kernel 128x32"),
+    (L("f32_mfma_one_stage", True, 4, 20, 44, 45, 140, 2, 2, 0, 0, 1, "NCHW", "f32"), "phase_gemm_kernel 128x128"),
     (L("f32_9x9", False, 1, 20, 21, 22, 40, 9, 1, 4, 0, 1, "NHWC", "f32"), "f32_kernel 128x64"),
 ]
 
