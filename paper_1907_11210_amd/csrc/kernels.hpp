@@ -521,19 +521,24 @@ hipError_t launch_wgrad_grouped(const WgArgs& a, int dtype, hipStream_t stream);
 // are no multiple of 8, the plain staging reads element by element: 424
 // channels of 8 x 59 x 28, 3x3 (50M copied elements), 91 us against 27.7; but it
 // shares a launch with the small tensor's, so it keeps less than 6M elements
-// (2.8M: 12.8 us against 11.2 and the other launch's 4).
+// (2.8M: 12.8 us against 11.2 and the other launch's 4), and what gives fewer than
+// a workgroup to a compute unit (136 channels of 2 images, 62 x 28, 4x4: the pass 41.0
+// us against 37.6; from 336 workgroups on the gather is the faster).
 constexpr int kWgGatherLds = 32 * 1024;
 inline int wgrad_gather_images(int hs, int ws, int hb, int wb, int esz, int nimg, int nb, int taps,
                                bool any_size) {
   const long long plane = (long long)hb * wb * esz;
-  if (!any_size && (hs * ws) % 8 != 0 && (long long)hs * ws * nimg * nb * taps < (6 << 20)) return 0;
+  const bool by_eight = any_size || (hs * ws) % 8 == 0;
+  if (!by_eight && (long long)hs * ws * nimg * nb * taps < (6 << 20)) return 0;
   const bool pairs = esz == 2 && ((long long)hs * ws) % 2 != 0 && nimg > 1;
   if (plane > kWgGatherLds) return 0;
   long long ib = (long long)nimg * nb / 1024;
   if (ib > kWgGatherLds / plane) ib = kWgGatherLds / plane;
   if (ib > nimg) ib = nimg;
   if (ib < 1) ib = 1;
-  return (int)(pairs ? (ib + 1) / 2 * 2 : ib);
+  if (pairs) ib = (ib + 1) / 2 * 2;
+  if (!by_eight && (nimg + ib - 1) / ib * nb < kComputeUnits) return 0;
+  return (int)ib;
 }
 
 // Re-layout the input into [n][h*w][c_stride] with zero channel padding.

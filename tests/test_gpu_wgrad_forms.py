@@ -86,6 +86,15 @@ def test_gather_of_a_last_single_image(case, monkeypatch):
     assert np.array_equal(got, W._gpu(case, xq, dyq))
 
 
+@pytest.mark.parametrize("n,gather", [(2, "gather0"), (12, "gather2")])
+def test_gather_by_workgroups(n, gather):
+    """Off multiples of 8 pixels the gather is taken where it has a workgroup
+    for every compute unit."""
+    case = ("workgroups", False, n, 136, 62, 28, 20, 4, 4, 1, 1, 0, 1, "bf16")
+    P.say("case", case)
+    assert gather in _kernel(case)
+
+
 # enough work for wide tiles (from 4096 tiles of 64 x 64 times 128-byte stages)
 TILES = [
     ("64x128", False, 8, 61, 60, 61, 60, 3, 3, 1, 1, 0, 1, "bf16"),
