@@ -1518,6 +1518,7 @@ huge2_status create_grouped(huge2_plan** out, const huge2_conv_desc& d, int tran
     q.stride_h = d.stride_h, q.stride_w = d.stride_w, q.pad_h = d.pad_h, q.pad_w = d.pad_w;
     q.dil_h = d.dil_h, q.dil_w = d.dil_w, q.ho = p->ho, q.wo = p->wo;
     q.transposed = transposed, q.nhwc = g.nhwc, q.act = d.activation;
+    q.chains = env_int("HUGE2_DEPTHWISE_CHAINS", -1);
     p->depthwise = depthwise_shape(&q, d.dtype, false) && depthwise_shape(&q, d.dtype, true);
     if (p->depthwise)
       std::snprintf(p->kernel_name, sizeof(p->kernel_name), "grouped_kernel depthwise%s v%d",

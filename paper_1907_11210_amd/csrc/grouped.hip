@@ -289,6 +289,14 @@ __global__ __launch_bounds__(256) void depthwise_kernel(DwArgs a) {
 
 constexpr int kDwRowsVec = 4;   // outputs per thread of the 3x3 kernel, 16-byte channel pieces
 constexpr int kDwRowsOne = 8;   // and one channel per thread
+// Chains need outputs for this many whole ones (pieces; one channel), times the
+// ratio: below, the kernel of one position per thread has more threads to hide
+// its loads (3x3 on 3 x 52 x 37 x 64, stride 2, bf16 NHWC, 2.7 thousand chains: 7.5 us
+// in chains, 6.0 without).  Chains' time in units of the other's, means of 400
+// layers: one channel, stride 1, 1.0 to 1.1 up to 32 thousand, 0.85 to 64, 0.7 to 128,
+// 0.4 beyond; stride 2 1.2 to 1.5, 1.14, 0.6, 0.7; pieces, stride 1, 1.0 to 1.1 up to 64
+// thousand, then 0.8 and 0.7; stride 2 1.1 to 1.3 up to 128.
+constexpr long long kDwChainsVec = 64 << 10, kDwChainsOne = 32 << 10;
 
 bool depthwise_shape(DwArgs* a, int dtype, bool pieces) {
   const int full = dtype == 1 ? 8 : 4;
@@ -317,6 +325,10 @@ bool depthwise_shape(DwArgs* a, int dtype, bool pieces) {
   }
   const int tr = a->vec > 1 ? kDwRowsVec : kDwRowsOne;
   a->rows3 = !a->transposed && a->r == 3 && a->s == 3 && a->ratio <= 2;
+  if (a->chains == 0 ||
+      (a->chains < 0 && (long long)a->n * (a->cout / a->vec) * a->ho * a->wo / tr <
+                            (a->vec > 1 ? kDwChainsVec : kDwChainsOne) * a->ratio))
+    a->rows3 = 0;
   const long long chains =
       a->rows3 ? (long long)a->step * ((a->ho + (long long)tr * a->step - 1) / ((long long)tr * a->step))
                : a->ho;

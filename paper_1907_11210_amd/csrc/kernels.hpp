@@ -392,6 +392,7 @@ struct DwArgs {
   int n, cin, cout, mult, h, w_, r, s, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, ho, wo;
   int transposed, nhwc, act;
   int vec;           // channels per thread: 16 bytes' worth, or 1
+  int chains;        // 1, 0: row chains or not, whatever the size; -1: by size
   int rows3;         // 1: the 3x3 conv kernel with tr outputs per thread, rows oh0 + j * step
   int step, ratio;   // step = dil_h / g, ratio = stride_h / g, g = gcd(stride_h, dil_h)
   uint32_t total;    // threads

@@ -45,10 +45,12 @@ def _inputs(layer, seed):
     return (wl.layer_input(layer, seed).to(dt), wl.random_weight(layer, seed + 1, 0.5).to(dt))
 
 
+@pytest.mark.parametrize("chains", ["0", "1"])
 @pytest.mark.parametrize("layer", LAYERS, ids=lambda l: l.name)
-def test_depthwise_forms(layer):
+def test_depthwise_forms(layer, chains, monkeypatch):
     """Every dispatch of the depthwise kernels (3x3 row chains or any taps;
     16-byte channel pieces or one channel per thread) with bias and ReLU."""
+    monkeypatch.setenv("HUGE2_DEPTHWISE_CHAINS", chains)
     layer = layer.with_(act="relu")
     P.say("case", layer)
     xq, wq = _inputs(layer, 7)
@@ -58,17 +60,46 @@ def test_depthwise_forms(layer):
     P.check(P.run_gpu(layer, xq, wq, bias, prefill_nan=True), ref, absref, layer.dtype, layer.name)
     plan = P.make_plan(layer, wq.contiguous().to(torch.device("cuda", 0)))
     try:
-        assert "depthwise" in plan.kernel, plan.kernel
+        rows3 = chains == "1" and layer.name.startswith("dw3")
+        assert ("depthwise3" if rows3 else "depthwise ") in plan.kernel, plan.kernel
     finally:
         plan.close()
 
 
+@pytest.mark.parametrize("layer,chains", [
+    (L("dw_small", False, 3, 64, 52, 37, 64, 3, 2, 0, 0, 1, "NHWC", "bf16"), False),
+    (L("dw_under", False, 4, 128, 64, 63, 128, 3, 1, 1, 0, 1, "NHWC", "bf16"), False),
+    (L("dw_over", False, 8, 128, 64, 64, 128, 3, 1, 1, 0, 4, "NHWC", "f32"), True),
+    (L("dw_under_one", False, 1, 63, 64, 64, 63, 3, 1, 1, 0, 1, "NCHW", "f32"), False),
+    (L("dw_under_s2", False, 2, 128, 63, 63, 128, 3, 2, 1, 0, 1, "NCHW", "bf16"), False),
+    (L("dw_over_one", False, 2, 128, 50, 50, 128, 3, 1, 1, 0, 1, "NCHW", "bf16"), True),
+], ids=lambda v: getattr(v, "name", None))
+def test_chains_by_size(layer, chains, monkeypatch):
+    """Row chains where there are enough of them for the chip; the same bits
+    either way."""
+    P.say("case", layer)
+    xq, wq = _inputs(layer, 11)
+    def run():
+        plan = P.make_plan(layer, wq.contiguous().to(torch.device("cuda", 0)))
+        try:
+            return plan.kernel, P.run_gpu(layer, xq, wq, plan=plan)
+        finally:
+            plan.close()
+    kernel, y = run()
+    assert ("depthwise3" in kernel) == chains, kernel
+    monkeypatch.setenv("HUGE2_DEPTHWISE_CHAINS", "0" if chains else "1")
+    kernel, other = run()
+    assert ("depthwise3" in kernel) != chains, kernel
+    assert np.array_equal(y, other)
+
+
 @pytest.mark.parametrize("layer", [l for l in LAYERS if l.layout == "NHWC"][:5],
                          ids=lambda l: l.name)
-def test_depthwise_unaligned(layer):
+def test_depthwise_unaligned(layer, monkeypatch):
     """Tensors that do not start on 16 bytes take one channel per thread and
     give the same bits: the taps are added in the same order."""
     P.say("case", layer)
+    monkeypatch.setenv("HUGE2_DEPTHWISE_CHAINS", "1")
     dev = torch.device("cuda", 0)
     xq, wq = _inputs(layer, 9)
     x, w = wl.to_layout(xq, layer.layout).to(dev), wq.contiguous().to(dev)
@@ -86,10 +117,12 @@ def test_depthwise_unaligned(layer):
         plan.close()
 
 
+@pytest.mark.parametrize("chains", ["0", "1"])
 @pytest.mark.parametrize("layout", ["NCHW", "NHWC"])
-def test_depthwise_skips_padding(layout):
+def test_depthwise_skips_padding(layout, chains, monkeypatch):
     """Products outside the input are skipped: an infinite weight whose tap
     lies in the padding leaves the outputs there finite."""
+    monkeypatch.setenv("HUGE2_DEPTHWISE_CHAINS", chains)
     dev = torch.device("cuda", 0)
     layer = L("dw_inf", False, 1, 8, 6, 6, 8, 3, 1, 1, 0, 1, layout, "bf16")
     w = torch.full((8, 1, 3, 3), 0.25, dtype=torch.bfloat16)
