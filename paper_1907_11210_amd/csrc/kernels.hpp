@@ -192,18 +192,7 @@ inline int tile_per_cu(int cfg, int dtype) {
 }
 inline int tile_bm(int cfg) { return kTiles[cfg].bm; }
 inline int tile_bn(int cfg) { return kTiles[cfg].bn; }
-inline int tile_threads(int cfg) {
-  return kTiles[cfg].pw * kTiles[cfg].cw * (kTiles[cfg].kind ? kTiles[cfg].ksplit : 1) * 64;
-}
 inline int tile_kb(int cfg) { return kTiles[cfg].kb; }
-// LDS bytes of a configuration (two stages of the rows that go through LDS,
-// 16-byte row pad)
-inline int tile_lds(int cfg) {
-  const TileShape& t = kTiles[cfg];
-  const int rows = t.kind == 0 ? t.bm + t.bn : t.bm;
-  return (t.kind == 3 ? 3 : 2) * rows * (t.kb + 16);
-}
-constexpr int kMaxBlockK_bytes = 256;  // largest K block per stage: 128 bf16 or 64 fp32
 
 // dtype: 0 fp32, 1 bf16; nchw_out selects the output layout.
 hipError_t launch_phase_gemm(const GemmArgs& a, int dtype, int cfg, bool nchw_out,
