@@ -34,9 +34,13 @@
  *   - Layout (HUGE2_NCHW or HUGE2_NHWC) applies to x and y.  Weights are
  *     always in the framework order given per entry point, whatever the
  *     activation layout.
- *   - dtype HUGE2_F32: x, w, y are float; MFMA in fp32.  HUGE2_BF16: x, w, y
- *     are bfloat16; products accumulate in fp32; y is rounded to nearest
- *     even.  bias is always float (nullable).
+ *   - dtype HUGE2_F32: x, w, y are float; products keep 24 bits (on the fp32
+ *     MFMA, or on the bf16 one in three exact parts an operand, less than
+ *     2^-25 of a product left out) and accumulate in fp32.  Infinities, NaN and
+ *     values from 2^104 give what fp32 arithmetic gives, in about 4 to 6 times the
+ *     time where such sums are formed again (hundreds of times only for infinite
+ *     or NaN weights).  HUGE2_BF16: x, w, y are bfloat16; products accumulate in
+ *     fp32; y is rounded to nearest even.  bias is always float (nullable).
  *   - hip_stream is a hipStream_t (NULL = the default stream).  Work is
  *     enqueued asynchronously; the call returns after enqueue.
  *   - Every argument is validated before any HIP call.  On an error nothing
@@ -329,8 +333,9 @@ const char* huge2_wgrad_plan_kernel(const huge2_wgrad_plan* plan);
  * huge2_plan_destroy.  Errors: HIP. */
 huge2_status huge2_wgrad_plan_destroy(huge2_wgrad_plan* plan);
 
-/* One-shot forms: plan_create + execute + destroy (synchronises the
- * stream before releasing the workspace). */
+/* One-shot forms: plan_create + execute + a release of the workspace behind
+ * the work (kept as huge2_conv2d_transpose describes), then a wait for the
+ * stream. */
 huge2_status huge2_conv2d_transpose_wgrad(const huge2_conv_desc* desc, const void* x,
                                           const void* dy, void* dw, void* hip_stream);
 huge2_status huge2_conv2d_dilated_wgrad(const huge2_conv_desc* desc, const void* x,

@@ -953,10 +953,10 @@ long long count_works(const huge2_conv_desc& d, bool transposed, int class_split
 // works: 21.3 against 25.1 us).  Both forms are built once, here.  That line lies
 // at the slots there are (tile_per_cu: one wave-K workgroup of fp32 to a unit;
 // 64 -> 30 channels 5x5 on 10 x 39 x 42, 256 works whole 15.9 us, split into more
-// 23.4).  The schedule model keeps two to a unit for them: beyond one round its choices then measured faster (200
-// -> 5 channels, dilation 4, on 12 x 45 x 33, 288 works 25.2 against 34.5 us), and
-// the order of works by it too (256 -> 19 5x5 on 9 x 24 x 24, 324 works, 26.2
-// against 38.7).
+// 23.4).  The schedule model keeps two to a unit for them: beyond one round its
+// choices then measured faster (200 -> 5 channels, dilation 4, on 12 x 45 x 33, 288
+// works 25.2 against 34.5 us), and the order of works by it too (256 -> 19 5x5 on 9 x
+// 24 x 24, 324 works, 26.2 against 38.7).
 bool choose_shape(const huge2_conv_desc& d, bool transposed, int cfg, PlanShape* shape) {
   const int bm = tile_bm(cfg);
   const int forced = env_int("HUGE2_CLASS_SPLIT", -1);

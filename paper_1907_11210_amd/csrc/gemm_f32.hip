@@ -7,17 +7,17 @@ namespace huge2 {
 // ---------------------------------------------------------------------------
 // Phase GEMM, fp32.  The fp32 MFMA runs at a sixteenth of the bf16 rate, so
 // every operand is split exactly into three bf16 parts (split8, which scales
-// it first; the weights once, when packed) and six of the nine products are summed in fp32, the
-// smallest first; the three left out stay below 2^-25 of the product, under
-// the rounding of the sums.  A workgroup of KS groups of PW x CW waves computes a tile of
-// 32 PW TP pixels x 32 CW TC output channels; a stage is 32 input channels of
-// one tap.  The pixel rows (128 bytes of fp32) are loaded two stages ahead,
+// it first; the weights once, when packed) and six of the nine products are
+// summed in fp32, the smallest first; the three left out stay below 2^-25 of the
+// product, under the rounding of the sums.  A workgroup of KS groups of PW x CW
+// waves computes a tile of 32 PW TP pixels x 32 CW TC output channels; a stage
+// is 32 input channels of one tap.  The pixel rows (128 bytes of fp32) are loaded two stages ahead,
 // split between the MFMAs of the stage before and kept in LDS as three planes
 // of bf16 rows, double buffered; each wave reads its weight fragments straight
 // from the lane-ordered planes.  Six MFMAs per fragment pair make the LDS and
-// L2 traffic per MFMA a third of the bf16 form's.  K groups (KS = 2: two waves per SIMD where a compute unit
-// gets one workgroup) take halves of the workgroup's stages; group 1's sums
-// are added to group 0's through LDS.
+// L2 traffic per MFMA a third of the bf16 form's.  K groups (KS = 2: two waves
+// per SIMD where a compute unit gets one workgroup) take halves of the
+// workgroup's stages; group 1's sums are added to group 0's through LDS.
 //
 // An operand that is or becomes infinite has no finite parts: a sum that comes
 // out infinite or NaN is formed again (mfma_f32_step).
