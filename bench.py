@@ -259,8 +259,10 @@ def _counter_per_dispatch(path, counter):
     return out
 
 
-MAIN_KERNELS = ("phase_gemm_kernel", "phase_gemm2_kernel", "phase_gemm3_kernel", "ztile_kernel",
-                "rowphase_kernel", "colphase_kernel", "quad_kernel", "grouped_kernel")
+MAIN_KERNELS = ("phase_gemm_kernel", "phase_gemm2_kernel", "phase_gemm3_kernel",
+                "phase_gemm_f32_kernel", "wavek_kernel", "ztile_kernel", "rowphase_kernel",
+                "colphase_kernel", "quad_kernel", "grouped_kernel", "depthwise_kernel",
+                "depthwise3_kernel")
 
 
 def _is_main(name):

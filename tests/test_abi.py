@@ -40,6 +40,23 @@ def test_every_declared_symbol_is_exported(L):
     assert declared <= exported
 
 
+def test_profile_summaries_know_every_main_kernel():
+    """Every kernel that a GEMM work list or a direct form is launched on is one
+    that the profile summaries give to its layer."""
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_1907_11210_amd", "csrc")
+    names = set()
+    for fn in os.listdir(csrc):
+        if fn.endswith(".hip"):
+            text = open(os.path.join(csrc, fn)).read()
+            names |= set(re.findall(r"void (\w+_kernel)\((?:GemmArgs|ZArgs|RpArgs|CpArgs|QArgs|GrArgs|DwArgs) a",
+                                    text))
+    assert {"wavek_kernel", "quad_kernel", "ztile_kernel"} <= names
+    assert names <= set(bench.MAIN_KERNELS), names - set(bench.MAIN_KERNELS)
+
+
 def test_status_strings(L):
     for code, name in enumerate(["HUGE2_OK", "HUGE2_ERR_INVALID_ARG", "HUGE2_ERR_UNSUPPORTED",
                                  "HUGE2_ERR_ALLOC", "HUGE2_ERR_HIP"]):
