@@ -2779,26 +2779,32 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgArgs a) {
           }
     }
   }
-  // one K slice and one chunk: the gradient itself, else this slice of G
-  float* const gt = a.g + (size_t)split * a.ms * a.nb;
+  // f(element of dw, sum) for this lane's sums, the kind of store chosen once: a
+  // choice for each (448 x 25 columns x 358 rows, K 224) took 13.3 us for 11.8.
+  auto each = [&](auto f) {
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mw + 32 * i + 8 * (r >> 2) + (r & 3);
-      if (m >= a.ms) continue;
+      for (int r = 0; r < 16; ++r) {
+        const int m = mw + 32 * i + 8 * (r >> 2) + (r & 3);
+        if (m >= a.ms) continue;
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) {
-        if (n + 32 * j >= a.nb) continue;
-        const size_t d = (size_t)m * a.nb + n + 32 * j;
-        if (!a.direct_out)
-          gt[d] = acc_in ? gt[d] + acc[i][j][r] : acc[i][j][r];
-        else if constexpr (BF16)
-          ((uint16_t*)a.dw)[d] = f32_to_bf16_rne(acc[i][j][r]);
-        else
-          ((float*)a.dw)[d] = acc[i][j][r];
+        for (int j = 0; j < TJ; ++j)
+          if (n + 32 * j < a.nb) f((size_t)m * a.nb + n + 32 * j, acc[i][j][r]);
       }
-    }
+  };
+  float* const gt = a.g + (size_t)split * a.ms * a.nb;
+  if (a.direct_out)  // one K slice and one chunk: the gradient itself
+    each([&](size_t d, float v) {
+      if constexpr (BF16)
+        ((uint16_t*)a.dw)[d] = f32_to_bf16_rne(v);
+      else
+        ((float*)a.dw)[d] = v;
+    });
+  else if (acc_in)  // else this slice of G
+    each([&](size_t d, float v) { gt[d] += v; });
+  else
+    each([&](size_t d, float v) { gt[d] = v; });
 }
 
 // dw from the K slices of G (each in dw's layout), added in slice order and
